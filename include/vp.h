@@ -191,6 +191,17 @@ int32_t vp_batch_layout(const vp_item* items, int32_t n_items, int32_t* grid_thw
                         int32_t* cu_seqlens, int64_t* total_rows, int64_t* workspace_bytes);
 
 /*
+ * Layout of a vp_patchify_batch call on items already at their target size:
+ * the rows are those of vp_batch_layout, the workspace the one that
+ * vp_patchify_batch and vp_position_ids need (no filter tables or work
+ * units; never more than vp_batch_layout's).
+ * total_rows, workspace_bytes: HOST; either may be NULL.
+ * Errors: as vp_patchify_batch's checks of the items.
+ */
+int32_t vp_patchify_layout(const vp_item* items, int32_t n_items, int64_t* total_rows,
+                           int64_t* workspace_bytes);
+
+/*
  * Diagnostic: the kernel launches that vp_preprocess_batch makes for a
  * batch, without running them (no device memory is touched): which form of
  * the resampling (Section 3.2: resize, normalise and patchify fused into one

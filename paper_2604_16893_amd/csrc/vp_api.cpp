@@ -1756,6 +1756,16 @@ int32_t vp_batch_layout(const vp_item* items, int32_t n_items, int32_t* grid_thw
     return VP_OK;
 }
 
+int32_t vp_patchify_layout(const vp_item* items, int32_t n_items, int64_t* total_rows,
+                           int64_t* workspace_bytes) {
+    std::shared_ptr<const Plan> plan;
+    const int32_t st = get_plan(PlanKind::kPatch, items, n_items, &plan);
+    if (st != VP_OK) return st;
+    if (total_rows) *total_rows = plan->total_rows;
+    if (workspace_bytes) *workspace_bytes = static_cast<int64_t>(plan->bytes);
+    return VP_OK;
+}
+
 int32_t vp_batch_kernels(const vp_item* items, int32_t n_items, int32_t* launches,
                          int32_t capacity, int32_t* n_launches) {
     if (n_launches == nullptr) return fail(VP_ERR_NULL, "n_launches is NULL");

@@ -441,3 +441,21 @@ def test_batch_kernels_capacity_truncates():
                                      ctypes.byref(n)) == vp.VP_OK
     assert n.value == len(full)
     assert rows[:2].tolist() == full[:2].tolist() and (rows[2] == -7).all()
+
+
+@pytest.mark.parametrize("patch", [16, 14])
+def test_patchify_layout_is_the_batch_layout_without_tables(patch):
+    """vp_patchify_layout: vp_batch_layout's rows, a workspace no larger,
+    and vp_patchify_batch's refusals of items that are not at their target."""
+    F = 2 * patch
+    items = [vp.Item((0x10000 * (k + 1), 5, h * F, w * F), list(range(n)), h * F, w * F, patch)
+             for k, (h, w, n) in enumerate([(1, 1, 1), (3, 7, 5), (8, 14, 4)])]
+    rows, ws = vp._layout(vp._Batch(items), "vp_patchify_layout")
+    _, _, rows_full, ws_full = vp.vp_batch_layout(items)
+    assert rows == rows_full and 0 < ws <= ws_full
+    for bad, status in ((vp.Item((0x10000, 2, F + 1, F), [0], F, F, patch), vp.VP_ERR_DIMS),
+                        (vp.Item((0x10001, 2, F, F), [0], F, F, patch), vp.VP_ERR_ARG),
+                        (vp.Item((0x10000, 2, F, F), [2], F, F, patch), vp.VP_ERR_INDEX)):
+        with pytest.raises(vp.VPError) as e:
+            vp._layout(vp._Batch(items + [bad]), "vp_patchify_layout")
+        assert e.value.status == status
