@@ -584,13 +584,45 @@ struct Keyed {
 // Output rows per streaming unit of an item: at most about max_src_rows
 // source rows, at least min_windows windows of source rows, a multiple of
 // `group` rows (the kernel's store group), and at least 16 rows (28 for
-// groups of 14).
-int64_t unit_row_band(const vp::DevItem& d, int64_t max_src_rows, int64_t group, int64_t min_windows = 10) {
+// groups of 14).  With short_rows > 0 (small batches, see short_unit_rows)
+// short_rows takes the place of both lower bounds.
+int64_t unit_row_band(const vp::DevItem& d, int64_t max_src_rows, int64_t group, int64_t min_windows = 10,
+                      int64_t short_rows = 0) {
     int64_t band = max_src_rows * d.h / d.H;
-    const int64_t min_band = (min_windows * d.ky * d.h + d.H - 1) / d.H;
+    const int64_t min_band = short_rows > 0 ? short_rows : (min_windows * d.ky * d.h + d.H - 1) / d.H;
+    const int64_t least = short_rows > 0 ? group : (group == 4 ? 16 : 2 * group);
     band = std::max(band, min_band);
-    band = std::max<int64_t>((band + group - 1) / group * group, group == 4 ? 16 : 2 * group);
+    band = std::max<int64_t>((band + group - 1) / group * group, least);
     return std::min<int64_t>(band, d.h);
+}
+
+// Output rows of the units of a small batch, or 0 where units of ten filter
+// windows are the better ones.  A unit is one wave's serial chain over its
+// source rows, about 0.35 us a row on an idle chip, so a batch that leaves
+// most wave slots empty lasts as long as one unit.  Shorter units re-read
+// more rows (from the caches, in a small batch).  `waves` gives the batch's
+// workgroups (waves) for units of a number of output rows; units of 16 rows
+// win up to `most` of them, where an x-first wave, whose rows are cheaper,
+// counts as 5/2 (`load`).  Measured, kernel us at ten windows
+// / 16 / 8 / 4 rows: 480p x 4 frames 29 / 17 / 13 / 14, 480p x 16
+// 31 / 22 / 24 / 28, 1080p x 2 52 / 26 / 19 / 17, 1080p x 32 77 / 67 / 70 / 86,
+// 1080p x 64 132 / 114 / 126 / 127, 720p x 128 134 / 134 / 138 / 137, 1080p x
+// 128 268 / 276 / 274 / 274; 480p x 64 in float32, x-first, 72 / 75 / 80 / 80.
+// So: 16 rows up to a load of 32,768 waves, and where that gives fewer than
+// 2,048 waves 8 rows, then 4.  Patch 14 stores whole patch
+// rows, 14 or 28 (ten windows / 28 / 14: 480p x 16 45 / 31 / 25, 480p x 64
+// 89 / 69 / 70, 720p x 64 92 / 82 / 86): 14 up to 10,240 waves.  The uint8
+// writer's forms re-read at a higher price (ten windows / 16: dot products
+// 720p x 64 108 / 99, 480p x 128 130 / 137; the matrix-core form, in chunks
+// of 16 source rows, 1080p x 8 62 / 42, 1080p x 32 104 / 113).
+constexpr int64_t kShortWaves = 32768, kShortWavesDot = 20480, kShortWavesMfma = 6144;
+
+template <class Waves, class Load>
+int64_t short_unit_rows(Waves waves, Load load, int64_t most, int32_t patch = 16) {
+    if (patch == 14 && waves(14) <= 10240) return 14;
+    if (load(16) > most) return 0;   // (patch 14 rounds 16 up to 28)
+    if (waves(16) >= 2048) return 16;
+    return waves(8) >= 1536 ? 8 : 4;
 }
 
 // A frame's h output rows cut into n = ceil(h / band) units whose boundaries
@@ -814,34 +846,33 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
     // tenth at ten windows -- but in a batch of few workgroups they end it
     // more evenly, which is worth more).
     constexpr int64_t kWaveSlots = 256 * 20;
+    std::vector<int64_t> distinct(n, 0);   // frames that item b streams: two per pair, one where they are one
     int64_t stream_frames = 0;
+    for (int32_t b = 0; b < n; ++b) {
+        const vp::DevItem& d = p->items[b];
+        if (d.route != vp::kRouteStream) continue;
+        const int32_t* ix = p->indices.data() + d.idx_off;
+        for (int32_t tt = 0; tt < d.t; ++tt) distinct[b] += ix[2 * tt] == ix[2 * tt + 1] ? 1 : 2;
+        stream_frames += distinct[b];
+    }
     auto source_row_cap = [&] {
         int64_t wave_rows = 0;   // source rows that all workgroups stream, whole frames
-        stream_frames = 0;
-        for (int32_t b = 0; b < n; ++b) {
-            const vp::DevItem& d = p->items[b];
-            if (d.route != vp::kRouteStream) continue;
-            for (int32_t tt = 0; tt < d.t; ++tt) {
-                const bool same = p->indices[d.idx_off + 2 * tt] == p->indices[d.idx_off + 2 * tt + 1];
-                wave_rows += int64_t(same ? 1 : 2) * shapes[b].bands * d.H;
-                stream_frames += same ? 1 : 2;
-            }
-        }
+        for (int32_t b = 0; b < n; ++b) wave_rows += distinct[b] * shapes[b].bands * p->items[b].H;
         return wave_rows / (kWaveSlots * 8);
     };
-    auto workgroup_waves = [&](int64_t min_windows, int64_t max_src_rows) {
+    auto workgroup_waves = [&](int64_t min_windows, int64_t max_src_rows, int64_t short_rows = 0,
+                               bool as_load = false) {
         int64_t waves = 0;
         for (int32_t b = 0; b < n; ++b) {
             const vp::DevItem& d = p->items[b];
             if (d.route != vp::kRouteStream) continue;
             const int64_t group = d.patch == 16 ? 4 : d.patch;
-            const int64_t units = UnitSplit(d.h, unit_row_band(d, max_src_rows, group, min_windows), group).n;
-            int64_t frames = 0;   // units per row band: one per distinct frame (patch 14: per pair)
-            for (int32_t tt = 0; tt < d.t; ++tt)
-                frames += d.patch == 14 || p->indices[d.idx_off + 2 * tt] == p->indices[d.idx_off + 2 * tt + 1]
-                              ? 1 : 2;
+            const int64_t units = UnitSplit(d.h, unit_row_band(d, max_src_rows, group, min_windows, short_rows), group).n;
+            // units per row band: one per distinct frame (patch 14: per pair)
+            const int64_t frames = d.patch == 14 ? d.t : distinct[b];
             const int64_t per_unit = d.patch == 14 ? 4 * ((shapes[b].bands + 1) / 2) : shapes[b].bands;
-            waves += frames * units * per_unit;
+            const int64_t w = frames * units * per_unit;
+            waves += as_load && shapes[b].px < 0 ? w * 5 / 2 : w;
         }
         return waves;
     };
@@ -865,46 +896,55 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
     }
     const int64_t max_src_rows = source_row_cap();
     const int64_t min_windows = workgroup_waves(15, max_src_rows) >= 4 * kWaveSlots ? 15 : 10;
-    std::vector<Keyed> keyed;
-    keyed.reserve(static_cast<size_t>(stream_frames));
-    for (int32_t b = 0; b < n; ++b) {
-        const vp::DevItem& d = p->items[b];
-        if (d.route != vp::kRouteStream) continue;
-        const StreamShape& sh = shapes[b];
-        // whole store groups: multiples of 4 rows for patch 16, whole
-        // patch rows (14 output rows, stored at once) for patch 14
-        const int64_t group = d.patch == 16 ? 4 : d.patch;
-        const UnitSplit split(d.h, unit_row_band(d, max_src_rows, group, min_windows), group);
-        for (int32_t tt = 0; tt < d.t; ++tt) {
-            const bool same = p->indices[d.idx_off + 2 * tt] == p->indices[d.idx_off + 2 * tt + 1];
-            const bool pair_units = d.patch == 14;   // both frames in one unit
-            for (int32_t dt = 0; dt < (same || pair_units ? 1 : 2); ++dt) {
-                for (int64_t u = 0; u < split.n; ++u) {
-                    const int32_t i0 = split.begin(u), i1 = split.end(u);
-                    Keyed k;
-                    k.key = std::make_tuple(sh.m, sh.kx, sh.px);
-                    k.bands = d.patch == 14 ? (sh.bands + 1) / 2 : sh.bands;   // patch 14: bands in pairs
-                    k.unit.item = b;
-                    k.unit.p_flags = (2 * tt + dt) | (same ? vp::kUnitBoth : 0);
-                    k.unit.i0 = i0;
-                    k.unit.i1 = i1;
-                    k.cost = int64_t(i1 - i0) * d.H / d.h * d.W   // source pixels read, roughly
-                             * (pair_units && !same ? 2 : 1);
-                    keyed.push_back(k);
+    const int64_t short_rows =
+        short_unit_rows([&](int64_t rows) { return workgroup_waves(10, max_src_rows, rows); },
+                        [&](int64_t rows) { return workgroup_waves(10, max_src_rows, rows, true); }, kShortWaves, P);
+    const auto lay_out = [&](int64_t short_rows) -> int32_t {
+        std::vector<Keyed> keyed;
+        keyed.reserve(static_cast<size_t>(stream_frames));
+        for (int32_t b = 0; b < n; ++b) {
+            const vp::DevItem& d = p->items[b];
+            if (d.route != vp::kRouteStream) continue;
+            const StreamShape& sh = shapes[b];
+            // whole store groups: multiples of 4 rows for patch 16, whole
+            // patch rows (14 output rows, stored at once) for patch 14
+            const int64_t group = d.patch == 16 ? 4 : d.patch;
+            const UnitSplit split(d.h, unit_row_band(d, max_src_rows, group, min_windows, short_rows), group);
+            for (int32_t tt = 0; tt < d.t; ++tt) {
+                const bool same = p->indices[d.idx_off + 2 * tt] == p->indices[d.idx_off + 2 * tt + 1];
+                const bool pair_units = d.patch == 14;   // both frames in one unit
+                for (int32_t dt = 0; dt < (same || pair_units ? 1 : 2); ++dt) {
+                    for (int64_t u = 0; u < split.n; ++u) {
+                        const int32_t i0 = split.begin(u), i1 = split.end(u);
+                        Keyed k;
+                        k.key = std::make_tuple(sh.m, sh.kx, sh.px);
+                        k.bands = d.patch == 14 ? (sh.bands + 1) / 2 : sh.bands;   // patch 14: bands in pairs
+                        k.unit.item = b;
+                        k.unit.p_flags = (2 * tt + dt) | (same ? vp::kUnitBoth : 0);
+                        k.unit.i0 = i0;
+                        k.unit.i1 = i1;
+                        k.cost = int64_t(i1 - i0) * d.H / d.h * d.W   // source pixels read, roughly
+                                 * (pair_units && !same ? 2 : 1);
+                        keyed.push_back(k);
+                    }
                 }
             }
         }
-    }
-    if (const int32_t st = assemble_launches(keyed, P, p); st != VP_OK) return st;
-
-    p->off_items = 0;
-    p->off_prefix = align_up(p->off_items + sizeof(vp::DevItem) * p->items.size());
-    p->off_indices = align_up(p->off_prefix + sizeof(int32_t) * p->prefix.size());
-    p->off_tables = align_up(p->off_indices + sizeof(int32_t) * p->indices.size());
-    p->off_units = align_up(p->off_tables + sizeof(int32_t) * p->table_words);
-    p->off_wgs = align_up(p->off_units + sizeof(vp::StreamUnit) * p->units.size());
-    p->bytes = align_up(p->off_wgs + sizeof(uint32_t) * p->wgs.size());
-    return VP_OK;
+        if (const int32_t st = assemble_launches(keyed, P, p); st != VP_OK) return st;
+        p->off_items = 0;
+        p->off_prefix = align_up(p->off_items + sizeof(vp::DevItem) * p->items.size());
+        p->off_indices = align_up(p->off_prefix + sizeof(int32_t) * p->prefix.size());
+        p->off_tables = align_up(p->off_indices + sizeof(int32_t) * p->indices.size());
+        p->off_units = align_up(p->off_tables + sizeof(int32_t) * p->table_words);
+        p->off_wgs = align_up(p->off_units + sizeof(vp::StreamUnit) * p->units.size());
+        p->bytes = align_up(p->off_wgs + sizeof(uint32_t) * p->wgs.size());
+        return VP_OK;
+    };
+    const int32_t st = lay_out(short_rows);
+    // (more units make a larger plan: one that no longer fits the no-alloc
+    // entry's plan memory keeps the longer units)
+    if (st == VP_OK && short_rows > 0 && p->bytes > static_cast<size_t>(vp::kNoAllocPlanBytes)) return lay_out(0);
+    return st;
 }
 
 // Plan of vp_patchify_batch: items whose frames are already at the target
@@ -1232,12 +1272,25 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
         if (d.route == vp::kRouteStream) wave_rows += int64_t(d.t) * shapes[b].bands * d.H;
     }
     const int64_t max_src_rows = wave_rows / (kWaveSlots * 8);
+    bool mfma = false;
+    for (int32_t b = 0; b < n; ++b)
+        mfma = mfma || (p->items[b].route == vp::kRouteStream && shapes[b].kx == vp::kRsMfmaWindow);
+    const auto unit_waves = [&](int64_t rows) {
+        int64_t waves = 0;
+        for (int32_t b = 0; b < n; ++b) {
+            const vp::DevItem& d = p->items[b];
+            if (d.route != vp::kRouteStream) continue;
+            waves += int64_t(d.t) * shapes[b].bands * UnitSplit(d.h, unit_row_band(d, max_src_rows, 4, 10, rows), 4).n;
+        }
+        return waves;
+    };
+    const int64_t short_rows = short_unit_rows(unit_waves, unit_waves, mfma ? kShortWavesMfma : kShortWavesDot);
     std::vector<Keyed> keyed;
     for (int32_t b = 0; b < n; ++b) {
         const vp::DevItem& d = p->items[b];
         if (d.route != vp::kRouteStream) continue;
         const StreamShape& sh = shapes[b];
-        const UnitSplit split(d.h, unit_row_band(d, max_src_rows, 4), 4);
+        const UnitSplit split(d.h, unit_row_band(d, max_src_rows, 4, 10, short_rows), 4);
         for (int32_t k = 0; k < d.t; ++k) {
             for (int64_t u = 0; u < split.n; ++u) {
                 const int32_t i0 = split.begin(u), i1 = split.end(u);
