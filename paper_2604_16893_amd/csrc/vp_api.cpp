@@ -268,19 +268,19 @@ int32_t build_slots(const AxisFilter& f, std::vector<int32_t>* words, bool fixed
     if (most > vp::kSlotWords) return -1;
     const int32_t m = most < 4 ? 4 : most;
     // close_row[n_out] and [n_out + 1]: never reached (kernels read one close row ahead)
-    words->assign(size_t(rows) * vp::kSlotWords + n_out + 2, 0);
-    (*words)[size_t(rows) * vp::kSlotWords + n_out] = INT32_MAX;
-    (*words)[size_t(rows) * vp::kSlotWords + n_out + 1] = INT32_MAX;
+    words->assign(size_t(rows) * m + n_out + 2, 0);
+    (*words)[size_t(rows) * m + n_out] = INT32_MAX;
+    (*words)[size_t(rows) * m + n_out + 1] = INT32_MAX;
     float* w = reinterpret_cast<float*>(words->data());
     for (int32_t i = 0; i < n_out; ++i)
         for (int32_t k = 0; k < f.count[i]; ++k) {
-            const size_t at = size_t(f.start[i] + k) * vp::kSlotWords + i % m;
+            const size_t at = size_t(f.start[i] + k) * m + i % m;
             if (fixed)
                 (*words)[at] = f.fixed[size_t(i) * f.taps + k];
             else
                 w[at] = f.weight[size_t(i) * f.taps + k] * kSlotScale;
         }
-    std::memcpy(words->data() + size_t(rows) * vp::kSlotWords, close.data(), sizeof(int32_t) * n_out);
+    std::memcpy(words->data() + size_t(rows) * m, close.data(), sizeof(int32_t) * n_out);
     return m;
 }
 
@@ -527,6 +527,13 @@ struct AxisEntry {
     std::vector<int32_t> words;         // the window table: start, count, weight
     std::vector<int32_t> fixed_words;   // the same with the fixed-point weights
 };
+// An axis of one plan: its cached tables, and where the plan holds them (-1:
+// not).  The streaming kernels read the window starts only; the whole window
+// table goes to the device for the general and the tile kernel.
+struct PlanAxis {
+    std::shared_ptr<const AxisEntry> entry;
+    int32_t windows = -1, starts = -1;
+};
 struct SlotEntry {
     int32_t m = -1;               // slots, or -1 if the axis needs too many
     std::vector<int32_t> words;
@@ -732,18 +739,15 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         p->tables.emplace_back(o, std::move(words));
         return o;
     };
-    std::map<std::pair<int32_t, int32_t>, std::pair<int32_t, std::shared_ptr<const AxisEntry>>> axes;
-    auto table_for = [&](int32_t n_in, int32_t n_out, int32_t* off) -> const AxisFilter* {
-        const auto key = std::make_pair(n_in, n_out);
-        auto found = axes.find(key);
-        if (found == axes.end()) {
-            auto e = cached(g_axis_cache, key, [&] { return make_axis_entry(n_in, n_out); });
-            const int32_t o = append(std::shared_ptr<const std::vector<int32_t>>(e, &e->words));
-            found = axes.emplace(key, std::make_pair(o, e)).first;
-        }
-        *off = found->second.first;
-        return &found->second.second->f;
+    std::map<std::pair<int32_t, int32_t>, PlanAxis> axes;
+    auto axis_for = [&](int32_t n_in, int32_t n_out) -> PlanAxis& {
+        PlanAxis& a = axes[std::make_pair(n_in, n_out)];
+        if (a.entry == nullptr)
+            a.entry = cached(g_axis_cache, std::make_pair(n_in, n_out), [&] { return make_axis_entry(n_in, n_out); });
+        return a;
     };
+    auto window_table = [&](PlanAxis& a) { return a.windows >= 0 ? a.windows : a.windows = append({a.entry, &a.entry->words}); };
+    auto start_table = [&](PlanAxis& a) { return a.starts >= 0 ? a.starts : a.starts = append({a.entry, &a.entry->f.start}); };
     std::map<SlotKey, std::pair<int32_t, std::shared_ptr<const SlotEntry>>> slot_tables;
     auto slots_for = [&](const AxisFilter& f, int32_t* off, int32_t* m) -> bool {
         const SlotKey key = std::make_tuple(f.n_in, f.n_out, false);
@@ -797,8 +801,10 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         d.idx_off = static_cast<int32_t>(p->indices.size());
         for (int32_t k = 0; k < 2 * d.t; ++k)
             p->indices.push_back(it.indices[k < it.n_idx ? k : it.n_idx - 1]);
-        const AxisFilter* fy = table_for(it.src_h, it.dst_h, &d.ty_off);
-        const AxisFilter* fx = table_for(it.src_w, it.dst_w, &d.tx_off);
+        PlanAxis& ay = axis_for(it.src_h, it.dst_h);
+        PlanAxis& ax = axis_for(it.src_w, it.dst_w);
+        const AxisFilter* fy = &ay.entry->f;
+        const AxisFilter* fx = &ax.entry->f;
         d.ky = fy->taps;
         d.kx = fx->taps;
         d.route = vp::kRouteGeneric;
@@ -814,6 +820,8 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
             return fail(VP_ERR_CAPACITY, "item " + std::to_string(b) +
                                              ": horizontal filter window too long (downscale too large)");
         }
+        d.ty_off = d.route == vp::kRouteStream ? start_table(ay) : window_table(ay);
+        d.tx_off = d.route == vp::kRouteStream ? start_table(ax) : window_table(ax);
         d.row_off = rows;
         const int64_t item_rows = int64_t(d.t) * (it.dst_h / P) * (it.dst_w / P);
         p->grid[3 * b + 0] = d.t;
@@ -1132,24 +1140,21 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
     p->wgs.clear();
     p->launches.clear();
     p->generic_cost = 0;
-    std::map<std::pair<int32_t, int32_t>, std::pair<int32_t, std::shared_ptr<const AxisEntry>>> axes;
     auto append = [&](std::shared_ptr<const std::vector<int32_t>> words) -> int32_t {
         const int32_t o = static_cast<int32_t>(p->table_words);
         p->table_words += words->size();
         p->tables.emplace_back(o, std::move(words));
         return o;
     };
-    auto table_for = [&](int32_t n_in, int32_t n_out, int32_t* off) -> const AxisFilter* {
-        const auto key = std::make_pair(n_in, n_out);
-        auto found = axes.find(key);
-        if (found == axes.end()) {
-            auto e = cached(g_axis_cache, key, [&] { return make_axis_entry(n_in, n_out); });
-            const int32_t o = append(std::shared_ptr<const std::vector<int32_t>>(e, &e->fixed_words));
-            found = axes.emplace(key, std::make_pair(o, e)).first;
-        }
-        *off = found->second.first;
-        return &found->second.second->f;
+    std::map<std::pair<int32_t, int32_t>, PlanAxis> axes;
+    auto axis_for = [&](int32_t n_in, int32_t n_out) -> PlanAxis& {
+        PlanAxis& a = axes[std::make_pair(n_in, n_out)];
+        if (a.entry == nullptr)
+            a.entry = cached(g_axis_cache, std::make_pair(n_in, n_out), [&] { return make_axis_entry(n_in, n_out); });
+        return a;
     };
+    auto window_table = [&](PlanAxis& a) { return a.windows >= 0 ? a.windows : a.windows = append({a.entry, &a.entry->fixed_words}); };
+    auto start_table = [&](PlanAxis& a) { return a.starts >= 0 ? a.starts : a.starts = append({a.entry, &a.entry->f.start}); };
     std::map<SlotKey, std::pair<int32_t, std::shared_ptr<const SlotEntry>>> slot_tables;
     auto slots_for = [&](const AxisFilter& f, int32_t* off, int32_t* m) -> bool {
         const SlotKey key = std::make_tuple(f.n_in, f.n_out, true);
@@ -1213,8 +1218,10 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
         d.t = it.n_idx;
         d.idx_off = static_cast<int32_t>(p->indices.size());
         p->indices.insert(p->indices.end(), it.indices, it.indices + it.n_idx);
-        const AxisFilter* fy = table_for(it.src_h, it.dst_h, &d.ty_off);
-        const AxisFilter* fx = table_for(it.src_w, it.dst_w, &d.tx_off);
+        PlanAxis& ay = axis_for(it.src_h, it.dst_h);
+        PlanAxis& ax = axis_for(it.src_w, it.dst_w);
+        const AxisFilter* fy = &ay.entry->f;
+        const AxisFilter* fx = &ax.entry->f;
         d.ky = fy->taps;
         d.kx = fx->taps;
         d.patch = P;
@@ -1256,6 +1263,8 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
             tiles += int64_t(it.n_idx) * d.hm * d.wm;
             p->generic_cost += int64_t(8) * it.n_idx * it.src_h * it.src_w;   // about 8x the streaming cost per pixel
         }
+        d.ty_off = d.route == vp::kRouteStream ? start_table(ay) : window_table(ay);
+        d.tx_off = d.route == vp::kRouteStream ? start_table(ax) : window_table(ax);
         if (tiles > INT32_MAX) return fail(VP_ERR_CAPACITY, "batch has more than 2^31-1 tiles");
         p->byte_off[b + 1] = bytes;
         p->prefix[b + 1] = static_cast<int32_t>(tiles);
@@ -1387,9 +1396,10 @@ int32_t get_plan(PlanKind kind, const vp_item* items, int32_t n, std::shared_ptr
 }
 
 // ---------------------------------------------------------------------------
-// Pinned staging ring: the plan blob is written into pinned host memory and
-// copied asynchronously; a slot is reused only after the copy that read it
-// has completed.
+// Pinned staging ring: the plan blob is written into pinned host memory,
+// from where a kernel on the call's stream copies it; a slot is reused only
+// after the kernel that read it has completed.  (Coherent memory: the kernel
+// must see what the host wrote since the slot's last use.)
 // ---------------------------------------------------------------------------
 
 struct Slot {
@@ -1460,13 +1470,16 @@ int32_t upload_plan(const Plan& p, void* workspace, hipStream_t stream) {
         s.host = nullptr;
         s.cap = 0;
         size_t cap = align_up(p.bytes * 2);
-        e = hipHostMalloc(&s.host, cap, hipHostMallocDefault);
+        e = hipHostMalloc(&s.host, cap, hipHostMallocCoherent);
         if (e != hipSuccess) return hip_fail(e, "hipHostMalloc");
         s.cap = cap;
     }
     pack_plan(p, static_cast<uint8_t*>(s.host));
-    e = hipMemcpyAsync(workspace, s.host, p.bytes, hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
+    void* src = nullptr;
+    e = hipHostGetDevicePointer(&src, s.host, 0);
+    if (e != hipSuccess) return hip_fail(e, "hipHostGetDevicePointer");
+    const int err = vp::launch_upload(workspace, src, static_cast<int64_t>(p.bytes), stream);
+    if (err != 0) return hip_fail(static_cast<hipError_t>(err), "plan upload launch");
     e = hipEventRecord(s.done, stream);
     if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
     s.pending = true;

@@ -97,6 +97,27 @@ __device__ __forceinline__ int find_item(const int32_t* prefix, int n_items, int
 }
 
 // ===========================================================================
+// Plan upload
+// ===========================================================================
+
+// The plan blob from pinned host memory to the workspace, 64 bytes a thread
+// with its four loads in flight: a small plan costs the host link's latency
+// (about 2 us), a large one its rate.  A kernel and not hipMemcpyAsync: the
+// copy engine's hand-over on both sides left the chip idle for about 10 us a
+// call (one photo 33 -> 23 us a call, a 480p clip 90 -> 80).
+__global__ __launch_bounds__(kUploadThreads) void upload_kernel(uint4* __restrict__ dst,
+                                                                const uint4* __restrict__ src, int n16) {
+    const int i0 = blockIdx.x * (4 * kUploadThreads) + threadIdx.x;
+    uint4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (i0 + k * kUploadThreads < n16) v[k] = src[i0 + k * kUploadThreads];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (i0 + k * kUploadThreads < n16) dst[i0 + k * kUploadThreads] = v[k];
+}
+
+// ===========================================================================
 // General kernel
 // ===========================================================================
 
@@ -675,8 +696,8 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
     const cptr<int32_t> xs = tables + it->tx_off;   // window starts of the x axis
     const int x0 = xs[j0];                          // first source pixel of the band
     const cptr<int32_t> ys = tables + it->ty_off;
-    const cptr<float> slot_w = (cptr<float>)(tables + it->sy_off);             // [H + 6][8]
-    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * kSlotWords;  // [h]
+    const cptr<float> slot_w = (cptr<float>)(tables + it->sy_off);             // [H + 6][M]
+    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * M;  // [h]
 
     // Source frame, read through buffer resources (loads past a resource's
     // range return 0).  Every load is dword-aligned: unaligned per-lane
@@ -981,12 +1002,12 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
         // wait for scalar loads per block, not per row (a block starts at a
         // row below H and the table has kSlotMax rows past the frame's
         // last, so all four rows are inside it)
-        const cptr<float> wblk = slot_w + yb * kSlotWords;
+        const cptr<float> wblk = slot_w + yb * M;
         float wk[kPrefetch][M];
 #pragma unroll
         for (int k = 0; k < kPrefetch; ++k)
 #pragma unroll
-            for (int s = 0; s < M; ++s) wk[k][s] = wblk[k * kSlotWords + s];
+            for (int s = 0; s < M; ++s) wk[k][s] = wblk[k * M + s];
 #pragma unroll
         for (int k = 0; k < kPrefetch; ++k) {
             const int y = yb + k;
@@ -1133,7 +1154,7 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
     const int x0 = xs[j0];                         // first source pixel of the band
     const cptr<int32_t> ys = tables + it->ty_off;
     const cptr<float> slot_w = (cptr<float>)(tables + it->sy_off);
-    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * kSlotWords;
+    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * M;
 
     // Source frame through buffer resources, as in the y-first kernel: row
     // blocks of four start at a multiple of 4 rows, so each block's offset
@@ -1367,12 +1388,12 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
         __builtin_amdgcn_sched_barrier(0);
     }
     for (int yb = yb0; yb < y1; yb += 4) {
-        const cptr<float> wblk = slot_w + yb * kSlotWords;
+        const cptr<float> wblk = slot_w + yb * M;
         float wk[4][M];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int s = 0; s < M; ++s) wk[k][s] = wblk[k * kSlotWords + s];
+            for (int s = 0; s < M; ++s) wk[k][s] = wblk[k * M + s];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int y = yb + k;
@@ -1480,8 +1501,8 @@ __global__ __launch_bounds__(64) void resize_stream_kernel(PlanView plan, int wg
     const cptr<int32_t> xs = tables + it->tx_off;
     const int x0 = xs[j0];
     const cptr<int32_t> ys = tables + it->ty_off;
-    const cptr<int32_t> slot_q = tables + it->sy_off;                                       // [H + 6][8]
-    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * kSlotWords;  // [h]
+    const cptr<int32_t> slot_q = tables + it->sy_off;                                       // [H + 6][M]
+    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * M;  // [h]
 
     // the frame through buffer resources, as in the float kernel
     const int f = as_const(plan.indices)[it->idx_off + u_k];
@@ -1621,12 +1642,12 @@ __global__ __launch_bounds__(64) void resize_stream_kernel(PlanView plan, int wg
     for (int yb = yb0; yb < y1; yb += kPrefetch) {
         // the block's slot weights, read together (a block starts below H,
         // and the table has kSlotMax rows past the frame's last)
-        const cptr<int32_t> wblk = slot_q + yb * kSlotWords;
+        const cptr<int32_t> wblk = slot_q + yb * M;
         int32_t wk[kPrefetch][M];
 #pragma unroll
         for (int k = 0; k < kPrefetch; ++k)
 #pragma unroll
-            for (int s = 0; s < M; ++s) wk[k][s] = wblk[k * kSlotWords + s];
+            for (int s = 0; s < M; ++s) wk[k][s] = wblk[k * M + s];
 #pragma unroll
         for (int k = 0; k < kPrefetch; ++k) {
             const int y = yb + k;
@@ -1693,7 +1714,7 @@ __global__ __launch_bounds__(64) void resize_mfma_kernel(PlanView plan, int wg0,
     }
     const cptr<int32_t> ys = tables + it->ty_off;
     const cptr<int32_t> slot_q = tables + it->sy_off;
-    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * kSlotWords;
+    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * M;
 
     // the frame through one buffer resource (loads past it return zeros)
     const int f = as_const(plan.indices)[it->idx_off + u_k];
@@ -1787,7 +1808,7 @@ __global__ __launch_bounds__(64) void resize_mfma_kernel(PlanView plan, int wg0,
 #pragma unroll
         for (int c = 0; c < 3; ++c) hv[c] = *reinterpret_cast<const uint4*>(hbuf + c * 1024 + lane * 16);
         wave_lds_fence();
-        const cptr<int32_t> wblk = slot_q + yc * kSlotWords;
+        const cptr<int32_t> wblk = slot_q + yc * M;
         int32_t wk[4][M];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -1798,7 +1819,7 @@ __global__ __launch_bounds__(64) void resize_mfma_kernel(PlanView plan, int wg0,
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
 #pragma unroll
-                    for (int s = 0; s < M; ++s) wk[k][s] = wblk[(r + k) * kSlotWords + s];
+                    for (int s = 0; s < M; ++s) wk[k][s] = wblk[(r + k) * M + s];
             }
             if (y < y0 || y >= y1) continue;   // wave-uniform
             const uint32_t dw = r >> 2;
@@ -2031,6 +2052,15 @@ int noalloc_plan_memory(void** ptr) {
     }
     *ptr = it->second;
     return 0;
+}
+
+int launch_upload(void* dst, const void* src, int64_t bytes, hipStream_t stream) {
+    if (bytes <= 0) return 0;
+    if (bytes % 16 != 0 || bytes / 16 > INT32_MAX) return static_cast<int>(hipErrorInvalidValue);
+    const int n16 = static_cast<int>(bytes / 16);
+    hipLaunchKernelGGL(upload_kernel, dim3((n16 + 4 * kUploadThreads - 1) / (4 * kUploadThreads)),
+                       dim3(kUploadThreads), 0, stream, static_cast<uint4*>(dst), static_cast<const uint4*>(src), n16);
+    return static_cast<int>(hipGetLastError());
 }
 
 int launch_positions(const PlanView& plan, int32_t* vit, int32_t* llm, int64_t rows,

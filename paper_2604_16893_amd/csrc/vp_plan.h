@@ -2,7 +2,7 @@
 //
 // The host planner (vp_api.cpp) validates the items, computes their filter
 // tables, work units and row offsets, packs everything into one blob and
-// copies it into the caller's workspace with a single async copy; the
+// copies it into the caller's workspace on the call's stream; the
 // kernels (vp_kernels.hip) read it from there.  Layout of the blob, each
 // section aligned to 256 bytes:
 //   DevItem    items[n_items]
@@ -16,8 +16,9 @@
 // Tables (word offsets into `tables`; items with the same axis share them):
 //   window table of an axis n_in -> n_out, K taps:
 //       int32 start[n_out]; int32 count[n_out]; float weight[n_out][K]
+//     (an axis that only streaming kernels use: the starts alone)
 //   slot table of a y axis n_in -> n_out (streaming kernel), M slots:
-//       [n_in + 6] rows of 8 words: float weight[slot]   (slots >= M zero)
+//       [n_in + 6] rows of M words: float weight[slot]
 //         -- output row i is accumulated in slot i mod M from the first row of
 //            its window to its close row; weight[s] is 2^24 times the weight
 //            of source row y in the output row that has slot s at y, or zero
@@ -51,7 +52,7 @@ constexpr int kRow = 1536;            // 3 * 2 * 16 * 16
 constexpr int kWinElems = 4 * kRow;   // one merge window of one frame pair
 constexpr int kGenericThreads = 256;
 constexpr int kGenericTCap = 8192;    // floats of the general kernel's LDS column tile
-constexpr int kSlotWords = 8;         // words per source row of a slot table
+constexpr int kSlotWords = 8;         // most slots of a slot table
 constexpr int kSlotMax = 6;           // most output rows open at once (accumulator slots)
 constexpr int kStreamLdsBudget = 64 * 1024;   // LDS of one streaming workgroup (one wave)
 
@@ -175,6 +176,10 @@ constexpr int64_t kNoAllocPlanBytes = int64_t(16) << 20;
 int noalloc_plan_memory(void** ptr);
 
 // Kernel launchers (vp_kernels.hip).  Return a hipError_t value.
+// The plan blob, `bytes` (a multiple of 16, both ends 16-byte aligned) from
+// host memory the device can read.
+constexpr int kUploadThreads = 256;
+int launch_upload(void* dst, const void* src, int64_t bytes, hipStream_t stream);
 int launch_generic(const PlanView& plan, void* out, int out_dtype, const Norm& norm,
                    hipStream_t stream);
 int launch_stream(const PlanView& plan, const StreamLaunch& launch, void* out, int out_dtype,
