@@ -461,75 +461,97 @@ __global__ __launch_bounds__(256) void patchify_kernel(PlanView plan, void* out,
 }
 
 // The same for patches of 14 (Qwen2/2.5-VL geometry: windows of 28, rows of
-// 1176).  Wave (dt, mh) as above; lane l < 56 owns one patch row, P = 14
-// pixels (42 bytes): row y = l % 14 of patch mw = (l / 14) & 1 in window
-// bw = 2 * step + (l / 28).  A patch row can start off a dword boundary, so
-// the lane loads the 12 dwords that cover it from any offset (42 bytes plus
-// up to 3) through a buffer resource (range-checked at the frame's end) and
-// aligns them with v_alignbyte.  Per channel its 14 values are one contiguous run of
-// the output row (4-byte aligned for bf16, 8-byte for float32).
+// 1176).  A patch row is 14 values, 28 or 56 bytes of output: stored lane by
+// lane from its pixels, every 128-byte line was written in parts.  But the
+// rows of a merge-window row are one contiguous run of output, so a workgroup
+// (2 windows of a merge-window row of a pair in float32, 3 in bf16) stages
+// its pixels in LDS as bytes -- 12-byte loads, four pixels each; rows of whole
+// windows are multiples of 84 bytes, so every load is dword aligned -- and
+// its lanes write consecutive 16-byte pieces, each gathering its values' bytes
+// from LDS.  Groups of four values never cross one of the 14 x 14 planes
+// (196 = 4 x 49), only their patch rows.  Bound by HBM, two thirds of it or
+// more stores.  Measured, 512 frames of 336x588: float32 449 -> 262 us (5.8
+// TB/s; 1, 3, 4, 6 windows 264, 271, 307, 311), bf16 253 -> 178 us (5.1 TB/s;
+// 1, 2, 4, 6 windows 261, 204, 194, 201).  The plan lists chunks of
+// kPatch14Chunk windows, each of which is kPatch14Chunk / NW workgroups.
 template <int OUT_BF16>
-__global__ __launch_bounds__(256) void patchify14_kernel(PlanView plan, void* out, Norm norm) {
-    using elem_t = typename std::conditional<OUT_BF16 != 0, uint16_t, float>::type;
-    constexpr int P = 14;
-    constexpr int kRowLen = 6 * P * P;   // 1176
-    const int tile = blockIdx.x;
+__global__ __launch_bounds__(256) void patchify14_kernel(PlanView plan, int tile0, void* out, Norm norm) {
+    constexpr int P = 14, NW = patch14_windows(OUT_BF16);
+    static_assert(kPatch14Chunk % NW == 0, "a chunk is a whole number of workgroups");
+    constexpr int kParts = kPatch14Chunk / NW;
+    constexpr int kRowB = NW * 6 * P;               // LDS bytes per pixel row
+    constexpr int kFrameB = 2 * P * kRowB;          // per frame: 28 pixel rows
+    constexpr int kPlane = P * P, kRowLen = 6 * kPlane, kWin = 4 * kRowLen;
+    constexpr int VPP = OUT_BF16 ? 8 : 4;           // values per 16-byte piece
+    static_assert(kPlane % 4 == 0 && kRowLen % VPP == 0, "pieces are whole groups of four values of a plane");
+    __shared__ __align__(16) uint8_t px[2 * kFrameB];
+    const int tile = tile0 + blockIdx.x / kParts;
     const int b = find_item(plan.tile_prefix, plan.n_items, tile);
     const cptr<DevItem> it = as_const(plan.items) + b;
+    const int hm = it->hm, wm = it->wm;
+    const int chunks = (wm + kPatch14Chunk - 1) / kPatch14Chunk;
     const int local = tile - plan.tile_prefix[b];
-    const int hm = it->hm, wm = it->wm, w = it->w;
-    const int bh = local % hm;
-    const int tt = local / hm;
-    const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
-    const int dt = wv >> 1, mh = wv & 1;
-    if (lane >= 4 * P) return;   // no barrier follows
-    const int y = lane % P, mw = (lane / P) & 1, par = lane / (2 * P);
-    const int f = as_const(plan.indices)[it->idx_off + 2 * tt + dt];
-    const uintptr_t fa = reinterpret_cast<uintptr_t>(it->frames + int64_t(f) * it->frame_bytes);
-    const uint32_t lead = static_cast<uint32_t>(fa & 3u);
-    const uint32_t range = static_cast<uint32_t>((it->frame_bytes + lead + 3) & ~int64_t(3));
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        reinterpret_cast<void*>(fa - lead), (short)0, static_cast<int>(range), 0x00020000);
-    const uint32_t row_byte0 = lead + static_cast<uint32_t>((2 * P * bh + P * mh + y) * w) * 3u;
-    const float a[3] = {norm.a[0], norm.a[1], norm.a[2]};
-    const float z[3] = {norm.z[0], norm.z[1], norm.z[2]};
-    const int64_t row_base = it->row_off + (int64_t(tt) * hm + bh) * wm * 4 + mh * 2 + mw;
+    const int bw0 = local % chunks * kPatch14Chunk + blockIdx.x % kParts * NW;
+    if (bw0 >= wm) return;   // (the whole workgroup: the barrier below is not split)
+    const int bh = local / chunks % hm;
+    const int tt = local / chunks / hm;
+    const int nw = min(NW, wm - bw0);
+    const int tid = threadIdx.x;
+    const int64_t row_bytes = int64_t(it->w) * 3;
+    const int64_t first = int64_t(2 * P * bh) * row_bytes + int64_t(bw0) * (6 * P);   // of the chunk, in a frame
+    const cptr<int32_t> pair = as_const(plan.indices) + it->idx_off + 2 * tt;
+    const uint8_t* const src0 = it->frames + int64_t(pair[0]) * it->frame_bytes + first;
+    const uint8_t* const src1 = it->frames + int64_t(pair[1]) * it->frame_bytes + first;
+    struct Px4 {
+        uint32_t d[3];
+    };
+    const int per_row = 7 * nw;                     // loads of four pixels per row of the chunk
+    for (int e = tid; e < 4 * P * per_row; e += 256) {
+        const int r = e / per_row, k = e - r * per_row;
+        const int dt = r >= 2 * P, y = r - dt * 2 * P;
+        const Px4 v = *reinterpret_cast<const Px4*>((dt ? src1 : src0) + y * row_bytes + 12 * k);
+        *reinterpret_cast<Px4*>(px + dt * kFrameB + y * kRowB + 12 * k) = v;
+    }
+    __syncthreads();
 
-    for (int bw = par; bw < wm; bw += 2) {
-        const uint32_t o = row_byte0 + static_cast<uint32_t>(2 * P * bw + P * mw) * 3u;
-        const uint32_t sh = o & 3u;
-        uint32_t d[12];
+    using elem_t = typename std::conditional<OUT_BF16 != 0, uint16_t, float>::type;
+    elem_t* const dst = static_cast<elem_t*>(out) +
+                        (it->row_off + ((int64_t(tt) * hm + bh) * wm + bw0) * 4) * kRowLen;
+    const float a0 = norm.a[0], a1 = norm.a[1], a2 = norm.a[2];
+    const float z0 = norm.z[0], z1 = norm.z[1], z2 = norm.z[2];
+    for (int e = tid; e < nw * (kWin / VPP); e += 256) {
+        const int v0 = e * VPP;
+        const int bw = v0 / kWin, in_win = v0 - bw * kWin;
+        const int sub = in_win / kRowLen, in_row = in_win - sub * kRowLen;
+        const uint8_t* const patch = px + (sub >> 1) * (P * kRowB) + bw * (6 * P) + (sub & 1) * (3 * P);
+        float v[VPP];
 #pragma unroll
-        for (int k = 0; k < 12; ++k)
-            d[k] = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (o & ~3u) + 4u * k, 0, 0));
-        uint32_t bytes[11];   // the patch row's 42 bytes from byte 0
+        for (int g = 0; g < VPP; g += 4) {
+            const int plane = (in_row + g) / kPlane, k = in_row + g - plane * kPlane;
+            const int c = plane >> 1, y = k / P, x = k - y * P;
+            const float a = c == 0 ? a0 : (c == 1 ? a1 : a2), z = c == 0 ? z0 : (c == 1 ? z1 : z2);
+            const uint8_t* const q = patch + (plane & 1) * kFrameB + y * kRowB + 3 * x + c;
 #pragma unroll
-        for (int k = 0; k < 11; ++k) bytes[k] = __builtin_amdgcn_alignbyte(d[k + 1], d[k], sh);
-        elem_t* dst = static_cast<elem_t*>(out) + (row_base + int64_t(bw) * 4) * kRowLen + (dt * P + y) * P;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            float v[P];
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                const int byte = 3 * q + c;
-                v[q] = (float((bytes[byte >> 2] >> (8 * (byte & 3))) & 255u) + z[c]) * a[c];
-            }
-            elem_t* dc = dst + c * 2 * P * P;
-            if constexpr (OUT_BF16 != 0) {
-                using f2 = float __attribute__((ext_vector_type(2)));
-                using b2 = __bf16 __attribute__((ext_vector_type(2)));
-#pragma unroll
-                for (int e = 0; e < P / 2; ++e) {
-                    const f2 pr = {v[2 * e], v[2 * e + 1]};
-                    reinterpret_cast<uint32_t*>(dc)[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, b2));
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < P / 2; ++e)
-                    reinterpret_cast<float2*>(dc)[e] = make_float2(v[2 * e], v[2 * e + 1]);
+            for (int i = 0; i < 4; ++i) {
+                const int at = 3 * i + (x + i >= P ? kRowB - 3 * P : 0);   // the next patch row
+                v[g + i] = (float(q[at]) + z) * a;
             }
         }
+        using u4v = unsigned __attribute__((ext_vector_type(4)));
+        u4v pk;
+        if constexpr (OUT_BF16 != 0) {
+            using f2 = float __attribute__((ext_vector_type(2)));
+            using b2 = __bf16 __attribute__((ext_vector_type(2)));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f2 pr = {v[2 * i], v[2 * i + 1]};
+                pk[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, b2));   // RNE
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) pk[i] = __float_as_uint(v[i]);
+        }
+        __builtin_nontemporal_store(pk, reinterpret_cast<u4v*>(dst + v0));
     }
 }
 
@@ -2098,10 +2120,16 @@ int launch_patchify(const PlanView& plan, void* out, int out_dtype, const Norm& 
     if (plan.n_tiles <= 0) return 0;
     dim3 grid(plan.n_tiles), block(256);
     if (patch == 14) {
-        if (out_dtype == 1)
-            hipLaunchKernelGGL(patchify14_kernel<1>, grid, block, 0, stream, plan, out, norm);
-        else
-            hipLaunchKernelGGL(patchify14_kernel<0>, grid, block, 0, stream, plan, out, norm);
+        // (a launch holds fewer than 2^24 workgroups of 256)
+        const int parts = kPatch14Chunk / patch14_windows(out_dtype == 1);
+        constexpr int kMost = 1 << 22;
+        for (int t0 = 0; t0 < plan.n_tiles; t0 += kMost) {
+            grid.x = static_cast<unsigned>(std::min(kMost, plan.n_tiles - t0) * parts);
+            if (out_dtype == 1)
+                hipLaunchKernelGGL(patchify14_kernel<1>, grid, block, 0, stream, plan, t0, out, norm);
+            else
+                hipLaunchKernelGGL(patchify14_kernel<0>, grid, block, 0, stream, plan, t0, out, norm);
+        }
     } else if (out_dtype == 1) {
         hipLaunchKernelGGL(patchify_kernel<1>, grid, block, 0, stream, plan, out, norm);
     } else {
