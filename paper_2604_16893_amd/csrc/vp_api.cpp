@@ -956,8 +956,8 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
 }
 
 // Plan of vp_patchify_batch: items whose frames are already at the target
-// size; one workgroup per merge-window row (32 pixel rows) of a frame pair,
-// for patch 14 per kPatch14Chunk windows of one.
+// size; one workgroup per merge-window row (32 pixel rows) of a frame pair
+// (patch 14 counts merge windows: its workgroups take a few of the batch's).
 int32_t build_patch_plan(const vp_item* items, int32_t n, Plan* p) {
     if (items == nullptr) return fail(VP_ERR_NULL, "items is NULL");
     if (n < 1) return fail(VP_ERR_ARG, "n_items < 1");
@@ -1002,7 +1002,7 @@ int32_t build_patch_plan(const vp_item* items, int32_t n, Plan* p) {
         p->grid[3 * b + 1] = it.dst_h / P;
         p->grid[3 * b + 2] = it.dst_w / P;
         rows += int64_t(d.t) * (it.dst_h / P) * (it.dst_w / P);
-        tiles += int64_t(d.t) * d.hm * (P == 14 ? (d.wm + vp::kPatch14Chunk - 1) / vp::kPatch14Chunk : 1);
+        tiles += int64_t(d.t) * d.hm * (P == 14 ? d.wm : 1);   // patch 14: merge windows
         if (rows > INT32_MAX || tiles > INT32_MAX)
             return fail(VP_ERR_CAPACITY, "batch has more than 2^31-1 rows");
         p->cu[b + 1] = static_cast<int32_t>(rows);

@@ -463,67 +463,70 @@ __global__ __launch_bounds__(256) void patchify_kernel(PlanView plan, void* out,
 // The same for patches of 14 (Qwen2/2.5-VL geometry: windows of 28, rows of
 // 1176).  A patch row is 14 values, 28 or 56 bytes of output: stored lane by
 // lane from its pixels, every 128-byte line was written in parts.  But the
-// rows of a merge-window row are one contiguous run of output, so a workgroup
-// (2 windows of a merge-window row of a pair in float32, 3 in bf16) stages
-// its pixels in LDS as bytes -- 12-byte loads, four pixels each; rows of whole
+// four rows of a merge window, and the windows of the whole batch one after
+// another, are one contiguous run of output.  So a workgroup takes NW
+// consecutive windows of the batch (2 in float32, 3 in bf16), stages their
+// pixels in LDS as bytes -- 12-byte loads, four pixels each; rows of whole
 // windows are multiples of 84 bytes, so every load is dword aligned -- and
 // its lanes write consecutive 16-byte pieces, each gathering its values' bytes
 // from LDS.  Groups of four values never cross one of the 14 x 14 planes
 // (196 = 4 x 49), only their patch rows.  Bound by HBM, two thirds of it or
 // more stores.  Measured, 512 frames of 336x588: float32 449 -> 262 us (5.8
-// TB/s; 1, 3, 4, 6 windows 264, 271, 307, 311), bf16 253 -> 178 us (5.1 TB/s;
-// 1, 2, 4, 6 windows 261, 204, 194, 201).  The plan lists chunks of
-// kPatch14Chunk windows, each of which is kPatch14Chunk / NW workgroups.
+// TB/s; with 1, 3, 4, 6 windows 264, 271, 307, 311), bf16 253 -> 174 us (5.3
+// TB/s; 1, 2, 4, 6 windows 261, 204, 194, 201).  Loading window by window,
+// also where they lie side by side, took bf16 195 us.
 template <int OUT_BF16>
-__global__ __launch_bounds__(256) void patchify14_kernel(PlanView plan, int tile0, void* out, Norm norm) {
+__global__ __launch_bounds__(256) void patchify14_kernel(PlanView plan, int block0, void* out, Norm norm) {
     constexpr int P = 14, NW = patch14_windows(OUT_BF16);
-    static_assert(kPatch14Chunk % NW == 0, "a chunk is a whole number of workgroups");
-    constexpr int kParts = kPatch14Chunk / NW;
-    constexpr int kRowB = NW * 6 * P;               // LDS bytes per pixel row
+    constexpr int kWinB = 6 * P;                    // bytes per pixel row of a window
+    constexpr int kRowB = NW * kWinB;               // LDS: the windows side by side
     constexpr int kFrameB = 2 * P * kRowB;          // per frame: 28 pixel rows
     constexpr int kPlane = P * P, kRowLen = 6 * kPlane, kWin = 4 * kRowLen;
     constexpr int VPP = OUT_BF16 ? 8 : 4;           // values per 16-byte piece
     static_assert(kPlane % 4 == 0 && kRowLen % VPP == 0, "pieces are whole groups of four values of a plane");
     __shared__ __align__(16) uint8_t px[2 * kFrameB];
-    const int tile = tile0 + blockIdx.x / kParts;
-    const int b = find_item(plan.tile_prefix, plan.n_items, tile);
-    const cptr<DevItem> it = as_const(plan.items) + b;
-    const int hm = it->hm, wm = it->wm;
-    const int chunks = (wm + kPatch14Chunk - 1) / kPatch14Chunk;
-    const int local = tile - plan.tile_prefix[b];
-    const int bw0 = local % chunks * kPatch14Chunk + blockIdx.x % kParts * NW;
-    if (bw0 >= wm) return;   // (the whole workgroup: the barrier below is not split)
-    const int bh = local / chunks % hm;
-    const int tt = local / chunks / hm;
-    const int nw = min(NW, wm - bw0);
+    const int win0 = (block0 + static_cast<int>(blockIdx.x)) * NW;   // windows in output order; tile_prefix counts them
+    const int nw = min(NW, plan.n_tiles - win0);
     const int tid = threadIdx.x;
-    const int64_t row_bytes = int64_t(it->w) * 3;
-    const int64_t first = int64_t(2 * P * bh) * row_bytes + int64_t(bw0) * (6 * P);   // of the chunk, in a frame
-    const cptr<int32_t> pair = as_const(plan.indices) + it->idx_off + 2 * tt;
-    const uint8_t* const src0 = it->frames + int64_t(pair[0]) * it->frame_bytes + first;
-    const uint8_t* const src1 = it->frames + int64_t(pair[1]) * it->frame_bytes + first;
     struct Px4 {
         uint32_t d[3];
     };
-    const int per_row = 7 * nw;                     // loads of four pixels per row of the chunk
-    for (int e = tid; e < 4 * P * per_row; e += 256) {
-        const int r = e / per_row, k = e - r * per_row;
-        const int dt = r >= 2 * P, y = r - dt * 2 * P;
-        const Px4 v = *reinterpret_cast<const Px4*>((dt ? src1 : src0) + y * row_bytes + 12 * k);
-        *reinterpret_cast<Px4*>(px + dt * kFrameB + y * kRowB + 12 * k) = v;
+    // windows [q, q + n) of the workgroup, which lie side by side in one
+    // merge-window row, from the pair's two frames
+    int b = find_item(plan.tile_prefix, plan.n_items, win0);
+    for (int q = 0; q < nw;) {
+        while (win0 + q >= plan.tile_prefix[b + 1]) ++b;   // (ends: a window of the batch)
+        const cptr<DevItem> it = as_const(plan.items) + b;
+        const int hm = it->hm, wm = it->wm;
+        const int local = win0 + q - plan.tile_prefix[b];
+        const int bw = local % wm, bh = local / wm % hm, tt = local / wm / hm;
+        const int n = min(nw - q, wm - bw);
+        const int64_t row_bytes = int64_t(it->w) * 3;
+        const int64_t first = int64_t(2 * P * bh) * row_bytes + int64_t(bw) * kWinB;
+        const cptr<int32_t> pair = as_const(plan.indices) + it->idx_off + 2 * tt;
+        const uint8_t* const src0 = it->frames + int64_t(pair[0]) * it->frame_bytes + first;
+        const uint8_t* const src1 = it->frames + int64_t(pair[1]) * it->frame_bytes + first;
+        const int per_row = 7 * n;                         // loads of four pixels
+        for (int e = tid; e < 4 * P * per_row; e += 256) {
+            const int r = e / per_row, k = e - r * per_row;
+            const int dt = r >= 2 * P, y = r - dt * 2 * P;
+            const Px4 v = *reinterpret_cast<const Px4*>((dt ? src1 : src0) + y * row_bytes + 12 * k);
+            *reinterpret_cast<Px4*>(px + dt * kFrameB + y * kRowB + q * kWinB + 12 * k) = v;
+        }
+        q += n;
     }
     __syncthreads();
 
     using elem_t = typename std::conditional<OUT_BF16 != 0, uint16_t, float>::type;
-    elem_t* const dst = static_cast<elem_t*>(out) +
-                        (it->row_off + ((int64_t(tt) * hm + bh) * wm + bw0) * 4) * kRowLen;
+    elem_t* const dst = static_cast<elem_t*>(out) + int64_t(win0) * kWin;
     const float a0 = norm.a[0], a1 = norm.a[1], a2 = norm.a[2];
     const float z0 = norm.z[0], z1 = norm.z[1], z2 = norm.z[2];
     for (int e = tid; e < nw * (kWin / VPP); e += 256) {
         const int v0 = e * VPP;
-        const int bw = v0 / kWin, in_win = v0 - bw * kWin;
-        const int sub = in_win / kRowLen, in_row = in_win - sub * kRowLen;
-        const uint8_t* const patch = px + (sub >> 1) * (P * kRowB) + bw * (6 * P) + (sub & 1) * (3 * P);
+        const int q4 = v0 / kRowLen;                // output row: window q4 / 4, its patch (q4 / 2) % 2, q4 % 2
+        const int in_row = v0 - q4 * kRowLen;
+        const uint8_t* const patch =
+            px + (q4 >> 2) * kWinB + ((q4 >> 1) & 1) * (P * kRowB) + (q4 & 1) * (3 * P);
         float v[VPP];
 #pragma unroll
         for (int g = 0; g < VPP; g += 4) {
@@ -2121,14 +2124,15 @@ int launch_patchify(const PlanView& plan, void* out, int out_dtype, const Norm& 
     dim3 grid(plan.n_tiles), block(256);
     if (patch == 14) {
         // (a launch holds fewer than 2^24 workgroups of 256)
-        const int parts = kPatch14Chunk / patch14_windows(out_dtype == 1);
-        constexpr int kMost = 1 << 22;
-        for (int t0 = 0; t0 < plan.n_tiles; t0 += kMost) {
-            grid.x = static_cast<unsigned>(std::min(kMost, plan.n_tiles - t0) * parts);
+        const int nw = patch14_windows(out_dtype == 1);
+        const int blocks = (plan.n_tiles - 1) / nw + 1;
+        constexpr int kMost = 1 << 23;
+        for (int b0 = 0; b0 < blocks; b0 += kMost) {
+            grid.x = static_cast<unsigned>(std::min(kMost, blocks - b0));
             if (out_dtype == 1)
-                hipLaunchKernelGGL(patchify14_kernel<1>, grid, block, 0, stream, plan, t0, out, norm);
+                hipLaunchKernelGGL(patchify14_kernel<1>, grid, block, 0, stream, plan, b0, out, norm);
             else
-                hipLaunchKernelGGL(patchify14_kernel<0>, grid, block, 0, stream, plan, t0, out, norm);
+                hipLaunchKernelGGL(patchify14_kernel<0>, grid, block, 0, stream, plan, b0, out, norm);
         }
     } else if (out_dtype == 1) {
         hipLaunchKernelGGL(patchify_kernel<1>, grid, block, 0, stream, plan, out, norm);

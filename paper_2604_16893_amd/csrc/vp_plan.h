@@ -85,10 +85,9 @@ constexpr int kRsMfmaWindow = 64;
 constexpr int kRsMfmaBandWords = 4 + 4 * 3 * 64 * 4;
 constexpr int resize_mfma_bytes() { return 3 * 64 * 16 + 4 * 64 * 3; }
 
-// Normalise + patchify, patch 14 (patchify14_kernel): merge windows of one
-// merge-window row per workgroup, and per entry of the plan.
+// Normalise + patchify, patch 14 (patchify14_kernel): merge windows per
+// workgroup.
 constexpr int patch14_windows(int out_bf16) { return out_bf16 ? 3 : 2; }
-constexpr int kPatch14Chunk = 6;
 
 // Kernel an item is routed to.
 enum Route : int32_t { kRouteGeneric = 0, kRouteStream = 1, kRoutePatch = 2, kRouteResize = 3 };
@@ -190,8 +189,8 @@ int launch_generic(const PlanView& plan, void* out, int out_dtype, const Norm& n
 int launch_stream(const PlanView& plan, const StreamLaunch& launch, void* out, int out_dtype,
                   const Norm& norm, hipStream_t stream);
 // Normalise + patchify of frames already at the target size: one workgroup
-// per merge-window row of a frame pair, for patch 14 per kPatch14Chunk
-// windows of one (tile_prefix counts them per item).
+// per merge-window row of a frame pair (tile_prefix counts them per item; for
+// patch 14 it counts merge windows).
 int launch_patchify(const PlanView& plan, void* out, int out_dtype, const Norm& norm, int patch,
                     hipStream_t stream);
 // uint8 cache writer over tile_prefix (items with route kRouteResize: rh x cw

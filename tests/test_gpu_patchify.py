@@ -177,16 +177,20 @@ def test_patch14_patchify_equals_preprocess_at_identity_size(dtype):
 
 @pytest.mark.parametrize("wm", [1, 2, 3, 4, 5, 6, 7, 13])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_patch14_window_chunks(wm, dtype):
-    """Widths around the 2 or 3 windows of a patch-14 workgroup and the 6 of a
-    plan entry: whole ones, remainders, workgroups with none; a pair, a padded
-    odd frame, a frame pointer off a 16-byte boundary."""
+def test_patch14_window_runs(wm, dtype):
+    """Two items whose windows do not fill the 2 or 3 windows of a patch-14
+    workgroup: workgroups that span window rows, pairs and items, and a last
+    one that is not full; a padded odd frame, a frame pointer off a 16-byte
+    boundary."""
     fd, fh = _frames(900 + wm, 3, 56, 28 * wm)
     buf = torch.empty(fd.numel() + 4, dtype=torch.uint8, device=DEV)
     frames = buf[4:].view(fd.shape)
     frames.copy_(fd)
     idx = np.array([2, 0, 1], np.int32)
+    fe, fg = _frames(950 + wm, 1, 28, 56)
     log(f"patch 14, {wm} windows {dtype}")
-    out, cu = run(vp.vp_patchify_batch, [(frames, idx)], MEAN, STD, dtype, patch=14)
+    out, cu = run(vp.vp_patchify_batch, [(frames, idx), (fe, idx[1:2])], MEAN, STD, dtype, patch=14)
     ref = oracle.patchify_item(fh, idx, MEAN, STD, patch=14)
     assert_close(host_rows(out, cu[0], cu[1], dtype), ref, dtype, f"{wm} windows")
+    ref = oracle.patchify_item(fg, [0], MEAN, STD, patch=14)
+    assert_close(host_rows(out, cu[1], cu[2], dtype), ref, dtype, "image of two windows")
