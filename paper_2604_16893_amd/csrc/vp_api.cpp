@@ -423,6 +423,9 @@ struct StreamShape {
 
 int32_t round_up(int32_t v, int32_t q) { return (v + q - 1) / q * q; }
 
+// Patch 14: the whole patches that two bands of `band` columns cover.
+int32_t band_patches(int32_t band) { return 2 * band / 14; }
+
 // Widest span of source pixels that one band of output columns reads.
 int32_t band_span(const AxisFilter& fx, int32_t band) {
     int32_t worst = 0;
@@ -435,9 +438,11 @@ int32_t band_span(const AxisFilter& fx, int32_t band) {
 }
 
 // Whether an item can take the streaming kernel, and with which shape: the
-// output width is cut into bands of 1 to 4 whole patches (16 to 64 columns,
-// or 14 to 56 for patch 14;
-// one single-wave workgroup each, one lane per column in the x pass), each
+// output width is cut into bands of 1 to 4 whole patches (16 to 64 columns;
+// one single-wave workgroup each, one lane per column in the x pass; for patch
+// 14 multiples of 7 columns from 14 to 63, in pairs: 49-column bands fill the
+// 128 pixels of px = 2 at 720p -> 588 columns, where 42-column ones took two
+// more waves in fourteen: 256 frames 305 -> 272 us), each
 // band's source pixels must fit 64 lanes of px pixels, and among the shapes
 // that fit, the one with the least estimated lane work is taken.  The LDS
 // budget is checked with float32 staging, so the routing does not depend on
@@ -450,14 +455,16 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
     // every load of a frame row (up to kSlotMax + 8 rows past the last one) stays below 4 GiB
     if (int64_t(it.src_h + vp::kSlotMax + 8) * it.src_w * 3 + 64 >= (int64_t(1) << 32)) return false;
     int64_t best = -1;
-    for (int32_t band = 4 * patch; band >= patch; band -= patch) {
-        const int32_t waves = (it.dst_w + band - 1) / band;
-        if (waves > vp::kWgBandMax) continue;   // the band index field of a workgroup entry
+    const int32_t step = patch == 14 ? 7 : patch;   // patch 14: two bands are whole patches
+    for (int32_t band = 64 / step * step; band >= patch; band -= step) {
+        const int32_t bands = (it.dst_w + band - 1) / band;
+        const int32_t waves = patch == 14 ? round_up(bands, 2) : bands;
+        if (bands > vp::kWgBandMax) continue;   // the band index field of a workgroup entry
         const int32_t span = band_span(fx, band);
         for (int32_t px = 2; px <= 4; ++px) {
             if (!vp::stream_shape_supported(mm, kx, px)) continue;
             if (span > 64 * px || kx > 64 * px) continue;
-            if (vp::stream_wave_bytes(px, kx, 4, patch) > vp::kStreamLdsBudget) continue;
+            if (vp::stream_wave_bytes(px, kx, 4, patch, band_patches(band)) > vp::kStreamLdsBudget) continue;
             // vector instructions per wave: per source row 3 px M
             // multiply-adds, about 2 px unpacks and 4 more; per output row
             // the x pass (3 kx FMAs, kx LDS reads), the slot's 3 px clears
@@ -470,7 +477,7 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
                 sh->kx = kx;
                 sh->px = px;
                 sh->band = band;
-                sh->bands = waves;
+                sh->bands = bands;
             }
             break;   // a wider px only adds idle lanes
         }
@@ -478,8 +485,8 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
     return best >= 0;
 }
 
-// The x-first streaming kernel (patch 16) for an item, if it can take it:
-// 4 to 12 taps (the window's own count, at least 4), M slots.  With
+// The x-first streaming kernel for an item, if it can take it: 4 to 12 taps
+// (the window's own count, at least 4; to 8 for patch 14), M slots.  With
 // `pairs`, windows of 6 to 8 taps -- x scales of about 1.3 to 2 -- whose
 // starts in each pair of columns (2i, 2i + 1) lie 0 to 2 pixels apart take
 // one column pair per lane and 128 columns per wave; else a lane takes one
@@ -488,19 +495,20 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
 // ran slower in pairs, at the lower occupancy of their larger register set.)
 // The last band is narrower where the width is not a multiple of the band.
 // Its shape is recorded with px = xfirst_px(0), or xfirst_px(2) for pairs.
-bool xfirst_shape(const vp_item& it, const AxisFilter& fx, int32_t m, bool pairs_ok, StreamShape* sh) {
+bool xfirst_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t patch, bool pairs_ok,
+                  StreamShape* sh) {
     const int32_t kx = std::max<int32_t>(fx.taps, 4);
-    bool pairs = pairs_ok && vp::xfirst_shape_supported(m, kx, 2) && fx.n_out % 2 == 0;
+    bool pairs = pairs_ok && vp::xfirst_shape_supported(m, kx, 2, patch) && fx.n_out % 2 == 0;
     for (int32_t j = 0; pairs && j + 1 < fx.n_out; j += 2) {
         const int32_t d = fx.start[j + 1] - fx.start[j];
         pairs = d >= 0 && d <= 2;
     }
     const int32_t db = pairs ? 2 : 0;
-    if (!vp::xfirst_shape_supported(m, kx, db)) return false;
+    if (!vp::xfirst_shape_supported(m, kx, db, patch)) return false;
     // every load of a frame row (a window of up to 3 (kx + db) + 6 bytes past
     // its start, up to kSlotMax + 8 rows past the last one) stays below 4 GiB
     if (int64_t(it.src_h + vp::kSlotMax + 8) * it.src_w * 3 + 3 * kx + 64 >= (int64_t(1) << 32)) return false;
-    const int32_t band = db > 0 ? 128 : 64;
+    const int32_t band = patch == 14 ? 63 : (db > 0 ? 128 : 64);
     const int32_t waves = (it.dst_w + band - 1) / band;
     if (waves > vp::kWgBandMax) return false;
     sh->m = m;
@@ -584,6 +592,7 @@ std::shared_ptr<const AxisEntry> make_axis_entry(int32_t n_in, int32_t n_out) {
 struct Keyed {
     std::tuple<int32_t, int32_t, int32_t> key;   // kernel shape (m, kx, px)
     int32_t bands;                               // column bands (workgroups) of the unit
+    int32_t wg_patches;                          // patch 14: patches of a workgroup's two bands
     vp::StreamUnit unit;
     int64_t cost;
 };
@@ -699,6 +708,7 @@ int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, Plan* p) {
                 const Keyed& e = keyed[order[k]];
                 p->units.push_back(e.unit);
                 L.cost += e.cost * e.bands;
+                L.wg_patches = std::max(L.wg_patches, e.wg_patches);
             }
             for (int32_t r = 0; r < rounds; ++r)
                 for (size_t col = 0; col < 8; ++col) {
@@ -811,8 +821,8 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         int32_t m = 0;
         StreamShape sh;
         const bool slots = slots_for(*fy, &d.sy_off, &m);
-        const bool near_one = P == 16 && double(it.src_h) <= kXFirstMaxScale * double(it.dst_h);
-        if (slots && ((near_one && xfirst_shape(it, *fx, m, false, &sh)) || stream_shape(it, *fx, m, P, &sh))) {
+        const bool near_one = double(it.src_h) <= kXFirstMaxScale * double(it.dst_h);
+        if (slots && ((near_one && xfirst_shape(it, *fx, m, P, false, &sh)) || stream_shape(it, *fx, m, P, &sh))) {
             d.route = vp::kRouteStream;   // (band and column table below, once the shape is final)
             shapes[b] = sh;
             x_axes[b] = fx;
@@ -890,7 +900,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         for (int32_t b = 0; b < n; ++b) {
             StreamShape sh;
             if (p->items[b].route == vp::kRouteStream && shapes[b].px == vp::xfirst_px(0) &&
-                xfirst_shape(items[b], *x_axes[b], shapes[b].m, true, &sh))
+                xfirst_shape(items[b], *x_axes[b], shapes[b].m, P, true, &sh))
                 shapes[b] = sh;
         }
     }
@@ -927,6 +937,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
                         Keyed k;
                         k.key = std::make_tuple(sh.m, sh.kx, sh.px);
                         k.bands = d.patch == 14 ? (sh.bands + 1) / 2 : sh.bands;   // patch 14: bands in pairs
+                        k.wg_patches = band_patches(sh.band);
                         k.unit.item = b;
                         k.unit.p_flags = (2 * tt + dt) | (same ? vp::kUnitBoth : 0);
                         k.unit.i0 = i0;
@@ -1307,6 +1318,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
                 Keyed e;
                 e.key = std::make_tuple(sh.m, sh.kx, sh.px);
                 e.bands = sh.bands;
+                e.wg_patches = 0;
                 e.unit.item = b;
                 e.unit.p_flags = k;
                 e.unit.i0 = i0;

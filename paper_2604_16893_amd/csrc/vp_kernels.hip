@@ -596,6 +596,31 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Patch 14 store-out of patch row pr (output rows 14 pr .. 14 pr + 13) by a
+// four-wave workgroup whose stage, [patch][1176] in output order, holds the
+// output columns j0 .. j0 + nbw - 1 of frame pair tt: the output rows leave
+// whole, in 16-byte pieces shared out over the waves; consecutive pieces are
+// consecutive in memory within each merge window.
+template <class elem_t>
+__device__ __forceinline__ void store_patch14_row(const elem_t* stage, void* out, int pr, int j0, int nbw, int tt,
+                                                  int64_t row_off, int hm, int wm) {
+    constexpr int kRowElems = 6 * 14 * 14;                         // 1176
+    constexpr int VPP = 16 / int(sizeof(elem_t));                  // values per piece
+    constexpr int PPR = kRowElems / VPP;                           // pieces per row
+    static_assert(kRowElems % VPP == 0, "rows are whole 16-byte pieces");
+    const int nq = nbw / 14;
+    const int64_t win_row0 = row_off + (int64_t(tt) * hm + (pr >> 1)) * wm * 4 + (pr & 1) * 2;
+    using u4v = unsigned __attribute__((ext_vector_type(4)));
+    for (int e = static_cast<int>(threadIdx.x); e < nq * PPR; e += 256) {
+        const int q = e / PPR;
+        const int pc = e - q * PPR;
+        const int qa = j0 / 14 + q;
+        const u4v val = *reinterpret_cast<const u4v*>(stage + q * kRowElems + pc * VPP);
+        elem_t* dst = static_cast<elem_t*>(out) + (win_row0 + (qa >> 1) * 4 + (qa & 1)) * kRowElems + pc * VPP;
+        __builtin_nontemporal_store(val, reinterpret_cast<u4v*>(dst));
+    }
+}
+
 // One workgroup streams one source frame (or a band of its output rows) top
 // to bottom; each of its waves owns one band of up to 64 output columns and
 // works alone -- no workgroup barrier anywhere:
@@ -665,30 +690,12 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
     const bool both = (u_pf & kUnitBoth) != 0;
 
     // patch 16: [row][stage [3][4][64]]; patch 14: [row of each of the four
-    // waves][stage [8 patches][1176]]
+    // waves][stage [patches][1176]]
     float4* row = reinterpret_cast<float4*>(smem + wv * kRowPx * 16);                  // [kRowPx]
     elem_t* stage = reinterpret_cast<elem_t*>(smem + (P == 16 ? 1 : 4) * kRowPx * 16);
 
-    // Patch 14 store-out of patch row pr (output rows 14 pr .. 14 pr + 13):
-    // the workgroup's output rows leave the stage whole, in 16-byte pieces
-    // shared out over its four waves; consecutive pieces are consecutive in
-    // memory within each merge window.
     auto store_rows = [&](int pr) __attribute__((always_inline)) {
-        constexpr int kRowElems = 6 * P * P;                           // 1176
-        constexpr int VPP = 16 / int(sizeof(elem_t));                  // values per piece
-        constexpr int PPR = kRowElems / VPP;                           // pieces per row
-        static_assert(kRowElems % VPP == 0, "rows are whole 16-byte pieces");
-        const int nq = nbw_wg / 14;
-        const int64_t win_row0 = it_row_off + (int64_t(tt) * it_hm + (pr >> 1)) * it_wm * 4 + (pr & 1) * 2;
-        using u4v = unsigned __attribute__((ext_vector_type(4)));
-        for (int e = static_cast<int>(threadIdx.x); e < nq * PPR; e += 256) {
-            const int q = e / PPR;
-            const int pc = e - q * PPR;
-            const int qa = j0_wg / 14 + q;
-            const u4v val = *reinterpret_cast<const u4v*>(stage + q * kRowElems + pc * VPP);
-            elem_t* dst = static_cast<elem_t*>(out) + (win_row0 + (qa >> 1) * 4 + (qa & 1)) * kRowElems + pc * VPP;
-            __builtin_nontemporal_store(val, reinterpret_cast<u4v*>(dst));
-        }
+        store_patch14_row(stage, out, pr, j0_wg, nbw_wg, tt, it_row_off, it_hm, it_wm);
     };
     if (P == 14 && (nbw <= 0 || (both && fw == 1))) {
         // a wave with no frame to stream (the second frame of a pair whose
@@ -807,9 +814,10 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
         }
     };
 
-    // Patch 14: the lane's column j0 + lane is column lane % 14 of the
-    // band's patch lane / 14, at this offset of the stage's patch-row origin.
-    const int st14 = ((j0 - j0_wg) / 14 + lane / 14) * (6 * P * P) + lane % 14;
+    // Patch 14: the lane's column is column c14 of the workgroup's, at this
+    // offset of the stage's patch-row origin.
+    const int c14 = j0 - j0_wg + lane;
+    const int st14 = c14 / 14 * (6 * P * P) + c14 % 14;
 
     // Store-out pieces of this lane (patch 16): piece e = lane + 64 r of the
     // band's (patch q, channel c, row ry, piece) runs, as a stage offset
@@ -1057,7 +1065,7 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
 template <int M, int KX, int PX>
 int launch_stream_shape(const PlanView& plan, const StreamLaunch& L, void* out, int out_dtype,
                         const Norm& norm, hipStream_t stream) {
-    const int lds = stream_wave_bytes(PX, KX, out_dtype == 1 ? 2 : 4, L.patch);
+    const int lds = stream_wave_bytes(PX, KX, out_dtype == 1 ? 2 : 4, L.patch, L.wg_patches);
     dim3 grid(static_cast<unsigned>(L.count)), block(L.patch == 14 ? 256 : 64);
     if (L.patch == 14) {
         if (out_dtype == 1)
@@ -1109,9 +1117,16 @@ int launch_stream_shape(const PlanView& plan, const StreamLaunch& L, void* out, 
 //     lanes per 128-byte run, as in the y-first kernel.
 // Window bytes past the end of a row are the next row's (or zeros past the
 // frame, from the buffer range check); they meet only zero weights.
-template <int M, int KXE, int DB, int OUT_BF16>
-__global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void* out, Norm norm) {
+//
+// Patch 14 (single columns, up to 8 taps): four-wave workgroups as in the
+// y-first kernel (two neighbouring bands of 63 columns x the pair's two
+// frames), which share a stage in output order and meet at a barrier once per
+// patch row.  256 frames at 588 columns, bf16, against the y-first kernel:
+// 360p 184 -> 141 us, 480p 219 -> 196 us (56-column bands: 147 and 213 us).
+template <int M, int KXE, int DB, int OUT_BF16, int P>
+__global__ __launch_bounds__(P == 16 ? 64 : 256) void xfirst_kernel(PlanView plan, int wg0, void* out, Norm norm) {
     using elem_t = typename std::conditional<OUT_BF16 != 0, uint16_t, float>::type;
+    static_assert(P == 16 || (P == 14 && DB == 0), "patch 16, or 14 with single columns");
     static_assert(KXE >= 4 && KXE <= 12 && DB >= 0 && DB <= 2, "tap counts from 4 to 12, pair offsets to 2");
     constexpr int CPL = DB > 0 ? 2 : 1;            // output columns per lane
     constexpr int BW = 64 * CPL;                   // output columns per wave
@@ -1120,9 +1135,11 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
     constexpr int ND = (3 * KW + 6) / 4;           // dwords loaded: the window at any alignment
     constexpr int S = 16 / int(sizeof(elem_t));    // output columns per 16-byte store
     extern __shared__ __align__(16) unsigned char smem[];
-    elem_t* const stage = reinterpret_cast<elem_t*>(smem);   // [3][4][BW]
+    elem_t* const stage = reinterpret_cast<elem_t*>(smem);   // [3][4][BW]; patch 14: [patches][1176]
 
     const int lane = static_cast<int>(threadIdx.x) & 63;
+    const int wv = P == 16 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int fw = wv & 1;                         // patch 14: the wave's frame of the pair
     const uint32_t wg = as_const(plan.wgs)[wg0 + static_cast<int>(blockIdx.x)];
     if (wg == kNoWork) return;
     const int u = static_cast<int>(wg & kWgUnitMask);
@@ -1133,14 +1150,29 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
     const cptr<DevItem> it = as_const(plan.items) + u_item;
     const int w = it->w;
     const int band = it->band;
-    const int j0 = wave * band;                    // first output column of this wave
-    const int nbw = min(band, w - j0);             // its columns
+    const int j0_wg = P == 16 ? wave * band : 2 * wave * band;   // the workgroup's first column
+    const int j0 = P == 16 ? j0_wg : j0_wg + (wv >> 1) * band;   // first output column of this wave
+    const int nbw = min(band, w - j0);             // its columns (none: a missing second band)
     const int tt = u_p >> 1;
-    const int dt_self = u_p & 1;
+    const int dt_self = P == 16 ? (u_p & 1) : fw;
     int64_t it_row_off = it->row_off;
     int it_hm = it->hm, it_wm = it->wm;
     asm volatile("" : "+s"(it_row_off), "+s"(it_hm), "+s"(it_wm));
     const bool both = (u_pf & kUnitBoth) != 0;
+    const int nbw_wg = min(2 * band, w - j0_wg);   // patch 14: the workgroup's columns
+    auto store_rows = [&](int pr) __attribute__((always_inline)) {
+        store_patch14_row(stage, out, pr, j0_wg, nbw_wg, tt, it_row_off, it_hm, it_wm);
+    };
+    if (P == 14 && (nbw <= 0 || (both && fw == 1))) {
+        // no frame to stream: keep step with the other waves' barriers (two
+        // per patch row) and store a share of the rows
+        for (int pr = i0 / 14; pr < i1 / 14; ++pr) {
+            lds_barrier();
+            store_rows(pr);
+            lds_barrier();
+        }
+        return;
+    }
 
     // Column table: window start relative to the band's first source pixel,
     // then KXE weights (zero past the window).  Lanes past the band's last
@@ -1185,7 +1217,7 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
     // blocks of four start at a multiple of 4 rows, so each block's offset
     // (a multiple of 4 bytes) goes into its resource, and the lane's window
     // in row phase k sits at the fixed dword offset voff[k], byte sh[k].
-    const int f = as_const(plan.indices)[it->idx_off + u_p];
+    const int f = as_const(plan.indices)[it->idx_off + u_p + (P == 16 ? 0 : fw)];
     const uintptr_t fa = reinterpret_cast<uintptr_t>(it->frames + int64_t(f) * it->frame_bytes);
     const uint32_t lead = static_cast<uint32_t>(fa & 3u);
     const uint32_t range = static_cast<uint32_t>((it->frame_bytes + lead + 3) & ~int64_t(3));
@@ -1275,6 +1307,10 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
     int next_close = close_row[base];
     int after_close = close_row[base + 1];
 
+    // patch 14: the lane's column in the stage's patch-row origin, as in the y-first kernel
+    const int c14 = j0 - j0_wg + lane;
+    const int st14 = c14 / 14 * (6 * P * P) + c14 % 14;
+
     // store-out pieces, as in the y-first kernel (patch 16)
     constexpr int kPieces = 16 / S;
     constexpr int kPerPatch = 3 * 4 * kPieces;
@@ -1362,7 +1398,9 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
             for (int s = 0; s < M; ++s) {
                 if (slot == s) {
                     if (keep) {
-                        elem_t* st = stage + yy * BW + CPL * lane;
+                        constexpr int kCh = P == 16 ? 4 * BW : 2 * P * P;   // stage channel stride
+                        elem_t* st = P == 16 ? stage + yy * BW + CPL * lane
+                                             : stage + st14 + (base % 14) * 14 + dt_self * (P * P);
 #pragma unroll
                         for (int c = 0; c < 3; ++c) {
                             const float sc = c == 0 ? a0 : (c == 1 ? a1 : a2);
@@ -1376,10 +1414,15 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
                                 else
                                     *reinterpret_cast<float2*>(st + c * 4 * BW) = make_float2(v, vb);
                             } else {
+                                elem_t ev;
                                 if constexpr (OUT_BF16 != 0)
-                                    st[c * 4 * BW] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(v));
+                                    ev = __builtin_bit_cast(uint16_t, static_cast<__bf16>(v));
                                 else
-                                    st[c * 4 * BW] = v;
+                                    ev = v;
+                                if (P == 16 || xlane) {
+                                    st[c * kCh] = ev;
+                                    if (P == 14 && both) st[c * kCh + P * P] = ev;   // both halves of the pair
+                                }
                             }
                         }
                     }
@@ -1391,7 +1434,15 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
                     }
                 }
             }
-            if (keep && yy == 3) store_out(base);
+            if constexpr (P == 14) {
+                if (keep && base % 14 == 13) {
+                    lds_barrier();
+                    store_rows(base / 14);
+                    lds_barrier();
+                }
+            } else if (keep && yy == 3) {
+                store_out(base);
+            }
             ++base;
             slot = slot + 1 == M ? 0 : slot + 1;
             next_close = after_close;
@@ -1445,12 +1496,22 @@ __global__ __launch_bounds__(64) void xfirst_kernel(PlanView plan, int wg0, void
 template <int M, int KXE, int DB>
 int launch_xfirst_shape(const PlanView& plan, const StreamLaunch& L, void* out, int out_dtype,
                         const Norm& norm, hipStream_t stream) {
-    const int lds = xfirst_wave_bytes(out_dtype == 1 ? 2 : 4, DB > 0 ? 2 : 1);
-    dim3 grid(static_cast<unsigned>(L.count)), block(64);
+    const int lds = xfirst_wave_bytes(out_dtype == 1 ? 2 : 4, DB > 0 ? 2 : 1, L.patch, L.wg_patches);
+    dim3 grid(static_cast<unsigned>(L.count)), block(L.patch == 14 ? 256 : 64);
+    if constexpr (DB == 0 && KXE <= kXFirstTaps14) {
+        if (L.patch == 14) {
+            if (out_dtype == 1)
+                hipLaunchKernelGGL((xfirst_kernel<M, KXE, 0, 1, 14>), grid, block, lds, stream, plan, L.first, out, norm);
+            else
+                hipLaunchKernelGGL((xfirst_kernel<M, KXE, 0, 0, 14>), grid, block, lds, stream, plan, L.first, out, norm);
+            return static_cast<int>(hipGetLastError());
+        }
+    }
+    if (L.patch != 16) return static_cast<int>(hipErrorInvalidConfiguration);
     if (out_dtype == 1)
-        hipLaunchKernelGGL((xfirst_kernel<M, KXE, DB, 1>), grid, block, lds, stream, plan, L.first, out, norm);
+        hipLaunchKernelGGL((xfirst_kernel<M, KXE, DB, 1, 16>), grid, block, lds, stream, plan, L.first, out, norm);
     else
-        hipLaunchKernelGGL((xfirst_kernel<M, KXE, DB, 0>), grid, block, lds, stream, plan, L.first, out, norm);
+        hipLaunchKernelGGL((xfirst_kernel<M, KXE, DB, 0, 16>), grid, block, lds, stream, plan, L.first, out, norm);
     return static_cast<int>(hipGetLastError());
 }
 
@@ -2165,16 +2226,17 @@ bool stream_shape_supported(int m, int kx, int px) {
     return px == 2 || (px == 3 && m <= 5 && kx <= 24);
 }
 
-bool xfirst_shape_supported(int m, int kx, int db) {
+bool xfirst_shape_supported(int m, int kx, int db, int patch) {
+    if (patch == 14 && (db != 0 || kx > kXFirstTaps14)) return false;
     return m >= 4 && m <= kSlotWords && kx >= 4 && (db == 0 ? kx <= 12 : db == 2 && kx >= 6 && kx <= 8);
 }
 
 int launch_stream(const PlanView& plan, const StreamLaunch& L, void* out, int out_dtype,
                   const Norm& norm, hipStream_t stream) {
     if (L.count <= 0) return 0;
-    if (L.px < 0 ? (L.px < xfirst_px(2) || !xfirst_shape_supported(L.m, L.kx, xfirst_db(L.px)) || L.patch != 16)
+    if (L.px < 0 ? (L.px < xfirst_px(2) || !xfirst_shape_supported(L.m, L.kx, xfirst_db(L.px), L.patch))
                  : (!stream_shape_supported(L.m, L.kx, L.px) ||
-                    stream_wave_bytes(L.px, L.kx, 4, L.patch) > kStreamLdsBudget))
+                    stream_wave_bytes(L.px, L.kx, 4, L.patch, L.wg_patches) > kStreamLdsBudget))
         return static_cast<int>(hipErrorInvalidConfiguration);
     for (const StreamPartFn part : kStreamParts)
         if (const int r = part(plan, L, out, out_dtype, norm, stream); r != -1) return r;

@@ -59,17 +59,20 @@ constexpr int kStreamLdsBudget = 64 * 1024;   // LDS of one streaming workgroup 
 // LDS of one streaming workgroup.  Patch 16 (one wave): its source row (64 *
 // px float4 pixels) and the stage of four output rows (3 channels x 4 rows x
 // 64 columns).  Patch 14 (four waves: a pair's two frames over two bands):
-// four source rows and the stage of up to eight whole output rows of 1176
-// values.
-constexpr int stream_wave_bytes(int px, int kx, int elem_bytes, int patch = 16) {
+// four source rows and the stage of `patches` whole output rows of 1176
+// values, the patches of the two bands.
+constexpr int stream_wave_bytes(int px, int kx, int elem_bytes, int patch, int patches) {
     return (void)kx, patch == 16 ? 64 * px * 16 + 3 * 4 * 64 * elem_bytes
-                                 : 4 * 64 * px * 16 + 8 * 6 * patch * patch * elem_bytes;
+                                 : 4 * 64 * px * 16 + patches * 6 * patch * patch * elem_bytes;
 }
 
 // LDS of one x-first streaming workgroup (one wave of cpl columns per lane):
 // the stage of four output rows (its lanes load their source windows from
-// memory).
-constexpr int xfirst_wave_bytes(int elem_bytes, int cpl) { return 3 * 4 * 64 * cpl * elem_bytes; }
+// memory).  Patch 14: a workgroup's stage of `patches` whole output rows.
+constexpr int xfirst_wave_bytes(int elem_bytes, int cpl, int patch, int patches) {
+    return patch == 16 ? 3 * 4 * 64 * cpl * elem_bytes : patches * 6 * patch * patch * elem_bytes;
+}
+constexpr int kXFirstTaps14 = 8;   // patch 14: most column taps of an x-first kernel
 
 // uint8 streaming writer: pixels per lane (a band's source span is at most
 // 64 * kRsPx pixels), and the LDS of one workgroup (one wave): its source
@@ -169,6 +172,7 @@ struct StreamLaunch {
     int32_t first, count;
     int32_t m, kx, px;       // accumulator slots, column taps, pixels per lane (or xfirst_px)
     int32_t patch;           // patch edge of the batch (16 or 14)
+    int32_t wg_patches;      // patch 14: most patches of two bands (a workgroup's columns)
     int64_t cost;            // host only: estimated work (source pixels read)
 };
 
@@ -206,6 +210,6 @@ int launch_positions(const PlanView& plan, int32_t* vit, int32_t* llm, int64_t r
 // Whether a (m, kx, px) shape has a compiled streaming kernel.
 bool stream_shape_supported(int m, int kx, int px);
 // Whether an (m, kx, pair offset) shape has a compiled x-first kernel.
-bool xfirst_shape_supported(int m, int kx, int db);
+bool xfirst_shape_supported(int m, int kx, int db, int patch);
 
 }  // namespace vp

@@ -61,3 +61,40 @@ def test_writer_short_units_match_long_ones(n_src, H, W, idx, h, w):
     ref = np.stack([oracle.resize_u8(src[i], h, w) for i in idx])
     assert np.array_equal(alone.cpu().numpy(), ref)
     assert torch.equal(many[0], alone) and torch.equal(many[-1], alone)
+
+
+# Patch 14: pairs of bands of up to 63 columns.  Widths of one window, of a
+# second band with no, some or all of its columns, of several workgroups; x
+# scales that give 4 to 8 taps on the x-first kernel (M up to 8 slots), and
+# y-first bands that are no whole number of patches (49 and 63 columns)
+BANDS14 = [
+    # H, W, h, w, kind, taps
+    (60, 31, 56, 28, vp.VP_KERNEL_XFIRST, 5),
+    (56, 112, 56, 112, vp.VP_KERNEL_XFIRST, 4),
+    (121, 181, 84, 140, vp.VP_KERNEL_XFIRST, 6),
+    (75, 409, 112, 252, vp.VP_KERNEL_XFIRST, 7),
+    (40, 511, 56, 280, vp.VP_KERNEL_XFIRST, 8),
+    (61, 131, 112, 252, vp.VP_KERNEL_XFIRST, 4),
+    (243, 641, 112, 280, vp.VP_KERNEL_YFIRST, 10),
+    (240, 427, 112, 196, vp.VP_KERNEL_YFIRST, 9),
+    (300, 421, 168, 364, vp.VP_KERNEL_YFIRST, 5),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,W,h,w,kind,taps", BANDS14)
+def test_patch14_bands(H, W, h, w, kind, taps, dtype):
+    it = workloads.Item("video", 3, H, W, "uniform", 47, {"mode": "uniform", "n": 3})
+    idx = [2, 0, 1]   # a pair, and an odd frame that stands for both of its pair
+    item = vp.Item(workloads.frames_torch(it, DEV), np.asarray(idx, np.int32), h, w, 14)
+    launches = vp.vp_batch_kernels([item])
+    assert [(int(r[0]), int(r[2])) for r in launches] == [(kind, taps)], launches.tolist()
+    print(f"[patch14 bands] {H}x{W} -> {h}x{w} {dtype} {launches.tolist()}", flush=True)
+    rows, _, _ = vp.preprocess([item], MEAN, STD, dtype)
+    torch.cuda.synchronize()
+    ref = oracle.preprocess_item(workloads.frames_np(it), idx, h, w, MEAN, STD, patch=14)
+    if dtype == "bf16":
+        res = compare.check_bf16(rows.view(torch.int16).cpu().numpy().view(np.uint16), ref)
+    else:
+        res = compare.check_f32(rows.cpu().numpy(), ref)
+    assert res["ok"], res
