@@ -355,70 +355,83 @@ bool build_columns_dot(const AxisFilter& f, int32_t kx, int32_t band, int32_t ro
     return true;
 }
 
-// Column table of an x axis for the uint8 writer's MFMA form.  Output
-// columns go in bands of 64, each of four blocks of 16; block b's window is
-// the 64 source pixels from the window start of its first column (for a
-// band's last block: the 64 that end where its columns' taps end), and the
-// horizontal sums of a block are a 16 x 16 x 64 byte matrix product per
-// channel and weight digit.  Per band: the four window starts (absolute
-// source pixels), then for each block and digit d2, d1, d0 the B operand of
-// v_mfma_i32_16x16x64_i8 for every lane l (column l % 16 of the block, window
-// taps 16 (l / 16) .. 16 (l / 16) + 15) as four dwords of digit bytes.  After
-// the bands, per column the start value 128 * (sum of q) + 2^21.  Returns
-// false if a block's columns do not fit its window or a weight its digits.
-bool build_columns_mfma(const AxisFilter& f, std::vector<int32_t>* words) {
-    const int32_t n = f.n_out;
-    const int32_t bands = (n + 63) / 64;
-    words->assign(size_t(bands) * vp::kRsMfmaBandWords + n, 0);
-    int32_t* cterm = words->data() + size_t(bands) * vp::kRsMfmaBandWords;
-    for (int32_t bd = 0; bd < bands; ++bd) {
-        int32_t* bw = words->data() + size_t(bd) * vp::kRsMfmaBandWords;
-        for (int32_t blk = 0; blk < 4; ++blk) {
-            const int32_t j0 = bd * 64 + blk * 16;
-            int32_t xb = j0 < n ? f.start[j0] : (blk > 0 ? bw[blk - 1] : 0);
-            // the band's last block ends its window where its columns' taps
-            // end: its pixels past that belong to the next band, whose own
-            // wave reads them
-            const bool last = j0 < n && (blk == 3 || j0 + 16 >= n);
-            if (last) {
-                int32_t end = 0;
-                for (int32_t j = j0; j < j0 + 16 && j < n; ++j) end = std::max(end, f.start[j] + f.count[j]);
-                xb = std::max(0, std::min(xb, end - 64));
+// Digit table of an axis for the uint8 writer's form with both passes on the
+// matrix cores.  Per output its window start, then per output the start value
+// 128 * (sum of q) + 2^21; then per block of 16 outputs, for an x axis
+// (`columns`) the first source pixel of its 64-pixel window, a multiple of 16
+// or, if some block does not fit then, of 8 or of 1, and for a y axis the first and the last chunk of 16 source rows its windows
+// read (all the first ones, then the last ones); then per output its digits
+// d2, d1, d0, a row of bytes each: 16 zeros, the taps (rounded up to 4), 16
+// zeros.  *extent: the most chunks of a block (y axis), or (x axis) 256 times
+// the multiple that windows start on plus the loads of four pixels a lane that
+// cover the widest band, 2, 4 or 8 loads of 64 lanes per 16 rows.  Returns false if a block's columns do not fit its
+// window or a band 32 lanes, its rows kRsMmRing chunks, or a weight its digits.
+bool build_digits(const AxisFilter& f, bool columns, std::vector<int32_t>* words, int32_t* extent) {
+    const int32_t n = f.n_out, blocks = (n + 15) / 16, taps4 = (f.taps + 3) & ~3, stride = taps4 + 32;
+    const size_t head = size_t(2) * n + size_t(columns ? 1 : 2) * blocks;
+    words->assign(head + size_t(n) * 3 * stride / 4, 0);
+    uint8_t* dig = reinterpret_cast<uint8_t*>(words->data() + head);
+    int32_t* const first = words->data() + size_t(2) * n;
+    int32_t* const last = first + blocks;
+    for (int32_t j = 1; j < n; ++j)   // windows never step back
+        if (f.start[j] < f.start[j - 1] || f.start[j] + f.count[j] < f.start[j - 1] + f.count[j - 1]) return false;
+    int32_t most = 0, align = 0;
+    if (columns) {
+        for (const int32_t a : {16, 8, 1}) {
+            bool fits = true;
+            most = 0;
+            for (int32_t b = 0; b < blocks; ++b) {
+                const int32_t j1 = std::min(16 * b + 16, n) - 1;
+                first[b] = f.start[16 * b] / a * a;
+                fits = fits && f.start[j1] + f.count[j1] - first[b] <= 64;
+                const int32_t x0 = first[b - b % (vp::kRsMmCols / 16)];
+                // (the kernel bounds a window's end by its start and the longest window)
+                most = std::max(most, (f.start[j1] + taps4 - x0 + 3) / 4);
             }
-            bw[blk] = xb;
-            for (int32_t nn = 0; nn < 16 && j0 + nn < n; ++nn) {
-                const int32_t j = j0 + nn;
-                if (f.start[j] + f.count[j] - xb > 64) return false;
-                int64_t sum = 0;
-                for (int32_t t = 0; t < f.count[j]; ++t) {
-                    const int32_t q = f.fixed[size_t(j) * f.taps + t];
-                    sum += q;
-                    const int32_t d0 = ((q + 128) & 255) - 128;
-                    const int32_t q1 = (q - d0) >> 8;
-                    const int32_t d1 = ((q1 + 128) & 255) - 128;
-                    const int32_t d2 = (q1 - d1) >> 8;
-                    if (d2 < -128 || d2 > 127) return false;
-                    const int32_t k = f.start[j] + t - xb;        // tap position in the window
-                    const int32_t lane = (k / 16) * 16 + nn;       // the lane holding (k, column nn)
-                    const int32_t byte = k % 16;
-                    const int32_t d[3] = {d2, d1, d0};
-                    for (int32_t dg = 0; dg < 3; ++dg) {
-                        uint32_t& w = reinterpret_cast<uint32_t&>(
-                            bw[4 + ((blk * 3 + dg) * 64 + lane) * 4 + byte / 4]);
-                        w |= (static_cast<uint32_t>(d[dg]) & 0xffu) << (8 * (byte % 4));
-                    }
-                }
-                const int64_t ct = 128 * sum + (int64_t(1) << 21);
-                if (ct > INT32_MAX || ct < INT32_MIN) return false;
-                cterm[j] = static_cast<int32_t>(ct);
+            if (fits && most <= 32) {
+                align = a;
+                break;
             }
         }
+        if (align == 0) return false;
+        const int32_t loads = most <= 8 ? 2 : most <= 16 ? 4 : 8;
+        if (align < 16 && loads < 8) return false;   // (the kernels' shapes; narrow spans fit at 16)
+        *extent = 256 * align + loads;
+    } else {
+        for (int32_t b = 0; b < blocks; ++b) {
+            const int32_t j1 = std::min(16 * b + 16, n) - 1;
+            first[b] = f.start[16 * b] / 16;
+            last[b] = (f.start[j1] + f.count[j1] - 1) / 16;
+            most = std::max(most, last[b] - first[b] + 1);
+        }
+        if (most > vp::kRsMmRing) return false;
+        *extent = most;
+    }
+    for (int32_t j = 0; j < n; ++j) {
+        int64_t sum = 0;
+        for (int32_t t = 0; t < f.count[j]; ++t) {
+            const int32_t q = f.fixed[size_t(j) * f.taps + t];
+            sum += q;
+            const int32_t d0 = ((q + 128) & 255) - 128;
+            const int32_t q1 = (q - d0) >> 8;
+            const int32_t d1 = ((q1 + 128) & 255) - 128;
+            const int32_t d2 = (q1 - d1) >> 8;
+            if (d2 < -128 || d2 > 127) return false;
+            const int32_t d[3] = {d2, d1, d0};
+            for (int32_t k = 0; k < 3; ++k)
+                dig[(size_t(j) * 3 + k) * stride + 16 + t] = static_cast<uint8_t>(d[k] & 0xff);
+        }
+        const int64_t ct = 128 * sum + (int64_t(1) << 21);
+        if (ct > INT32_MAX || ct < INT32_MIN) return false;
+        (*words)[j] = f.start[j];
+        (*words)[size_t(n) + j] = static_cast<int32_t>(ct);
     }
     return true;
 }
 
 struct StreamShape {
     int32_t m = 0, kx = 0, px = 0, band = 0, bands = 0;
+    int32_t ring = 0;   // uint8 writer's matrix-core form: chunks of 16 source rows a group of 16 rows reads
 };
 
 int32_t round_up(int32_t v, int32_t q) { return (v + q - 1) / q * q; }
@@ -592,7 +605,7 @@ std::shared_ptr<const AxisEntry> make_axis_entry(int32_t n_in, int32_t n_out) {
 struct Keyed {
     std::tuple<int32_t, int32_t, int32_t> key;   // kernel shape (m, kx, px)
     int32_t bands;                               // column bands (workgroups) of the unit
-    int32_t wg_patches;                          // patch 14: patches of a workgroup's two bands
+    int32_t lds_units;                          // patch 14: patches of a workgroup's two bands; uint8 writer: ring chunks
     vp::StreamUnit unit;
     int64_t cost;
 };
@@ -628,10 +641,9 @@ int64_t unit_row_band(const vp::DevItem& d, int64_t max_src_rows, int64_t group,
 // 2,048 waves 8 rows, then 4.  Patch 14 stores whole patch
 // rows, 14 or 28 (ten windows / 28 / 14: 480p x 16 45 / 31 / 25, 480p x 64
 // 89 / 69 / 70, 720p x 64 92 / 82 / 86): 14 up to 10,240 waves.  The uint8
-// writer's forms re-read at a higher price (ten windows / 16: dot products
-// 720p x 64 108 / 99, 480p x 128 130 / 137; the matrix-core form, in chunks
-// of 16 source rows, 1080p x 8 62 / 42, 1080p x 32 104 / 113).
-constexpr int64_t kShortWaves = 32768, kShortWavesDot = 20480, kShortWavesMfma = 6144;
+// writer's dot-product form re-reads at a higher price (ten windows / 16 rows:
+// 720p x 64 108 / 99, 480p x 128 130 / 137).
+constexpr int64_t kShortWaves = 32768, kShortWavesDot = 20480;
 
 template <class Waves, class Load>
 int64_t short_unit_rows(Waves waves, Load load, int64_t most, int32_t patch = 16) {
@@ -708,7 +720,7 @@ int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, Plan* p) {
                 const Keyed& e = keyed[order[k]];
                 p->units.push_back(e.unit);
                 L.cost += e.cost * e.bands;
-                L.wg_patches = std::max(L.wg_patches, e.wg_patches);
+                L.lds_units = std::max(L.lds_units, e.lds_units);
             }
             for (int32_t r = 0; r < rounds; ++r)
                 for (size_t col = 0; col < 8; ++col) {
@@ -937,7 +949,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
                         Keyed k;
                         k.key = std::make_tuple(sh.m, sh.kx, sh.px);
                         k.bands = d.patch == 14 ? (sh.bands + 1) / 2 : sh.bands;   // patch 14: bands in pairs
-                        k.wg_patches = band_patches(sh.band);
+                        k.lds_units = band_patches(sh.band);
                         k.unit.item = b;
                         k.unit.p_flags = (2 * tt + dt) | (same ? vp::kUnitBoth : 0);
                         k.unit.i0 = i0;
@@ -1199,18 +1211,22 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
         }
         return found->second;
     };
-    std::map<std::pair<int32_t, int32_t>, int32_t> mfma_tables;
-    // the MFMA column table, or -1 if a block's columns do not fit its window
-    auto mfma_columns_for = [&](const AxisFilter& f) -> int32_t {
-        const ColumnKey key = std::make_tuple(f.n_in, f.n_out, vp::kRsMfmaWindow, 64, 0, true);
-        auto found = mfma_tables.find(std::make_pair(f.n_in, f.n_out));
-        if (found == mfma_tables.end()) {
-            auto e = cached(g_column_cache, key, [&] {
+    std::map<std::tuple<int32_t, int32_t, bool>, std::pair<int32_t, int32_t>> digit_tables;
+    // the digit table of an axis (offset, extent), or offset -1 if the axis does not fit
+    auto digits_for = [&](const AxisFilter& f, bool columns) -> std::pair<int32_t, int32_t> {
+        const auto at = std::make_tuple(f.n_in, f.n_out, columns);
+        auto found = digit_tables.find(at);
+        if (found == digit_tables.end()) {
+            // (the extent rides behind the words)
+            auto e = cached(g_column_cache, std::make_tuple(f.n_in, f.n_out, vp::kRsMmShape, columns ? 1 : 0, 0, true), [&] {
                 auto v = std::make_shared<std::vector<int32_t>>();
-                if (!build_columns_mfma(f, v.get())) v->clear();
+                int32_t extent = 0;
+                if (build_digits(f, columns, v.get(), &extent)) v->push_back(extent);
+                else v->clear();
                 return std::shared_ptr<const std::vector<int32_t>>(std::move(v));
             });
-            found = mfma_tables.emplace(std::make_pair(f.n_in, f.n_out), e->empty() ? -1 : append(e)).first;
+            const int32_t extent = e->empty() ? 0 : e->back();
+            found = digit_tables.emplace(at, std::make_pair(e->empty() ? -1 : append(e), extent)).first;
         }
         return found->second;
     };
@@ -1241,23 +1257,25 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
         bytes += int64_t(it.n_idx) * it.dst_h * it.dst_w * 3;
         int32_t m = 0;
         StreamShape sh;
-        const bool slots = slots_for(*fy, &d.sy_off, &m);
-        // The MFMA form costs about the same per source row whatever the
-        // window; byte dot products cost in proportion to it.  Measured, the
-        // MFMA form wins from 16 dot-product taps (windows of 10 or more).
-        const bool long_x = round_up(fx->taps + 3, 4) >= 16;
-        if (slots && long_x && m >= 4 && m <= vp::kSlotWords && (it.dst_w + 63) / 64 <= vp::kWgBandMax &&
-            (d.sx_off = mfma_columns_for(*fx)) >= 0 &&
-            int64_t(it.src_h + vp::kSlotMax + 20) * it.src_w * 3 + 256 < (int64_t(1) << 32)) {
-            // the MFMA form: bands of 64 columns, blocks of 16 with 64-pixel windows
+        const int32_t mm_bands = (it.dst_w + vp::kRsMmCols - 1) / vp::kRsMmCols;
+        std::pair<int32_t, int32_t> dx(-1, 0), dy(-1, 0);
+        if (mm_bands <= vp::kWgBandMax && int64_t(it.src_h + 64) * it.src_w * 3 + 256 < (int64_t(1) << 32) &&
+            (dx = digits_for(*fx, true)).first >= 0)
+            dy = digits_for(*fy, false);
+        const bool mm = dx.first >= 0 && dy.first >= 0;
+        const bool slots = !mm && slots_for(*fy, &d.sy_off, &m);
+        if (mm) {
             d.route = vp::kRouteStream;
-            d.band = 64;
+            d.band = vp::kRsMmCols;
             d.row_px = 0;
-            sh.m = m;
-            sh.kx = vp::kRsMfmaWindow;
-            sh.px = vp::kRsPx;
-            sh.band = 64;
-            sh.bands = (it.dst_w + 63) / 64;
+            d.sx_off = dx.first;
+            d.sy_off = dy.first;
+            sh.m = dx.second % 256 + (dy.second > 4 ? vp::kRsMmTwo : 0);
+            sh.px = dx.second / 256;
+            sh.kx = vp::kRsMmShape;
+            sh.band = vp::kRsMmCols;
+            sh.bands = mm_bands;
+            sh.ring = dy.second;
             shapes[b] = sh;
         } else if (slots && resize_stream_shape(it, *fx, m, &sh) &&
             (d.sx_off = columns_for(*fx, sh.kx, sh.band, 64 * sh.px)) >= 0) {
@@ -1293,32 +1311,44 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
         if (d.route == vp::kRouteStream) wave_rows += int64_t(d.t) * shapes[b].bands * d.H;
     }
     const int64_t max_src_rows = wave_rows / (kWaveSlots * 8);
-    bool mfma = false;
+    // Units of the matrix-core form, by the batch's waves at 16-row units.
+    // Setting one up costs about four chunks of source rows, so they are as
+    // long as the chip stays full with: measured, kernel us at 16 / 32 / 64 /
+    // 128 / 192 rows: 1080p x 2 frames 15 / 17 / 25 / 41 / 58, x 8
+    // 30 / 23 / 27 / 42 / 59, x 16 49 / 42 / 35 / 47 / 61, x 64 160 / 131 / 124 /
+    // 124 / 154, x 256 605 / 480 / 425 / 428 / 446; 480p x 8 15 / 15 / 19 / 27 /
+    // 34, x 32 35 / 30 / 27 / 31 / 38, x 256 248 / 194 / 177 / 164 / 160.
+    int64_t mm_waves = 0;
     for (int32_t b = 0; b < n; ++b)
-        mfma = mfma || (p->items[b].route == vp::kRouteStream && shapes[b].kx == vp::kRsMfmaWindow);
-    const auto unit_waves = [&](int64_t rows) {
+        if (p->items[b].route == vp::kRouteStream && shapes[b].kx == vp::kRsMmShape)
+            mm_waves += int64_t(p->items[b].t) * shapes[b].bands * ((p->items[b].h + 15) / 16);
+    const int64_t mm_rows = mm_waves < 3000 ? 16 : mm_waves < 6000 ? 32 : mm_waves < 60000 ? 64 : 128;
+    const auto unit_waves = [&](int64_t rows) {   // of the dot-product form
         int64_t waves = 0;
         for (int32_t b = 0; b < n; ++b) {
             const vp::DevItem& d = p->items[b];
-            if (d.route != vp::kRouteStream) continue;
-            waves += int64_t(d.t) * shapes[b].bands * UnitSplit(d.h, unit_row_band(d, max_src_rows, 4, 10, rows), 4).n;
+            if (d.route != vp::kRouteStream || shapes[b].kx == vp::kRsMmShape) continue;
+            waves += int64_t(d.t) * shapes[b].bands *
+                     UnitSplit(d.h, unit_row_band(d, max_src_rows, 4, 10, rows), 4).n;
         }
         return waves;
     };
-    const int64_t short_rows = short_unit_rows(unit_waves, unit_waves, mfma ? kShortWavesMfma : kShortWavesDot);
+    const int64_t short_rows = short_unit_rows(unit_waves, unit_waves, kShortWavesDot);
     std::vector<Keyed> keyed;
     for (int32_t b = 0; b < n; ++b) {
         const vp::DevItem& d = p->items[b];
         if (d.route != vp::kRouteStream) continue;
         const StreamShape& sh = shapes[b];
-        const UnitSplit split(d.h, unit_row_band(d, max_src_rows, 4, 10, short_rows), 4);
+        // whole store groups: 4 rows, or 16 of the matrix-core form
+        const bool mm = sh.kx == vp::kRsMmShape;
+        const UnitSplit split(d.h, mm ? mm_rows : unit_row_band(d, max_src_rows, 4, 10, short_rows), mm ? 16 : 4);
         for (int32_t k = 0; k < d.t; ++k) {
             for (int64_t u = 0; u < split.n; ++u) {
                 const int32_t i0 = split.begin(u), i1 = split.end(u);
                 Keyed e;
                 e.key = std::make_tuple(sh.m, sh.kx, sh.px);
                 e.bands = sh.bands;
-                e.wg_patches = 0;
+                e.lds_units = sh.ring;
                 e.unit.item = b;
                 e.unit.p_flags = k;
                 e.unit.i0 = i0;

@@ -1065,7 +1065,7 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
 template <int M, int KX, int PX>
 int launch_stream_shape(const PlanView& plan, const StreamLaunch& L, void* out, int out_dtype,
                         const Norm& norm, hipStream_t stream) {
-    const int lds = stream_wave_bytes(PX, KX, out_dtype == 1 ? 2 : 4, L.patch, L.wg_patches);
+    const int lds = stream_wave_bytes(PX, KX, out_dtype == 1 ? 2 : 4, L.patch, L.lds_units);
     dim3 grid(static_cast<unsigned>(L.count)), block(L.patch == 14 ? 256 : 64);
     if (L.patch == 14) {
         if (out_dtype == 1)
@@ -1496,7 +1496,7 @@ __global__ __launch_bounds__(P == 16 ? 64 : 256) void xfirst_kernel(PlanView pla
 template <int M, int KXE, int DB>
 int launch_xfirst_shape(const PlanView& plan, const StreamLaunch& L, void* out, int out_dtype,
                         const Norm& norm, hipStream_t stream) {
-    const int lds = xfirst_wave_bytes(out_dtype == 1 ? 2 : 4, DB > 0 ? 2 : 1, L.patch, L.wg_patches);
+    const int lds = xfirst_wave_bytes(out_dtype == 1 ? 2 : 4, DB > 0 ? 2 : 1, L.patch, L.lds_units);
     dim3 grid(static_cast<unsigned>(L.count)), block(L.patch == 14 ? 256 : 64);
     if constexpr (DB == 0 && KXE <= kXFirstTaps14) {
         if (L.patch == 14) {
@@ -1744,28 +1744,62 @@ __global__ __launch_bounds__(64) void resize_stream_kernel(PlanView plan, int wg
     }
 }
 
-// The uint8 writer's MFMA form, for x axes whose 16-column blocks read at
-// most 64 source pixels (downscales up to about 3x).  One single-wave
-// workgroup per (frame, band of output rows, band of 64 output columns), as
-// above, but source rows go in chunks of 16:
-//   * horizontal pass, per block of 16 columns and per channel: lane l loads
-//     its own 16 pixels of source row (chunk + l % 16) from the block's
-//     window (16 (l / 16) .. +15), de-interleaves them into one channel's
-//     signed bytes (value - 128): the A operand of v_mfma_i32_16x16x64_i8
-//     (rows x window taps); the B operands are the block's weight digits
-//     (taps x columns), held in registers.  Three products, one per digit,
-//     from zero, zero and the start value, give the sums exactly (each stays
-//     below 2^30); they are combined, rounded to bytes and packed four rows
-//     per dword into LDS, [channel][column][16 rows];
-//   * vertical pass: lane j reads its column's 16 bytes per channel and
-//     adds the chunk's rows into the M rotating slots as before.
-template <int M>
-__global__ __launch_bounds__(64) void resize_mfma_kernel(PlanView plan, int wg0, uint8_t* out) {
+#if VP_PART == 0
+// The uint8 writer's matrix-core form, both passes.  One single-wave workgroup
+// streams one sampled frame (or a run of its output rows) for one band of up
+// to 32 output columns:
+//   * source rows go in chunks of 16, chunk c = rows 16 c .. 16 c + 15.  4 T
+//     lanes load a row, four pixels each, neighbouring lanes neighbouring
+//     pixels (T loads of 64 / (4 T) rows, one chunk ahead); a lane realigns its
+//     12 bytes and writes them to LDS as signed bytes (value - 128), one
+//     dword in each of the row's three channel planes;
+//   * horizontal pass, per block of 16 columns and per channel: lane l reads
+//     16 bytes of row l % 16 from the block's window of 64 pixels (pixels 16
+//     (l / 16) .. + 15; windows start on a multiple of A = 16 pixels, so that
+//     the read is aligned, or where some block does not fit 64 pixels then, of
+//     8, or anywhere), the A operand of v_mfma_i32_16x16x64_i8 (rows x window
+//     taps); the B operands, the block's weight digits (taps x columns), stay
+//     in registers.  Three products, one per base-256 digit, chained through
+//     their accumulators, give the sums exactly; they are rounded and packed to
+//     bytes (v_ashr_pk_u8_i32 shifts, clamps and packs two) and written, as
+//     signed bytes, to a ring of chunks in LDS, [chunk][channel][column][16
+//     rows];
+//   * vertical pass, per group of 16 output rows, once the chunks its windows
+//     read are there (at most `ring`; a product covers four chunks, 64 rows,
+//     and with TWO a second one the next four): the A operands come from the ring as they lie (columns x source rows),
+//     the B operands are the rows' weight digits at the chunks' places.  Lane l
+//     then has four neighbouring columns of output row l % 16 in each channel:
+//     12 consecutive bytes of the frame, which go through LDS to whole rows of
+//     the band.
+// Any tap counts take the same kernel, so a batch of any mix of scales is a
+// launch or two.
+// The forms before it were bound by vector issue: 78 instructions per source
+// row and 64 columns with the vertical pass on 24-bit multiply-adds, 60 or
+// more with dot products for the horizontal one too.  This one issues about 20
+// per source row (and 200 per 16 output rows), and waits for memory: at 4
+// waves a SIMD (120 registers) it reaches 4.1 TB/s at scale 2.8 and 2.5 TB/s
+// at 1.0.  Measured, 256 frames at the 262,144-pixel budget, us before and
+// after: 1080p 601 -> 437, 720p 336 -> 255, 480p 236 -> 170, 360p 161 -> 138;
+// two frames of 1080p 62 -> 15.  Lanes that load their own window's 48 bytes of
+// one row each (no LDS in between) took 648 us for the first: sixteen rows, 32
+// cache lines, an instruction.
+template <int T, int A, bool TWO>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T == 8 ? (TWO ? 3 : 4) : (TWO ? 4 : 5))))
+void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
     using v4i = int __attribute__((ext_vector_type(4)));
-    constexpr int kStageRow = 3 * 64;
+    constexpr int kLanes = 4 * T;                 // lanes per source row
+    constexpr int kRowsPerLoad = 64 / kLanes;
+    constexpr int kPlaneRow = resize_mm_plane_row(T);
+    constexpr int kPlane = 16 * kPlaneRow;        // LDS bytes of one channel of a chunk's source rows
+    constexpr int kChunk = 3 * kRsMmCols * 16;    // LDS bytes of one chunk's horizontal sums
+    constexpr int kStageRow = 3 * kRsMmCols;
+    static_assert(3 * kPlane >= 16 * kStageRow, "the stage takes the source planes' place");
     extern __shared__ __align__(16) unsigned char smem[];
+    uint8_t* const planes = smem;                 // [3][16][kPlaneRow]; the output stage [16][kStageRow] too
+    uint8_t* const hbuf = smem + 3 * kPlane;      // [ring][3][32 columns][16 rows]
 
     const int lane = threadIdx.x;
+    const int row16 = lane & 15, kg = lane >> 4;
     const uint32_t wg = as_const(plan.wgs)[wg0 + static_cast<int>(blockIdx.x)];
     if (wg == kNoWork) return;
     const int u = static_cast<int>(wg & kWgUnitMask);
@@ -1773,189 +1807,223 @@ __global__ __launch_bounds__(64) void resize_mfma_kernel(PlanView plan, int wg0,
     const cptr<StreamUnit> up = as_const(plan.units) + u;
     const int u_item = up->item, u_k = up->p_flags, i0 = up->i0, i1 = up->i1;
     const cptr<DevItem> it = as_const(plan.items) + u_item;
+    const int w = it->w, h = it->h;
+    const int j0 = wave * kRsMmCols;
+    const int nbw = min(kRsMmCols, w - j0);
 
-    const int w = it->w;
-    const int j0 = wave * 64;
-    const int nbw = min(64, w - j0);
-    const bool xlane = lane < nbw;
+    // Digit table of an axis: window starts, start values, block or group
+    // words, then per output three rows of digit bytes, 16 zeros on each side.
+    // digits16: the 16 digits of `row` that meet source positions pos .. pos + 15.
+    auto digits16 = [&](const int32_t* dig, int taps4, int row, int d, int pos) __attribute__((always_inline)) -> v4i {
+        const uint8_t* r = reinterpret_cast<const uint8_t*>(dig) + (int64_t(row) * 3 + d) * (taps4 + 32);
+        v4i v;
+        __builtin_memcpy(&v, r + min(max(pos + 16, 0), taps4 + 16), 16);
+        return v;
+    };
+    const int32_t* const xt = plan.tables + it->sx_off;   // start[w], term[w], window start[ceil(w / 16)]
+    const int xblocks = (w + 15) >> 4;
+    const int32_t* const xdig = xt + 2 * w + xblocks;
+    const int taps_x = (it->kx + 3) & ~3, taps_y = (it->ky + 3) & ~3;
+    const int x0 = as_const(xt)[2 * w + (j0 >> 4)];       // the band's first source pixel, a multiple of A
 
-    uint8_t* hbuf = smem;                         // [3][64 columns][16 rows]
-    uint8_t* stage = smem + 3 * 64 * 16;          // [4][kStageRow]
-
-    const cptr<int32_t> tables = as_const(plan.tables);
-    const cptr<int32_t> band_tab = tables + it->sx_off + wave * kRsMfmaBandWords;
-    const cptr<int32_t> cterm = tables + it->sx_off + ((w + 63) / 64) * kRsMfmaBandWords;
-    // B operands (weight digits) and start values of the lane's columns
-    v4i wt[4][3];
-    int32_t cb[4];
+    v4i wt[2][3];
+    int32_t cb[2];            // start values
+    const uint8_t* win[2];    // the lane's 16 bytes of each block's window, in the first plane
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < 2; ++b) {
+        const int blk = min((j0 >> 4) + b, xblocks - 1);
+        const int j = min(16 * blk + row16, w - 1);
+        const int xb = as_const(xt)[2 * w + blk];
+        const int pos = xb + 16 * kg - xt[j];
+        cb[b] = xt[w + j];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const cptr<int32_t> src = band_tab + 4 + ((b * 3 + d) * 64 + lane) * 4;
-            wt[b][d] = v4i{src[0], src[1], src[2], src[3]};
-        }
-        const int j = j0 + 16 * b + (lane & 15);
-        cb[b] = j < w ? cterm[j] : 0;
+        for (int d = 0; d < 3; ++d) wt[b][d] = digits16(xdig, taps_x, j, d, pos);
+        win[b] = planes + row16 * kPlaneRow + (xb - x0) + 16 * kg;
     }
-    const cptr<int32_t> ys = tables + it->ty_off;
-    const cptr<int32_t> slot_q = tables + it->sy_off;
-    const cptr<int32_t> close_row = tables + it->sy_off + (it->H + kSlotMax) * M;
 
-    // the frame through one buffer resource (loads past it return zeros)
+    const int32_t* const yt = plan.tables + it->sy_off;   // start[h], term[h], first and last chunk[ceil(h / 16)]
+    const int groups = (h + 15) >> 4;
+    const cptr<int32_t> chunk_lo = as_const(yt) + 2 * h;
+    const cptr<int32_t> chunk_hi = chunk_lo + groups;
+    const int32_t* const ydig = yt + 2 * h + 2 * groups;
+
+    // the frame through buffer resources, one per chunk (loads past the frame
+    // return zeros)
+    const uint32_t row_bytes = static_cast<uint32_t>(it->W) * 3u;
     const int f = as_const(plan.indices)[it->idx_off + u_k];
     const uintptr_t fa = reinterpret_cast<uintptr_t>(it->frames + int64_t(f) * it->frame_bytes);
     const uint32_t lead = static_cast<uint32_t>(fa & 3u);
     const uint32_t range = static_cast<uint32_t>((it->frame_bytes + lead + 3) & ~int64_t(3));
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(fa - lead), (short)0, static_cast<int>(range), 0x00020000);
-    const uint32_t row_bytes = static_cast<uint32_t>(it->W) * 3u;
-
-    int32_t acc[M][3];
+    const int lrow = lane / kLanes, piece = lane % kLanes;
+    // a lane whose pixels all lie past the band's taps loads nothing (its
+    // offset is past the range, or harmlessly inside a frame of 2 GiB)
+    const int need = as_const(xt)[j0 + nbw - 1] + taps_x - x0;
+    const uint32_t lane_off = 4 * piece < need ? lead + static_cast<uint32_t>(lrow) * row_bytes +
+                                                     3u * static_cast<uint32_t>(x0 + 4 * piece)
+                                               : 0x7FFF0000u;   // (16 rows more stay below 2^32)
+    uint32_t raw[T][4];
+    auto load_rows = [&](int c, int t) __attribute__((always_inline)) {
+        const uint32_t o = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(c)) * 16u * row_bytes;
+        const uint32_t n = uniform_sat_sub(range, o);
+        const uintptr_t bp = fa - lead + o;
+        const uint32_t b_lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bp));
+        const uint32_t b_hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bp >> 32));
+        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<void*>((uintptr_t(b_hi) << 32) | b_lo), (short)0, static_cast<int>(n), 0x00020000);
+        const uint32_t at = (lane_off + static_cast<uint32_t>(t * kRowsPerLoad) * row_bytes) & ~3u;
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rb, at, 0, 0);
 #pragma unroll
-    for (int s = 0; s < M; ++s) acc[s][0] = acc[s][1] = acc[s][2] = 0;
-    const int y0 = ys[i0];
-    const int y1 = close_row[i1 - 1] + 1;
-    int base = i0;
-    while (base > 0 && close_row[base - 1] >= y0) --base;
-    int slot = base % M;
-    int next_close = close_row[base];
-    int after_close = close_row[base + 1];   // read one ahead (the table ends in two sentinels)
-
-    // the item's output offset and height, held in scalar registers (as
-    // constant-memory loads the compiler would re-read them at every flush)
-    int64_t it_row_off = it->row_off;
-    int it_h = it->h;
-    asm volatile("" : "+s"(it_row_off), "+s"(it_h));
-    auto flush = [&](int i) __attribute__((always_inline)) {
-        const int nd = 3 * nbw / 4;
-        uint8_t* const ob = out + it_row_off + ((int64_t(u_k) * it_h + (i - 3)) * w + j0) * 3;
-        for (int e = lane; e < 4 * nd; e += 64) {
-            const int r = e / nd;
-            const int d = e - r * nd;
-            const uint32_t v = *reinterpret_cast<const uint32_t*>(stage + r * kStageRow + 4 * d);
-            __builtin_nontemporal_store(v, reinterpret_cast<uint32_t*>(ob + int64_t(r) * w * 3 + 4 * d));
-        }
+        for (int q = 0; q < 4; ++q) raw[t][q] = v[q];
     };
+    // Digit by digit, each product starting from the one before it times 2^8
+    // and a part of the start value (term = (term >> 8) 2^8 + (term & 255)):
+    // every partial sum fits int32.
+    auto shifted = [](const v4i& sum, int32_t term) __attribute__((always_inline)) -> v4i {
+        v4i r;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[q] = static_cast<int>((static_cast<uint32_t>(sum[q]) << 8) + static_cast<uint32_t>(term));
+        return r;
+    };
+    // the sums, rounded and clamped to bytes, in order
+    auto pack4 = [](const v4i& sum) __attribute__((always_inline)) -> uint32_t {
+        using us2 = unsigned short __attribute__((ext_vector_type(2)));
+        const us2 p = {static_cast<unsigned short>(__builtin_amdgcn_ashr_pk_u8_i32(sum[0], sum[1], 22)),
+                       static_cast<unsigned short>(__builtin_amdgcn_ashr_pk_u8_i32(sum[2], sum[3], 22))};
+        return __builtin_bit_cast(uint32_t, p);
+    };
+    const v4i zero = {0, 0, 0, 0};
+    // Store-out of a full band whose rows are 16-byte aligned: the lane's
+    // pieces of 16 bytes, six to a band row (its pieces lane and lane + 64)
+    const int row_out = w * 3;
+    const int piece_row0 = lane / 6, piece_row1 = (lane + 64) / 6;
+    const int piece_at0 = piece_row0 * row_out + (lane - piece_row0 * 6) * 16;
+    const int piece_at1 = piece_row1 * row_out + (lane + 64 - piece_row1 * 6) * 16;
 
-    const int g = lane >> 4;          // k group of the lane: window taps 16 g .. 16 g + 15
-    for (int yc = y0 & ~15; yc < y1; yc += 16) {
-        // ---- horizontal pass of source rows yc .. yc + 15
-        const uint32_t rowoff = lead + static_cast<uint32_t>(yc + (lane & 15)) * row_bytes;
+    int64_t it_row_off = it->row_off;
+    asm volatile("" : "+s"(it_row_off));
+    int cnext = chunk_lo[i0 >> 4];
+    int slot_next = 0, slot_lo = 0, c_lo = cnext;   // ring slots of chunks cnext and c_lo
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t o = rowoff + 3u * static_cast<uint32_t>(band_tab[b] + 16 * g);
-            const uint32_t oa = o & ~3u;
-            const uint32_t sh = o & 3u;
-            const auto l0 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, oa, 0, 0);
-            const auto l1 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, oa + 16, 0, 0);
-            const auto l2 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, oa + 32, 0, 0);
-            const uint32_t l3 = __builtin_amdgcn_raw_buffer_load_b32(rsrc, oa + 48, 0, 0);
-            const uint32_t raw[13] = {l0[0], l0[1], l0[2], l0[3], l1[0], l1[1], l1[2], l1[3],
-                                      l2[0], l2[1], l2[2], l2[3], l3};
-            uint32_t a[12];
+    for (int t = 0; t < T; ++t) load_rows(cnext, t);
+    for (int ig = i0; ig < i1; ig += 16) {
+        const int lo = chunk_lo[ig >> 4], hi = chunk_hi[ig >> 4];
+        slot_lo += lo - c_lo;
+        if (slot_lo >= ring) slot_lo -= ring;   // (lo <= cnext and the ring holds c_lo .. cnext - 1: less than one turn)
+        c_lo = lo;
+        // the rows' weights: loaded ahead of the horizontal pass
+        const int i = min(ig + row16, h - 1);
+        const int ystart = yt[i];
+        const int32_t yterm = yt[h + i];
+        v4i wv[TWO ? 2 : 1][3];
 #pragma unroll
-            for (int q = 0; q < 12; ++q) a[q] = __builtin_amdgcn_alignbyte(raw[q + 1], raw[q], sh);
-            // channel planes of the lane's 16 pixels, as signed bytes
-            v4i pc[3];
+        for (int d = 0; d < 3; ++d) wv[0][d] = digits16(ydig, taps_y, i, d, 16 * (lo + kg) - ystart);
+        if constexpr (TWO) {   // (past the windows: zeros)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t x0w = a[3 * k], x1w = a[3 * k + 1], x2w = a[3 * k + 2];
-                pc[0][k] = static_cast<int>(__builtin_amdgcn_perm(x2w, __builtin_amdgcn_perm(x1w, x0w, 0x00060300u), 0x05020100u) ^ 0x80808080u);
-                pc[1][k] = static_cast<int>(__builtin_amdgcn_perm(x2w, __builtin_amdgcn_perm(x1w, x0w, 0x00070401u), 0x06020100u) ^ 0x80808080u);
-                pc[2][k] = static_cast<int>(__builtin_amdgcn_perm(__builtin_amdgcn_perm(x2w, x1w, 0x07040100u), x0w, 0x07060502u) ^ 0x80808080u);
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const v4i zero = {0, 0, 0, 0};
-                const v4i cs = {cb[b], cb[b], cb[b], cb[b]};
-                const v4i s2 = __builtin_amdgcn_mfma_i32_16x16x64_i8(pc[c], wt[b][0], zero, 0, 0, 0);
-                const v4i s1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(pc[c], wt[b][1], zero, 0, 0, 0);
-                const v4i s0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(pc[c], wt[b][2], cs, 0, 0, 0);
-                // D[row 4 g + r][column l % 16]: rows 4g .. 4g + 3 of the lane's column
-                uint32_t hb[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const uint32_t sum = (static_cast<uint32_t>(s2[r]) << 16) + (static_cast<uint32_t>(s1[r]) << 8) +
-                                         static_cast<uint32_t>(s0[r]);
-                    hb[r] = static_cast<uint32_t>(min(max(static_cast<int32_t>(sum) >> 22, 0), 255));
-                }
-                // packed with v_perm: left to itself the compiler fuses two of
-                // the clamps with the packing into a 16-bit v_ashr_pk_u8_i32 and
-                // ORs the other two bytes over its undefined upper half
-                const uint32_t packed = __builtin_amdgcn_perm(hb[1], hb[0], 0x0C0C0400u) |
-                                        __builtin_amdgcn_perm(hb[3], hb[2], 0x04000C0Cu);
-                *reinterpret_cast<uint32_t*>(hbuf + c * 1024 + (16 * b + (lane & 15)) * 16 + 4 * g) = packed;
-            }
+            for (int d = 0; d < 3; ++d) wv[1][d] = digits16(ydig, taps_y, i, d, 16 * (lo + 4 + kg) - ystart);
         }
-        wave_lds_fence();
-        // ---- vertical pass over the chunk's rows
-        uint4 hv[3];
+
+        for (; cnext <= hi; ++cnext) {
+            // the chunk's source rows to the planes, the next chunk's loads
 #pragma unroll
-        for (int c = 0; c < 3; ++c) hv[c] = *reinterpret_cast<const uint4*>(hbuf + c * 1024 + lane * 16);
-        wave_lds_fence();
-        const cptr<int32_t> wblk = slot_q + yc * M;
-        int32_t wk[4][M];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int y = yc + r;
-            if ((r & 3) == 0 && y < y1) {
-                // the next four rows' slot weights, read together (y < y1 <= H,
-                // and the table has kSlotMax rows past the frame's last)
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int s = 0; s < M; ++s) wk[k][s] = wblk[(r + k) * M + s];
+            for (int t = 0; t < T; ++t) {
+                const uint32_t sh = lane_off + static_cast<uint32_t>(t * kRowsPerLoad) * row_bytes;   // (its low two bits)
+                const uint32_t a0 = __builtin_amdgcn_alignbyte(raw[t][1], raw[t][0], sh);
+                const uint32_t a1 = __builtin_amdgcn_alignbyte(raw[t][2], raw[t][1], sh);
+                const uint32_t a2 = __builtin_amdgcn_alignbyte(raw[t][3], raw[t][2], sh);
+                asm volatile("" : : "v"(a0), "v"(a1), "v"(a2));
+                load_rows(cnext + 1, t);   // (past the frame: zeros)
+                // r0 g0 b0 r1 | g1 b1 r2 g2 | b2 r3 g3 b3
+                const uint32_t rr = __builtin_amdgcn_perm(a2, __builtin_amdgcn_perm(a1, a0, 0x00060300u), 0x05020100u);
+                const uint32_t gg = __builtin_amdgcn_perm(a2, __builtin_amdgcn_perm(a1, a0, 0x00070401u), 0x06020100u);
+                const uint32_t bb = __builtin_amdgcn_perm(__builtin_amdgcn_perm(a2, a1, 0x07040100u), a0, 0x07060502u);
+                uint32_t* const dst =
+                    reinterpret_cast<uint32_t*>(planes + (t * kRowsPerLoad + lrow) * kPlaneRow + 4 * piece);
+                dst[0] = rr ^ 0x80808080u;
+                dst[kPlane / 4] = gg ^ 0x80808080u;
+                dst[2 * kPlane / 4] = bb ^ 0x80808080u;
             }
-            if (y < y0 || y >= y1) continue;   // wave-uniform
-            const uint32_t dw = r >> 2;
-            const uint32_t sel = 8u * static_cast<uint32_t>(r & 3);
-            int32_t h[3];
+            wave_lds_fence();
+            uint8_t* const hrow = hbuf + slot_next * kChunk + row16 * 16 + 4 * kg;
+            slot_next = slot_next + 1 == ring ? 0 : slot_next + 1;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const uint32_t word = dw == 0 ? hv[c].x : dw == 1 ? hv[c].y : dw == 2 ? hv[c].z : hv[c].w;
-                h[c] = static_cast<int32_t>(__builtin_amdgcn_ubfe(word, sel, 8));
-            }
+            for (int b = 0; b < 2; ++b) {
 #pragma unroll
-            for (int s = 0; s < M; ++s) {
-                const int32_t ws = wk[r & 3][s];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[s][c] += __mul24(ws, h[c]);
-            }
-            while (y == next_close && base < i1) {   // wave-uniform
-                const bool keep = base >= i0;
-#pragma unroll
-                for (int s = 0; s < M; ++s) {
-                    if (slot == s) {
-                        if (keep && xlane) {
-                            uint8_t* st = stage + (base & 3) * kStageRow + 3 * lane;
-#pragma unroll
-                            for (int c = 0; c < 3; ++c)
-                                st[c] = static_cast<uint8_t>(min(max((acc[s][c] + (1 << 21)) >> 22, 0), 255));
-                        }
-                        acc[s][0] = acc[s][1] = acc[s][2] = 0;
+                for (int c = 0; c < 3; ++c) {
+                    v4i av;
+                    if constexpr (A == 16) {
+                        av = *reinterpret_cast<const v4i*>(win[b] + c * kPlane);
+                    } else if constexpr (A == 1) {
+                        __builtin_memcpy(&av, win[b] + c * kPlane, 16);
+                    } else {
+                        using v2i = int __attribute__((ext_vector_type(2)));
+                        const v2i* const pw = reinterpret_cast<const v2i*>(win[b] + c * kPlane);
+                        av = v4i{pw[0][0], pw[0][1], pw[1][0], pw[1][1]};
                     }
+                    v4i sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, wt[b][0], zero, 0, 0, 0);
+                    sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, wt[b][1], shifted(sum, cb[b] >> 8), 0, 0, 0);
+                    sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, wt[b][2], shifted(sum, cb[b] & 255), 0, 0, 0);
+                    // D[row 4 kg + r][column row16]: rows 4 kg .. 4 kg + 3 of the lane's column
+                    *reinterpret_cast<uint32_t*>(hrow + c * (kRsMmCols * 16) + b * 256) = pack4(sum) ^ 0x80808080u;
                 }
-                if (keep && (base & 3) == 3) {
-                    wave_lds_fence();
-                    flush(base);
-                    wave_lds_fence();
+            }
+            wave_lds_fence();
+        }
+
+        // vertical pass of output rows ig .. ig + 15
+        auto ring_slot = [&](int k) __attribute__((always_inline)) -> int {   // of chunk lo + k + kg, or of chunk lo past hi
+            const int c = k + kg <= hi - lo ? slot_lo + k + kg : slot_lo;
+            return c >= ring ? c - ring : c;
+        };
+        const uint8_t* const src_a = hbuf + ring_slot(0) * kChunk + row16 * 16;
+        const uint8_t* const src_b = hbuf + ring_slot(4) * kChunk + row16 * 16;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            uint32_t px[3];   // per channel the bytes of columns 4 kg .. 4 kg + 3 of row ig + row16
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int at = c * (kRsMmCols * 16) + b * 256;
+                const v4i av = *reinterpret_cast<const v4i*>(src_a + at);
+                v4i bv = zero, sum = zero;
+                if constexpr (TWO) bv = *reinterpret_cast<const v4i*>(src_b + at);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    if (d > 0) sum = shifted(sum, d == 1 ? yterm >> 8 : yterm & 255);
+                    sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, wv[0][d], sum, 0, 0, 0);
+                    if constexpr (TWO) sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(bv, wv[TWO ? 1 : 0][d], sum, 0, 0, 0);
                 }
-                ++base;
-                slot = slot + 1 == M ? 0 : slot + 1;
-                next_close = after_close;
-                after_close = close_row[base + 1];
+                px[c] = pack4(sum);
+            }
+            // r0 g0 b0 r1 | g1 b1 r2 g2 | b2 r3 g3 b3
+            const uint32_t rg01 = __builtin_amdgcn_perm(px[1], px[0], 0x05010400u);   // r0 g0 r1 g1
+            const uint32_t rg23 = __builtin_amdgcn_perm(px[1], px[0], 0x07030602u);   // r2 g2 r3 g3
+            uint32_t* const st = reinterpret_cast<uint32_t*>(planes + row16 * kStageRow + 48 * b + 12 * kg);
+            st[0] = __builtin_amdgcn_perm(px[2], rg01, 0x02040100u);
+            st[1] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(px[2], rg01, 0x00000503u), rg23, 0x01000504u);
+            st[2] = __builtin_amdgcn_perm(px[2], rg23, 0x07030206u);
+        }
+        wave_lds_fence();
+        const int rows = min(16, i1 - ig);
+        uint8_t* const ob = out + it_row_off + ((int64_t(u_k) * h + ig) * w + j0) * 3;
+        const uint32_t low = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ob)) |
+                                                            static_cast<uint32_t>(row_out));
+        if (nbw == kRsMmCols && (low & 15u) == 0) {
+            if (piece_row0 < rows)
+                *reinterpret_cast<uint4*>(ob + piece_at0) = *reinterpret_cast<const uint4*>(planes + 16 * lane);
+            if (piece_row1 < rows)   // (rows 10 .. 21: none past 15, rows is at most 16)
+                *reinterpret_cast<uint4*>(ob + piece_at1) = *reinterpret_cast<const uint4*>(planes + 16 * (lane + 64));
+        } else {
+            const int nd = 3 * nbw / 4;   // dwords per band row (nbw is a multiple of 4)
+            for (int e = lane; e < rows * nd; e += 64) {
+                const int r = e / nd;
+                const int d = e - r * nd;
+                *reinterpret_cast<uint32_t*>(ob + int64_t(r) * row_out + 4 * d) =
+                    *reinterpret_cast<const uint32_t*>(planes + r * kStageRow + 4 * d);
             }
         }
+        wave_lds_fence();
     }
 }
-
-template <int M>
-int launch_resize_mfma_shape(const PlanView& plan, const StreamLaunch& L, void* out, hipStream_t stream) {
-    hipLaunchKernelGGL((resize_mfma_kernel<M>), dim3(static_cast<unsigned>(L.count)), dim3(64),
-                       resize_mfma_bytes(), stream, plan, L.first, static_cast<uint8_t*>(out));
-    return static_cast<int>(hipGetLastError());
-}
+#endif  // VP_PART == 0
 
 template <int M, int KX>
 int launch_resize_stream_shape(const PlanView& plan, const StreamLaunch& L, void* out, hipStream_t stream) {
@@ -1990,10 +2058,7 @@ template <int MM, int KK, int ID>
 int resize_case(const PlanView& plan, const StreamLaunch& L, void* out, hipStream_t stream) {
     if constexpr (ID % VP_PARTS == VP_PART) {
         if (L.m == MM && L.kx == KK) {
-            if constexpr (KK == kRsMfmaWindow)
-                return launch_resize_mfma_shape<MM>(plan, L, out, stream);
-            else
-                return launch_resize_stream_shape<MM, KK>(plan, L, out, stream);
+            return launch_resize_stream_shape<MM, KK>(plan, L, out, stream);
         }
     }
     return -1;
@@ -2044,7 +2109,7 @@ int VP_CAT(launch_resize_stream_part, VP_PART)(const PlanView& plan, const Strea
 #define VP_RS_CASE(MM, KK) \
     if (const int r = resize_case<MM, KK, __COUNTER__>(plan, L, out, stream); r != -1) return r;
 #define VP_RS_KX(MM) VP_RS_CASE(MM, 8) VP_RS_CASE(MM, 12) VP_RS_CASE(MM, 16) VP_RS_CASE(MM, 20) \
-    VP_RS_CASE(MM, 24) VP_RS_CASE(MM, 28) VP_RS_CASE(MM, 32) VP_RS_CASE(MM, kRsMfmaWindow)
+    VP_RS_CASE(MM, 24) VP_RS_CASE(MM, 28) VP_RS_CASE(MM, 32)
     VP_RS_KX(4) VP_RS_KX(5) VP_RS_KX(6) VP_RS_KX(7) VP_RS_KX(8)
 #undef VP_RS_KX
 #undef VP_RS_CASE
@@ -2171,8 +2236,27 @@ bool resize_stream_supported(int m, int kx, int px) {
 
 int launch_resize_stream(const PlanView& plan, const StreamLaunch& L, void* out, hipStream_t stream) {
     if (L.count <= 0) return 0;
-    if (L.kx == kRsMfmaWindow ? (L.px != kRsPx || L.m < 4 || L.m > kSlotWords)
-                              : !resize_stream_supported(L.m, L.kx, L.px))
+    if (L.kx == kRsMmShape) {
+        if (L.lds_units < 1 || L.lds_units > kRsMmRing) return static_cast<int>(hipErrorInvalidConfiguration);
+        const dim3 grid(static_cast<unsigned>(L.count)), block(64);
+        const int ring = L.lds_units, t = L.m % kRsMmTwo;
+        const bool two = L.m >= kRsMmTwo;
+        if (ring > (two ? kRsMmRing : 4)) return static_cast<int>(hipErrorInvalidConfiguration);
+        const int lds = resize_mm_bytes(t, ring);
+        uint8_t* const o = static_cast<uint8_t*>(out);
+#define VP_MM_CASE(T, A)                                                                                          \
+    if (t == T && L.px == A) {                                                                                    \
+        if (two)                                                                                                  \
+            hipLaunchKernelGGL((resize_mm_kernel<T, A, true>), grid, block, lds, stream, plan, L.first, o, ring); \
+        else                                                                                                      \
+            hipLaunchKernelGGL((resize_mm_kernel<T, A, false>), grid, block, lds, stream, plan, L.first, o, ring); \
+    } else
+        VP_MM_CASE(2, 16) VP_MM_CASE(4, 16) VP_MM_CASE(8, 16) VP_MM_CASE(8, 8) VP_MM_CASE(8, 1)
+#undef VP_MM_CASE
+            return static_cast<int>(hipErrorInvalidConfiguration);
+        return static_cast<int>(hipGetLastError());
+    }
+    if (!resize_stream_supported(L.m, L.kx, L.px))
         return static_cast<int>(hipErrorInvalidConfiguration);
     for (const ResizePartFn part : kResizeParts)
         if (const int r = part(plan, L, out, stream); r != -1) return r;
@@ -2236,7 +2320,7 @@ int launch_stream(const PlanView& plan, const StreamLaunch& L, void* out, int ou
     if (L.count <= 0) return 0;
     if (L.px < 0 ? (L.px < xfirst_px(2) || !xfirst_shape_supported(L.m, L.kx, xfirst_db(L.px), L.patch))
                  : (!stream_shape_supported(L.m, L.kx, L.px) ||
-                    stream_wave_bytes(L.px, L.kx, 4, L.patch, L.wg_patches) > kStreamLdsBudget))
+                    stream_wave_bytes(L.px, L.kx, 4, L.patch, L.lds_units) > kStreamLdsBudget))
         return static_cast<int>(hipErrorInvalidConfiguration);
     for (const StreamPartFn part : kStreamParts)
         if (const int r = part(plan, L, out, out_dtype, norm, stream); r != -1) return r;

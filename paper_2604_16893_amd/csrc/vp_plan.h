@@ -80,17 +80,25 @@ constexpr int kXFirstTaps14 = 8;   // patch 14: most column taps of an x-first k
 // RGB pixels.
 constexpr int kRsPx = 4;
 constexpr int resize_stream_bytes() { return 3 * 64 * kRsPx + 4 * 64 * 3; }
-// The writer's MFMA form (launch shape kx = kRsMfmaWindow): column table words
-// per band of 64 columns (four window starts, then 4 blocks x 3 digits x 64
-// lanes x 4 dwords), and its LDS: the horizontal pass's bytes of 16 source
-// rows for 64 columns and 3 channels, and the stage.
-constexpr int kRsMfmaWindow = 64;
-constexpr int kRsMfmaBandWords = 4 + 4 * 3 * 64 * 4;
-constexpr int resize_mfma_bytes() { return 3 * 64 * 16 + 4 * 64 * 3; }
-
 // Normalise + patchify, patch 14 (patchify14_kernel): merge windows per
 // workgroup.
 constexpr int patch14_windows(int out_bf16) { return out_bf16 ? 3 : 2; }
+
+// The uint8 writer's form with both passes on the matrix cores (launch shape kx =
+// kRsMmShape; m = T, the loads per chunk of 16 source rows: 4 T lanes of four
+// pixels cover a band's source span, plus kRsMmTwo where a group of 16 output
+// rows can read more than four chunks; px = A, the pixels that the windows of 16
+// columns start on a multiple of: 16, 8 or 1): output columns per wave, most chunks
+// that a group of 16 output rows reads, and its LDS: the chunk's source
+// pixels as three planes of 16 rows (16 bytes more than a row's pixels, so
+// that eight rows' 16-byte reads meet all banks) and a ring of chunks of
+// horizontal sums (16 rows x columns x 3 channels).
+constexpr int kRsMmShape = 128;
+constexpr int kRsMmCols = 32;
+constexpr int kRsMmRing = 8;
+constexpr int kRsMmTwo = 16;
+constexpr int resize_mm_plane_row(int t) { return 16 * t + 16; }
+constexpr int resize_mm_bytes(int t, int ring) { return 3 * 16 * resize_mm_plane_row(t) + ring * 3 * kRsMmCols * 16; }
 
 // Kernel an item is routed to.
 enum Route : int32_t { kRouteGeneric = 0, kRouteStream = 1, kRoutePatch = 2, kRouteResize = 3 };
@@ -172,7 +180,8 @@ struct StreamLaunch {
     int32_t first, count;
     int32_t m, kx, px;       // accumulator slots, column taps, pixels per lane (or xfirst_px)
     int32_t patch;           // patch edge of the batch (16 or 14)
-    int32_t wg_patches;      // patch 14: most patches of two bands (a workgroup's columns)
+    int32_t lds_units;       // sizes the LDS: patch 14, most patches of two bands (a workgroup's
+                             // columns); uint8 writer's matrix-core form, its ring of chunks
     int64_t cost;            // host only: estimated work (source pixels read)
 };
 

@@ -150,3 +150,41 @@ def test_resize_u8_patch14_widths():
         log(f"patch14_widths item {k}: {diff} differing bytes of {ref.size}")
         assert diff == 0
 
+
+
+# The matrix-core form at the edges of its shapes: 2, 4 and 8 loads per chunk
+# (spans of up to 32, 64 and 128 pixels), windows on multiples of 16, 8 and 1,
+# one product and two in the vertical pass, upscales, a frame of fewer rows
+# than one chunk, last bands of 24, 20 and 12 columns, rows that are not 16-byte
+# aligned, odd row lengths (every byte alignment), single frames
+MM_CASES = [
+    # H, W, h, w, patch
+    (9, 7, 32, 32, 16),
+    (40, 33, 96, 128, 16),
+    (33, 61, 32, 64, 16),
+    (101, 157, 96, 96, 16),
+    (77, 190, 64, 96, 16),
+    (181, 271, 64, 96, 16),
+    (200, 301, 64, 128, 16),
+    (120, 183, 64, 64, 16),
+    (290, 365, 96, 128, 16),
+    (290, 202, 96, 64, 16),
+    (203, 199, 64, 64, 16),
+    (330, 211, 64, 64, 16),
+    (61, 117, 56, 56, 14),
+    (150, 245, 56, 140, 14),
+    (165, 260, 84, 84, 14),
+]
+
+
+@pytest.mark.parametrize("H,W,h,w,patch", MM_CASES)
+def test_matrix_core_form_edges(H, W, h, w, patch):
+    it, fd = _video(71, 2, H, W)
+    src = workloads.frames_np(it)
+    log(f"matrix-core {H}x{W} -> {h}x{w} patch {patch}")
+    out, off = run([(fd, np.array([1, 0], np.int32), h, w)], patch=patch)
+    got = frames_of(out, off, 0, 2, h, w).cpu().numpy()
+    for k, f in enumerate([1, 0]):
+        ref = oracle.resize_u8(src[f], h, w)
+        bad = np.argwhere(got[k] != ref)
+        assert bad.size == 0, f"frame {f}: {len(bad)} bytes differ, first at {bad[0]}"
