@@ -363,8 +363,9 @@ bool build_columns_dot(const AxisFilter& f, int32_t kx, int32_t band, int32_t ro
 // read (all the first ones, then the last ones); then per output its digits
 // d2, d1, d0, a row of bytes each: 16 zeros, the taps (rounded up to 4), 16
 // zeros.  *extent: the most chunks of a block (y axis), or (x axis) 256 times
-// the multiple that windows start on plus the loads of four pixels a lane that
-// cover the widest band, 2, 4 or 8 loads of 64 lanes per 16 rows.  Returns false if a block's columns do not fit its
+// the multiple that windows start on, plus the loads of four pixels a lane that
+// cover the widest band (2, 4 or 8 loads of 64 lanes per 16 rows), plus
+// kRsMmWide where windows of 64 pixels do not do and 128 do.  Returns false if a block's columns do not fit its
 // window or a band 32 lanes, its rows kRsMmRing chunks, or a weight its digits.
 bool build_digits(const AxisFilter& f, bool columns, std::vector<int32_t>* words, int32_t* extent) {
     const int32_t n = f.n_out, blocks = (n + 15) / 16, taps4 = (f.taps + 3) & ~3, stride = taps4 + 32;
@@ -375,28 +376,27 @@ bool build_digits(const AxisFilter& f, bool columns, std::vector<int32_t>* words
     int32_t* const last = first + blocks;
     for (int32_t j = 1; j < n; ++j)   // windows never step back
         if (f.start[j] < f.start[j - 1] || f.start[j] + f.count[j] < f.start[j - 1] + f.count[j - 1]) return false;
-    int32_t most = 0, align = 0;
+    int32_t most = 0;
     if (columns) {
-        for (const int32_t a : {16, 8, 1}) {
+        *extent = 0;
+        for (const auto& [wide, a] : {std::pair{false, 16}, {false, 8}, {false, 1}, {true, 16}, {true, 1}}) {
             bool fits = true;
             most = 0;
             for (int32_t b = 0; b < blocks; ++b) {
                 const int32_t j1 = std::min(16 * b + 16, n) - 1;
                 first[b] = f.start[16 * b] / a * a;
-                fits = fits && f.start[j1] + f.count[j1] - first[b] <= 64;
-                const int32_t x0 = first[b - b % (vp::kRsMmCols / 16)];
+                fits = fits && f.start[j1] + f.count[j1] - first[b] <= (wide ? 128 : 64);
+                const int32_t x0 = first[b - b % (vp::resize_mm_cols(wide) / 16)];
                 // (the kernel bounds a window's end by its start and the longest window)
                 most = std::max(most, (f.start[j1] + taps4 - x0 + 3) / 4);
             }
-            if (fits && most <= 32) {
-                align = a;
+            const int32_t loads = wide ? 8 : most <= 8 ? 2 : most <= 16 ? 4 : 8;
+            if (fits && most <= 32 && (a == 16 || loads == 8)) {   // (narrow spans fit at 16)
+                *extent = 256 * a + (wide ? vp::kRsMmWide : 0) + loads;
                 break;
             }
         }
-        if (align == 0) return false;
-        const int32_t loads = most <= 8 ? 2 : most <= 16 ? 4 : 8;
-        if (align < 16 && loads < 8) return false;   // (the kernels' shapes; narrow spans fit at 16)
-        *extent = 256 * align + loads;
+        if (*extent == 0) return false;
     } else {
         for (int32_t b = 0; b < blocks; ++b) {
             const int32_t j1 = std::min(16 * b + 16, n) - 1;
@@ -521,7 +521,10 @@ bool xfirst_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
     // every load of a frame row (a window of up to 3 (kx + db) + 6 bytes past
     // its start, up to kSlotMax + 8 rows past the last one) stays below 4 GiB
     if (int64_t(it.src_h + vp::kSlotMax + 8) * it.src_w * 3 + 3 * kx + 64 >= (int64_t(1) << 32)) return false;
-    const int32_t band = patch == 14 ? 63 : (db > 0 ? 128 : 64);
+    // (patch 14: the narrowest bands, in multiples of 7 columns up to 63, that
+    // give the fewest pairs: a pair's stage is its workgroup's LDS)
+    const int32_t pairs14 = (it.dst_w + 125) / 126;
+    const int32_t band = patch == 14 ? round_up((it.dst_w + 2 * pairs14 - 1) / (2 * pairs14), 7) : (db > 0 ? 128 : 64);
     const int32_t waves = (it.dst_w + band - 1) / band;
     if (waves > vp::kWgBandMax) return false;
     sh->m = m;
@@ -1257,24 +1260,24 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
         bytes += int64_t(it.n_idx) * it.dst_h * it.dst_w * 3;
         int32_t m = 0;
         StreamShape sh;
-        const int32_t mm_bands = (it.dst_w + vp::kRsMmCols - 1) / vp::kRsMmCols;
         std::pair<int32_t, int32_t> dx(-1, 0), dy(-1, 0);
-        if (mm_bands <= vp::kWgBandMax && int64_t(it.src_h + 64) * it.src_w * 3 + 256 < (int64_t(1) << 32) &&
+        if ((it.dst_w + 15) / 16 <= vp::kWgBandMax && int64_t(it.src_h + 64) * it.src_w * 3 + 256 < (int64_t(1) << 32) &&
             (dx = digits_for(*fx, true)).first >= 0)
             dy = digits_for(*fy, false);
         const bool mm = dx.first >= 0 && dy.first >= 0;
         const bool slots = !mm && slots_for(*fy, &d.sy_off, &m);
         if (mm) {
             d.route = vp::kRouteStream;
-            d.band = vp::kRsMmCols;
+            const int32_t cols = vp::resize_mm_cols((dx.second & vp::kRsMmWide) != 0);
+            d.band = cols;
             d.row_px = 0;
             d.sx_off = dx.first;
             d.sy_off = dy.first;
             sh.m = dx.second % 256 + (dy.second > 4 ? vp::kRsMmTwo : 0);
             sh.px = dx.second / 256;
             sh.kx = vp::kRsMmShape;
-            sh.band = vp::kRsMmCols;
-            sh.bands = mm_bands;
+            sh.band = cols;
+            sh.bands = (it.dst_w + cols - 1) / cols;
             sh.ring = dy.second;
             shapes[b] = sh;
         } else if (slots && resize_stream_shape(it, *fx, m, &sh) &&

@@ -1747,7 +1747,8 @@ __global__ __launch_bounds__(64) void resize_stream_kernel(PlanView plan, int wg
 #if VP_PART == 0
 // The uint8 writer's matrix-core form, both passes.  One single-wave workgroup
 // streams one sampled frame (or a run of its output rows) for one band of up
-// to 32 output columns:
+// to 32 output columns, or WIDE, where the windows of 16 columns read more than
+// 64 source pixels (x downscales over about 3.2), 16:
 //   * source rows go in chunks of 16, chunk c = rows 16 c .. 16 c + 15.  4 T
 //     lanes load a row, four pixels each, neighbouring lanes neighbouring
 //     pixels (T loads of 64 / (4 T) rows, one chunk ahead); a lane realigns its
@@ -1757,7 +1758,8 @@ __global__ __launch_bounds__(64) void resize_stream_kernel(PlanView plan, int wg
 //     16 bytes of row l % 16 from the block's window of 64 pixels (pixels 16
 //     (l / 16) .. + 15; windows start on a multiple of A = 16 pixels, so that
 //     the read is aligned, or where some block does not fit 64 pixels then, of
-//     8, or anywhere), the A operand of v_mfma_i32_16x16x64_i8 (rows x window
+//     8, or anywhere; WIDE takes a second product for 64 pixels more), the A
+//     operand of v_mfma_i32_16x16x64_i8 (rows x window
 //     taps); the B operands, the block's weight digits (taps x columns), stay
 //     in registers.  Three products, one per base-256 digit, chained through
 //     their accumulators, give the sums exactly; they are rounded and packed to
@@ -1780,10 +1782,10 @@ __global__ __launch_bounds__(64) void resize_stream_kernel(PlanView plan, int wg
 // waves a SIMD (120 registers) it reaches 4.1 TB/s at scale 2.8 and 2.5 TB/s
 // at 1.0.  Measured, 256 frames at the 262,144-pixel budget, us before and
 // after: 1080p 601 -> 437, 720p 336 -> 255, 480p 236 -> 170, 360p 161 -> 138;
-// two frames of 1080p 62 -> 15.  Lanes that load their own window's 48 bytes of
+// two frames of 1080p 62 -> 15; WIDE, 32 frames of 4K 347 -> 192 (4.3 TB/s).  Lanes that load their own window's 48 bytes of
 // one row each (no LDS in between) took 648 us for the first: sixteen rows, 32
 // cache lines, an instruction.
-template <int T, int A, bool TWO>
+template <int T, int A, bool TWO, bool WIDE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T == 8 ? (TWO ? 3 : 4) : (TWO ? 4 : 5))))
 void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
     using v4i = int __attribute__((ext_vector_type(4)));
@@ -1791,12 +1793,14 @@ void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
     constexpr int kRowsPerLoad = 64 / kLanes;
     constexpr int kPlaneRow = resize_mm_plane_row(T);
     constexpr int kPlane = 16 * kPlaneRow;        // LDS bytes of one channel of a chunk's source rows
-    constexpr int kChunk = 3 * kRsMmCols * 16;    // LDS bytes of one chunk's horizontal sums
-    constexpr int kStageRow = 3 * kRsMmCols;
+    constexpr int kCols = resize_mm_cols(WIDE);   // output columns of the band, in blocks of 16
+    constexpr int NB = kCols / 16, KB = WIDE ? 2 : 1;   // blocks; 64-pixel products of a window
+    constexpr int kChunk = 3 * kCols * 16;        // LDS bytes of one chunk's horizontal sums
+    constexpr int kStageRow = 3 * kCols;
     static_assert(3 * kPlane >= 16 * kStageRow, "the stage takes the source planes' place");
     extern __shared__ __align__(16) unsigned char smem[];
     uint8_t* const planes = smem;                 // [3][16][kPlaneRow]; the output stage [16][kStageRow] too
-    uint8_t* const hbuf = smem + 3 * kPlane;      // [ring][3][32 columns][16 rows]
+    uint8_t* const hbuf = smem + 3 * kPlane;      // [ring][3][columns][16 rows]
 
     const int lane = threadIdx.x;
     const int row16 = lane & 15, kg = lane >> 4;
@@ -1808,8 +1812,8 @@ void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
     const int u_item = up->item, u_k = up->p_flags, i0 = up->i0, i1 = up->i1;
     const cptr<DevItem> it = as_const(plan.items) + u_item;
     const int w = it->w, h = it->h;
-    const int j0 = wave * kRsMmCols;
-    const int nbw = min(kRsMmCols, w - j0);
+    const int j0 = wave * kCols;
+    const int nbw = min(kCols, w - j0);
 
     // Digit table of an axis: window starts, start values, block or group
     // words, then per output three rows of digit bytes, 16 zeros on each side.
@@ -1826,18 +1830,20 @@ void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
     const int taps_x = (it->kx + 3) & ~3, taps_y = (it->ky + 3) & ~3;
     const int x0 = as_const(xt)[2 * w + (j0 >> 4)];       // the band's first source pixel, a multiple of A
 
-    v4i wt[2][3];
-    int32_t cb[2];            // start values
-    const uint8_t* win[2];    // the lane's 16 bytes of each block's window, in the first plane
+    v4i wt[NB][KB][3];
+    int32_t cb[NB];           // start values
+    const uint8_t* win[NB];   // the lane's 16 bytes of each block's window, in the first plane
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < NB; ++b) {
         const int blk = min((j0 >> 4) + b, xblocks - 1);
         const int j = min(16 * blk + row16, w - 1);
         const int xb = as_const(xt)[2 * w + blk];
         const int pos = xb + 16 * kg - xt[j];
         cb[b] = xt[w + j];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) wt[b][d] = digits16(xdig, taps_x, j, d, pos);
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) wt[b][kb][d] = digits16(xdig, taps_x, j, d, pos + 64 * kb);
         win[b] = planes + row16 * kPlaneRow + (xb - x0) + 16 * kg;
     }
 
@@ -1893,11 +1899,11 @@ void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
     };
     const v4i zero = {0, 0, 0, 0};
     // Store-out of a full band whose rows are 16-byte aligned: the lane's
-    // pieces of 16 bytes, six to a band row (its pieces lane and lane + 64)
+    // pieces of 16 bytes, lane and lane + 64 of the group's 3 NB to a row
     const int row_out = w * 3;
-    const int piece_row0 = lane / 6, piece_row1 = (lane + 64) / 6;
-    const int piece_at0 = piece_row0 * row_out + (lane - piece_row0 * 6) * 16;
-    const int piece_at1 = piece_row1 * row_out + (lane + 64 - piece_row1 * 6) * 16;
+    const int piece_row0 = lane / (3 * NB), piece_row1 = (lane + 64) / (3 * NB);
+    const int piece_at0 = piece_row0 * row_out + (lane - piece_row0 * (3 * NB)) * 16;
+    const int piece_at1 = piece_row1 * row_out + (lane + 64 - piece_row1 * (3 * NB)) * 16;
 
     int64_t it_row_off = it->row_off;
     asm volatile("" : "+s"(it_row_off));
@@ -1946,24 +1952,32 @@ void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
             uint8_t* const hrow = hbuf + slot_next * kChunk + row16 * 16 + 4 * kg;
             slot_next = slot_next + 1 == ring ? 0 : slot_next + 1;
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
+            for (int b = 0; b < NB; ++b) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    v4i av;
-                    if constexpr (A == 16) {
-                        av = *reinterpret_cast<const v4i*>(win[b] + c * kPlane);
-                    } else if constexpr (A == 1) {
-                        __builtin_memcpy(&av, win[b] + c * kPlane, 16);
-                    } else {
-                        using v2i = int __attribute__((ext_vector_type(2)));
-                        const v2i* const pw = reinterpret_cast<const v2i*>(win[b] + c * kPlane);
-                        av = v4i{pw[0][0], pw[0][1], pw[1][0], pw[1][1]};
+                    v4i av[KB], sum = zero;
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb) {
+                        const uint8_t* const pw = win[b] + c * kPlane + 64 * kb;
+                        if constexpr (A == 16) {
+                            av[kb] = *reinterpret_cast<const v4i*>(pw);
+                        } else if constexpr (A == 8) {
+                            using v2i = int __attribute__((ext_vector_type(2)));
+                            const v2i* const p2 = reinterpret_cast<const v2i*>(pw);
+                            av[kb] = v4i{p2[0][0], p2[0][1], p2[1][0], p2[1][1]};
+                        } else {
+                            __builtin_memcpy(&av[kb], pw, 16);
+                        }
                     }
-                    v4i sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, wt[b][0], zero, 0, 0, 0);
-                    sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, wt[b][1], shifted(sum, cb[b] >> 8), 0, 0, 0);
-                    sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, wt[b][2], shifted(sum, cb[b] & 255), 0, 0, 0);
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        if (d > 0) sum = shifted(sum, d == 1 ? cb[b] >> 8 : cb[b] & 255);
+#pragma unroll
+                        for (int kb = 0; kb < KB; ++kb)
+                            sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[kb], wt[b][kb][d], sum, 0, 0, 0);
+                    }
                     // D[row 4 kg + r][column row16]: rows 4 kg .. 4 kg + 3 of the lane's column
-                    *reinterpret_cast<uint32_t*>(hrow + c * (kRsMmCols * 16) + b * 256) = pack4(sum) ^ 0x80808080u;
+                    *reinterpret_cast<uint32_t*>(hrow + c * (kCols * 16) + b * 256) = pack4(sum) ^ 0x80808080u;
                 }
             }
             wave_lds_fence();
@@ -1977,11 +1991,11 @@ void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
         const uint8_t* const src_a = hbuf + ring_slot(0) * kChunk + row16 * 16;
         const uint8_t* const src_b = hbuf + ring_slot(4) * kChunk + row16 * 16;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < NB; ++b) {
             uint32_t px[3];   // per channel the bytes of columns 4 kg .. 4 kg + 3 of row ig + row16
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const int at = c * (kRsMmCols * 16) + b * 256;
+                const int at = c * (kCols * 16) + b * 256;
                 const v4i av = *reinterpret_cast<const v4i*>(src_a + at);
                 v4i bv = zero, sum = zero;
                 if constexpr (TWO) bv = *reinterpret_cast<const v4i*>(src_b + at);
@@ -2006,10 +2020,10 @@ void resize_mm_kernel(PlanView plan, int wg0, uint8_t* out, int ring) {
         uint8_t* const ob = out + it_row_off + ((int64_t(u_k) * h + ig) * w + j0) * 3;
         const uint32_t low = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ob)) |
                                                             static_cast<uint32_t>(row_out));
-        if (nbw == kRsMmCols && (low & 15u) == 0) {
+        if (nbw == kCols && (low & 15u) == 0) {
             if (piece_row0 < rows)
                 *reinterpret_cast<uint4*>(ob + piece_at0) = *reinterpret_cast<const uint4*>(planes + 16 * lane);
-            if (piece_row1 < rows)   // (rows 10 .. 21: none past 15, rows is at most 16)
+            if (piece_row1 < rows)   // (past row 15: none, rows is at most 16)
                 *reinterpret_cast<uint4*>(ob + piece_at1) = *reinterpret_cast<const uint4*>(planes + 16 * (lane + 64));
         } else {
             const int nd = 3 * nbw / 4;   // dwords per band row (nbw is a multiple of 4)
@@ -2240,18 +2254,19 @@ int launch_resize_stream(const PlanView& plan, const StreamLaunch& L, void* out,
         if (L.lds_units < 1 || L.lds_units > kRsMmRing) return static_cast<int>(hipErrorInvalidConfiguration);
         const dim3 grid(static_cast<unsigned>(L.count)), block(64);
         const int ring = L.lds_units, t = L.m % kRsMmTwo;
-        const bool two = L.m >= kRsMmTwo;
+        const bool two = (L.m & kRsMmTwo) != 0, wide = (L.m & kRsMmWide) != 0;
         if (ring > (two ? kRsMmRing : 4)) return static_cast<int>(hipErrorInvalidConfiguration);
-        const int lds = resize_mm_bytes(t, ring);
+        const int lds = resize_mm_bytes(t, ring, wide);
         uint8_t* const o = static_cast<uint8_t*>(out);
-#define VP_MM_CASE(T, A)                                                                                          \
-    if (t == T && L.px == A) {                                                                                    \
+#define VP_MM_CASE(T, A, WIDE)                                                                                    \
+    if (t == T && L.px == A && wide == WIDE) {                                                                    \
         if (two)                                                                                                  \
-            hipLaunchKernelGGL((resize_mm_kernel<T, A, true>), grid, block, lds, stream, plan, L.first, o, ring); \
+            hipLaunchKernelGGL((resize_mm_kernel<T, A, true, WIDE>), grid, block, lds, stream, plan, L.first, o, ring); \
         else                                                                                                      \
-            hipLaunchKernelGGL((resize_mm_kernel<T, A, false>), grid, block, lds, stream, plan, L.first, o, ring); \
+            hipLaunchKernelGGL((resize_mm_kernel<T, A, false, WIDE>), grid, block, lds, stream, plan, L.first, o, ring); \
     } else
-        VP_MM_CASE(2, 16) VP_MM_CASE(4, 16) VP_MM_CASE(8, 16) VP_MM_CASE(8, 8) VP_MM_CASE(8, 1)
+        VP_MM_CASE(2, 16, false) VP_MM_CASE(4, 16, false) VP_MM_CASE(8, 16, false) VP_MM_CASE(8, 8, false)
+        VP_MM_CASE(8, 1, false) VP_MM_CASE(8, 16, true) VP_MM_CASE(8, 1, true)
 #undef VP_MM_CASE
             return static_cast<int>(hipErrorInvalidConfiguration);
         return static_cast<int>(hipGetLastError());

@@ -84,21 +84,25 @@ constexpr int resize_stream_bytes() { return 3 * 64 * kRsPx + 4 * 64 * 3; }
 // workgroup.
 constexpr int patch14_windows(int out_bf16) { return out_bf16 ? 3 : 2; }
 
-// The uint8 writer's form with both passes on the matrix cores (launch shape kx =
-// kRsMmShape; m = T, the loads per chunk of 16 source rows: 4 T lanes of four
-// pixels cover a band's source span, plus kRsMmTwo where a group of 16 output
-// rows can read more than four chunks; px = A, the pixels that the windows of 16
-// columns start on a multiple of: 16, 8 or 1): output columns per wave, most chunks
-// that a group of 16 output rows reads, and its LDS: the chunk's source
+// The uint8 writer's form with both passes on the matrix cores (launch shape
+// kx = kRsMmShape; m = T, the loads per chunk of 16 source rows: 4 T lanes of
+// four pixels cover a band's source span, plus kRsMmTwo where a group of 16
+// output rows can read more than four chunks, plus kRsMmWide where 16 columns
+// read more than 64 source pixels; px = A, the pixels that the windows of 16
+// columns start on a multiple of: 16, 8 or 1): output columns per wave, most
+// chunks that a group of 16 output rows reads, and its LDS: the chunk's source
 // pixels as three planes of 16 rows (16 bytes more than a row's pixels, so
 // that eight rows' 16-byte reads meet all banks) and a ring of chunks of
 // horizontal sums (16 rows x columns x 3 channels).
 constexpr int kRsMmShape = 128;
-constexpr int kRsMmCols = 32;
-constexpr int kRsMmRing = 8;
 constexpr int kRsMmTwo = 16;
+constexpr int kRsMmWide = 32;
+constexpr int kRsMmRing = 8;
+constexpr int resize_mm_cols(bool wide) { return wide ? 16 : 32; }
 constexpr int resize_mm_plane_row(int t) { return 16 * t + 16; }
-constexpr int resize_mm_bytes(int t, int ring) { return 3 * 16 * resize_mm_plane_row(t) + ring * 3 * kRsMmCols * 16; }
+constexpr int resize_mm_bytes(int t, int ring, bool wide) {
+    return 3 * 16 * resize_mm_plane_row(t) + ring * 3 * resize_mm_cols(wide) * 16;
+}
 
 // Kernel an item is routed to.
 enum Route : int32_t { kRouteGeneric = 0, kRouteStream = 1, kRoutePatch = 2, kRouteResize = 3 };

@@ -169,6 +169,10 @@ MM_CASES = [
     (120, 183, 64, 64, 16),
     (290, 365, 96, 128, 16),
     (290, 202, 96, 64, 16),
+    (400, 441, 96, 96, 16),     # wide: windows of 128 pixels, 16-column bands
+    (372, 373, 64, 64, 16),
+    (120, 395, 64, 64, 16),     # wide at any pixel
+    (301, 655, 84, 140, 14),
     (203, 199, 64, 64, 16),
     (330, 211, 64, 64, 16),
     (61, 117, 56, 56, 14),
