@@ -243,7 +243,9 @@ bool generic_subtile(const AxisFilter& fx, int32_t win, int32_t* rh, int32_t* cw
 // kernel shapes take that many is up to the caller).
 constexpr float kSlotScale = 16777216.0f;   // 2^24
 
-int32_t build_slots(const AxisFilter& f, std::vector<int32_t>* words, bool fixed = false) {
+// With slots > 0 the table has that many slots a row (no fewer than the axis
+// needs).
+int32_t build_slots(const AxisFilter& f, std::vector<int32_t>* words, bool fixed = false, int32_t slots = 0) {
     const int32_t n_in = f.n_in, n_out = f.n_out;
     const int32_t rows = n_in + vp::kSlotMax;
     std::vector<int32_t> close(n_out, 0);
@@ -266,7 +268,8 @@ int32_t build_slots(const AxisFilter& f, std::vector<int32_t>* words, bool fixed
         most = open > most ? open : most;
     }
     if (most > vp::kSlotWords) return -1;
-    const int32_t m = most < 4 ? 4 : most;
+    if (slots > 0 && (slots < most || slots > vp::kSlotWords)) return -1;
+    const int32_t m = slots > 0 ? slots : (most < 4 ? 4 : most);
     // close_row[n_out] and [n_out + 1]: never reached (kernels read one close row ahead)
     words->assign(size_t(rows) * m + n_out + 2, 0);
     (*words)[size_t(rows) * m + n_out] = INT32_MAX;
@@ -563,7 +566,7 @@ struct SlotEntry {
     std::vector<int32_t> words;
 };
 using ColumnKey = std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t, bool>;   // n_in, n_out, kx, band, row_px, fixed
-using SlotKey = std::tuple<int32_t, int32_t, bool>;                                 // n_in, n_out, fixed
+using SlotKey = std::tuple<int32_t, int32_t, bool, int32_t>;                        // n_in, n_out, fixed, slots (0: its own)
 
 constexpr size_t kTableCacheMax = 4096;
 std::mutex g_cache_mu;
@@ -671,6 +674,84 @@ struct UnitSplit {
     int32_t end(int64_t u) const { return static_cast<int32_t>(u + 1 == n ? h : group * (groups * (u + 1) / n)); }
 };
 
+// Vector instructions per source row of a wave (with the output rows that
+// close on it), read off the compiled kernels.
+int64_t row_instructions(const StreamShape& sh, const vp::DevItem& d) {
+    const int64_t m = sh.m, kx = sh.kx;
+    if (sh.px < 0) {   // x-first: align, extract, window sums, slots; closes
+        const int64_t cols = vp::xfirst_db(sh.px) > 0 ? 2 : 1;
+        return (3 * kx + 3) / 4 + 3 * ((kx + 1) / 2) + cols * 3 * (kx + m) + 4 + 12 * d.h / d.H;
+    }
+    return 3 * sh.px * m + 2 * sh.px + 4 + (4 * kx + 3 * sh.px + 12) * d.h / d.H;
+}
+
+// Fewer launches: two kernel shapes of a batch become one, with the larger of
+// their slots and taps (more slots and taps hold zero weights, which change no
+// bit of the sums), where the extra instructions cost less than a launch does.
+// A launch costs its call about 5 us on the host, and a small one leaves the
+// chip waiting for its last unit; the chip issues about 3 million wave
+// instructions in that time.  Measured, kernel us before and
+// after: 16 images 71 -> 26, 4 images 55 -> 16, 24 images with small and large
+// ones 160 -> 113 (11 launches -> 4); from half the limit to ten times it the
+// same.
+constexpr int64_t kMergeInstructions = 3000000;
+
+
+void merge_shapes(const vp_item* items, const std::vector<vp::DevItem>& dev, const std::vector<int64_t>& distinct,
+                  int32_t patch, std::vector<StreamShape>* shapes) {
+    std::map<std::tuple<int32_t, int32_t, int32_t>, std::vector<int32_t>> groups;   // (px, m, kx) -> items
+    for (size_t b = 0; b < dev.size(); ++b)
+        if (dev[b].route == vp::kRouteStream)
+            groups[std::make_tuple((*shapes)[b].px, (*shapes)[b].m, (*shapes)[b].kx)].push_back(static_cast<int32_t>(b));
+    while (groups.size() > 1) {
+        int64_t best = kMergeInstructions;
+        auto best_a = groups.end(), best_b = groups.end();
+        std::tuple<int32_t, int32_t, int32_t> best_key;
+        for (auto a = groups.begin(); a != groups.end(); ++a)
+            for (auto b = std::next(a); b != groups.end(); ++b) {
+                const int32_t px = std::get<0>(a->first);
+                if (std::get<0>(b->first) != px || px == vp::xfirst_px(2)) continue;   // (pairs keep their own taps)
+                StreamShape to;
+                to.px = px;
+                to.m = std::max(std::get<1>(a->first), std::get<1>(b->first));
+                to.kx = std::max(std::get<2>(a->first), std::get<2>(b->first));
+                if (px < 0 ? !vp::xfirst_shape_supported(to.m, to.kx, vp::xfirst_db(px), patch)
+                           : !vp::stream_shape_supported(to.m, to.kx, px))
+                    continue;
+                int64_t extra = 0;
+                bool fits = true;
+                for (const auto* g : {&a->second, &b->second})
+                    for (const int32_t k : *g) {
+                        const StreamShape& sh = (*shapes)[k];
+                        const vp::DevItem& d = dev[k];
+                        // (every load of a window still ends below 4 GiB, a source row still holds its taps)
+                        fits = fits && int64_t(items[k].src_h + vp::kSlotMax + 8) * items[k].src_w * 3 + 3 * to.kx + 64 <
+                                           (int64_t(1) << 32);
+                        extra += distinct[k] * sh.bands * d.H * (row_instructions(to, d) - row_instructions(sh, d));
+
+                    }
+                if (fits && extra < best) {
+                    best = extra;
+                    best_a = a;
+                    best_b = b;
+                    best_key = std::make_tuple(px, to.m, to.kx);
+                }
+            }
+        if (best_a == groups.end()) return;
+        std::vector<int32_t> both = std::move(best_a->second);
+        both.insert(both.end(), best_b->second.begin(), best_b->second.end());
+        std::sort(both.begin(), both.end());
+        for (const int32_t k : both) {
+            (*shapes)[k].m = std::get<1>(best_key);
+            (*shapes)[k].kx = std::get<2>(best_key);
+        }
+        groups.erase(best_a);
+        groups.erase(best_b);
+        auto& into = groups[best_key];   // (both were joined into a shape that one of them may have had)
+        into.insert(into.end(), both.begin(), both.end());
+    }
+}
+
 // Lays out the streaming units as launches and their workgroup lists.
 int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, Plan* p) {
     // Units of one kernel shape form one launch, whatever their widths.  Its
@@ -773,22 +854,23 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
     };
     auto window_table = [&](PlanAxis& a) { return a.windows >= 0 ? a.windows : a.windows = append({a.entry, &a.entry->words}); };
     auto start_table = [&](PlanAxis& a) { return a.starts >= 0 ? a.starts : a.starts = append({a.entry, &a.entry->f.start}); };
-    std::map<SlotKey, std::pair<int32_t, std::shared_ptr<const SlotEntry>>> slot_tables;
-    auto slots_for = [&](const AxisFilter& f, int32_t* off, int32_t* m) -> bool {
-        const SlotKey key = std::make_tuple(f.n_in, f.n_out, false);
+    // the slot table of an axis with its own number of slots, or a larger one
+    auto slot_entry = [&](const AxisFilter& f, int32_t slots) {
+        return cached(g_slot_cache, std::make_tuple(f.n_in, f.n_out, false, slots), [&] {
+            auto v = std::make_shared<SlotEntry>();
+            v->m = build_slots(f, &v->words, false, slots);
+            return std::shared_ptr<const SlotEntry>(std::move(v));
+        });
+    };
+    std::map<SlotKey, int32_t> slot_tables;
+    auto slots_for = [&](const AxisFilter& f, int32_t slots) -> int32_t {
+        const SlotKey key = std::make_tuple(f.n_in, f.n_out, false, slots);
         auto found = slot_tables.find(key);
         if (found == slot_tables.end()) {
-            auto e = cached(g_slot_cache, key, [&] {
-                auto v = std::make_shared<SlotEntry>();
-                v->m = build_slots(f, &v->words);
-                return std::shared_ptr<const SlotEntry>(std::move(v));
-            });
-            const int32_t o = e->m > 0 ? append(std::shared_ptr<const std::vector<int32_t>>(e, &e->words)) : -1;
-            found = slot_tables.emplace(key, std::make_pair(o, e)).first;
+            auto e = slot_entry(f, slots);
+            found = slot_tables.emplace(key, append(std::shared_ptr<const std::vector<int32_t>>(e, &e->words))).first;
         }
-        *off = found->second.first;
-        *m = found->second.second->m;
-        return found->second.first >= 0;
+        return found->second;
     };
     std::map<ColumnKey, int32_t> column_tables;
     auto columns_for = [&](const AxisFilter& f, int32_t kx, int32_t band, int32_t row_px) -> int32_t {
@@ -805,7 +887,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         return found->second;
     };
     std::vector<StreamShape> shapes(n);
-    std::vector<const AxisFilter*> x_axes(n, nullptr);
+    std::vector<const AxisFilter*> x_axes(n, nullptr), y_axes(n, nullptr);
 
     int64_t rows = 0, tiles = 0;
     for (int32_t b = 0; b < n; ++b) {
@@ -833,14 +915,14 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         d.ky = fy->taps;
         d.kx = fx->taps;
         d.route = vp::kRouteGeneric;
-        int32_t m = 0;
         StreamShape sh;
-        const bool slots = slots_for(*fy, &d.sy_off, &m);
+        const int32_t m = slot_entry(*fy, 0)->m;
         const bool near_one = double(it.src_h) <= kXFirstMaxScale * double(it.dst_h);
-        if (slots && ((near_one && xfirst_shape(it, *fx, m, P, false, &sh)) || stream_shape(it, *fx, m, P, &sh))) {
+        if (m > 0 && ((near_one && xfirst_shape(it, *fx, m, P, false, &sh)) || stream_shape(it, *fx, m, P, &sh))) {
             d.route = vp::kRouteStream;   // (band and column table below, once the shape is final)
             shapes[b] = sh;
             x_axes[b] = fx;
+            y_axes[b] = fy;
         } else if (!generic_subtile(*fx, 2 * P, &d.rh, &d.cw)) {
             return fail(VP_ERR_CAPACITY, "item " + std::to_string(b) +
                                              ": horizontal filter window too long (downscale too large)");
@@ -919,10 +1001,12 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
                 shapes[b] = sh;
         }
     }
+    merge_shapes(items, p->items, distinct, P, &shapes);
     for (int32_t b = 0; b < n; ++b) {
         vp::DevItem& d = p->items[b];
         if (d.route != vp::kRouteStream) continue;
         const StreamShape& sh = shapes[b];
+        d.sy_off = slots_for(*y_axes[b], sh.m == slot_entry(*y_axes[b], 0)->m ? 0 : sh.m);
         d.band = sh.band;
         d.row_px = sh.px > 0 ? 64 * sh.px : d.W + sh.kx;
         d.sx_off = columns_for(*x_axes[b], sh.kx, sh.band, d.row_px);
@@ -1184,7 +1268,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
     auto start_table = [&](PlanAxis& a) { return a.starts >= 0 ? a.starts : a.starts = append({a.entry, &a.entry->f.start}); };
     std::map<SlotKey, std::pair<int32_t, std::shared_ptr<const SlotEntry>>> slot_tables;
     auto slots_for = [&](const AxisFilter& f, int32_t* off, int32_t* m) -> bool {
-        const SlotKey key = std::make_tuple(f.n_in, f.n_out, true);
+        const SlotKey key = std::make_tuple(f.n_in, f.n_out, true, 0);
         auto found = slot_tables.find(key);
         if (found == slot_tables.end()) {
             auto e = cached(g_slot_cache, key, [&] {
