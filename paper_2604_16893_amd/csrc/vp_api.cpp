@@ -160,8 +160,14 @@ struct Plan {
     int64_t total_rows = 0;
     std::vector<int64_t> byte_off;   // uint8 writer: [n + 1] output byte offsets of the items
     int64_t generic_cost = 0;   // source pixels the general kernel reads, roughly
-    size_t off_items = 0, off_prefix = 0, off_indices = 0, off_tables = 0, off_units = 0, off_wgs = 0,
-           bytes = 0;
+    // tables computed on the device: their pieces, their words, and where they
+    // begin (the blob up to there is copied)
+    std::vector<vp::TableJob> jobs;
+    size_t gen_words = 0;
+    size_t off_items = 0, off_prefix = 0, off_indices = 0, off_tables = 0, off_units = 0, off_wgs = 0, off_jobs = 0,
+           off_gen = 0, bytes = 0;
+    // no tables of the device's: the whole blob is copied
+    void all_copied() { off_jobs = off_gen = bytes; }
 };
 
 int32_t item_patch(const vp_item& it) { return it.patch == 0 ? vp::kPatch : it.patch; }
@@ -227,35 +233,21 @@ bool generic_subtile(const AxisFilter& fx, int32_t win, int32_t* rh, int32_t* cw
 // Streaming-kernel routing and tables
 // ---------------------------------------------------------------------------
 
-// Slot table of a y axis for the streaming kernel.  Output row i lives in
-// accumulator slot i mod M while it is open: from the first row of its
-// window to its close row, the last row of its window or, if that is
-// earlier, the close row of output row i - 1 (close rows never decrease;
-// several output rows close on the same source row when the axis is
-// upscaled, and at the bottom border).  M is the most output rows open at
-// once (at least 4), so two open rows never share a slot.  For every source
-// row y the table holds, per slot s < M, the weight of y in the output row
-// that has slot s at y (zero if that row does not read y), times 2^24 (the
-// kernel reads byte b as the f16 denormal b * 2^-24; the power of two is
-// exact both ways), then the close row of every output row.  With `fixed`
-// the weights are the int32 fixed-point weights of the uint8 writer instead.
-// Returns M, or -1 if the axis needs more than kSlotWords slots (which
-// kernel shapes take that many is up to the caller).
-constexpr float kSlotScale = 16777216.0f;   // 2^24
-
-// With slots > 0 the table has that many slots a row (no fewer than the axis
-// needs).
-int32_t build_slots(const AxisFilter& f, std::vector<int32_t>* words, bool fixed = false, int32_t slots = 0) {
-    const int32_t n_in = f.n_in, n_out = f.n_out;
-    const int32_t rows = n_in + vp::kSlotMax;
+// Slots of a y axis for a streaming kernel.  Output row i lives in accumulator
+// slot i mod M while it is open: from the first row of its window to its close
+// row, the last row of its window (close rows never decrease; several output
+// rows close on the same source row when the axis is upscaled, and at the
+// bottom border).  M is the most output rows open at once (at least 4), so two
+// open rows never share a slot.  Returns M, or -1 if the axis needs more than
+// kSlotWords slots (which kernel shapes take that many is up to the caller);
+// *close_rows (may be null) receives the close row of every output row.
+int32_t count_slots(const AxisFilter& f, std::vector<int32_t>* close_rows) {
+    const int32_t n_out = f.n_out, rows = f.n_in + vp::kSlotMax;
     std::vector<int32_t> close(n_out, 0);
     for (int32_t i = 0; i < n_out; ++i) {
-        int32_t c = f.start[i] + f.count[i] - 1;
-        if (i > 0 && c < close[i - 1]) c = close[i - 1];
-        if (i > 0 && f.start[i] < f.start[i - 1]) return -1;
-        close[i] = c;
+        close[i] = f.start[i] + f.count[i] - 1;
+        if (i > 0 && (f.start[i] < f.start[i - 1] || close[i] < close[i - 1])) return -1;
     }
-    if (close[n_out - 1] >= rows) return -1;
     // most rows open at once: a row is open on [start, close]
     std::vector<int32_t> delta(rows + 1, 0);
     for (int32_t i = 0; i < n_out; ++i) {
@@ -268,45 +260,29 @@ int32_t build_slots(const AxisFilter& f, std::vector<int32_t>* words, bool fixed
         most = open > most ? open : most;
     }
     if (most > vp::kSlotWords) return -1;
-    if (slots > 0 && (slots < most || slots > vp::kSlotWords)) return -1;
-    const int32_t m = slots > 0 ? slots : (most < 4 ? 4 : most);
-    // close_row[n_out] and [n_out + 1]: never reached (kernels read one close row ahead)
-    words->assign(size_t(rows) * m + n_out + 2, 0);
-    (*words)[size_t(rows) * m + n_out] = INT32_MAX;
-    (*words)[size_t(rows) * m + n_out + 1] = INT32_MAX;
-    float* w = reinterpret_cast<float*>(words->data());
-    for (int32_t i = 0; i < n_out; ++i)
-        for (int32_t k = 0; k < f.count[i]; ++k) {
-            const size_t at = size_t(f.start[i] + k) * m + i % m;
-            if (fixed)
-                (*words)[at] = f.fixed[size_t(i) * f.taps + k];
-            else
-                w[at] = f.weight[size_t(i) * f.taps + k] * kSlotScale;
-        }
-    std::memcpy(words->data() + size_t(rows) * m, close.data(), sizeof(int32_t) * n_out);
-    return m;
+    if (close_rows != nullptr) *close_rows = std::move(close);
+    return most < 4 ? 4 : most;
 }
 
-// Column table of an x axis for the streaming kernel.  Output columns are
-// cut into bands of `band`; a band's source pixels start at the window start
-// of its first column, x0.  For column j: start[j] = (window start - x0),
-// lowered where needed so that start[j] + kx <= row_px, and the window's
-// weights shifted by the amount it was lowered, inside kx zero-padded taps.
-// The caller has checked that every window ends within row_px of its x0.
-void build_columns(const AxisFilter& f, int32_t kx, int32_t band, int32_t row_px,
-                   std::vector<int32_t>* words) {
-    words->assign(size_t(f.n_out) * (1 + kx), 0);
-    int32_t* start = words->data();
-    float* w = reinterpret_cast<float*>(words->data() + f.n_out);
-    for (int32_t j = 0; j < f.n_out; ++j) {
-        const int32_t x0 = f.start[j / band * band];
-        const int32_t l = f.start[j] - x0;
-        const int32_t s = l < row_px - kx ? l : row_px - kx;
-        const int32_t shift = l - s;
-        start[j] = s;
-        for (int32_t k = 0; k < f.count[j]; ++k)
-            w[size_t(j) * kx + shift + k] = f.weight[size_t(j) * f.taps + k];
-    }
+// Slot table of a y axis for the uint8 writer's dot-product form: for every
+// source row y and slot s < M the fixed-point weight of y in the output row
+// that has slot s at y (zero if that row does not read y), then the close row
+// of every output row, and two that no row reaches (the kernel reads one close
+// row ahead).  (The float kernels' slot tables, laid out alike, and their
+// column tables are computed on the device.)  Returns M or -1 as count_slots.
+int32_t build_slots(const AxisFilter& f, std::vector<int32_t>* words) {
+    std::vector<int32_t> close;
+    const int32_t m = count_slots(f, &close);
+    if (m < 0) return -1;
+    const int32_t rows = f.n_in + vp::kSlotMax;
+    words->assign(size_t(rows) * m + f.n_out + 2, 0);
+    for (int32_t i = 0; i < f.n_out; ++i)
+        for (int32_t k = 0; k < f.count[i]; ++k)
+            (*words)[size_t(f.start[i] + k) * m + i % m] = f.fixed[size_t(i) * f.taps + k];
+    std::memcpy(words->data() + size_t(rows) * m, close.data(), sizeof(int32_t) * f.n_out);
+    (*words)[size_t(rows) * m + f.n_out] = INT32_MAX;
+    (*words)[size_t(rows) * m + f.n_out + 1] = INT32_MAX;
+    return m;
 }
 
 // Column table of an x axis for the uint8 streaming writer.  The kernel
@@ -553,6 +529,7 @@ struct AxisEntry {
     AxisFilter f;
     std::vector<int32_t> words;         // the window table: start, count, weight
     std::vector<int32_t> fixed_words;   // the same with the fixed-point weights
+    int32_t slots = -1;                 // accumulator slots of a streaming kernel (count_slots)
 };
 // An axis of one plan: its cached tables, and where the plan holds them (-1:
 // not).  The streaming kernels read the window starts only; the whole window
@@ -566,7 +543,7 @@ struct SlotEntry {
     std::vector<int32_t> words;
 };
 using ColumnKey = std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t, bool>;   // n_in, n_out, kx, band, row_px, fixed
-using SlotKey = std::tuple<int32_t, int32_t, bool, int32_t>;                        // n_in, n_out, fixed, slots (0: its own)
+using SlotKey = std::pair<int32_t, int32_t>;                                        // n_in, n_out
 
 constexpr size_t kTableCacheMax = 4096;
 std::mutex g_cache_mu;
@@ -592,6 +569,7 @@ typename Map::mapped_type cached(Map& map, const typename Map::key_type& key, Ma
 std::shared_ptr<const AxisEntry> make_axis_entry(int32_t n_in, int32_t n_out) {
     auto e = std::make_shared<AxisEntry>();
     build_axis(n_in, n_out, axis_taps(n_in, n_out), &e->f);
+    e->slots = count_slots(e->f, nullptr);
     const AxisFilter& f = e->f;
     e->words.reserve(2 * f.start.size() + f.weight.size());
     e->words.insert(e->words.end(), f.start.begin(), f.start.end());
@@ -836,6 +814,8 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
     p->indices.clear();
     p->tables.clear();
     p->table_words = 0;
+    p->jobs.clear();
+    p->gen_words = 0;
     // Tables come from the process-wide cache; each one used by the batch is
     // copied into the plan once, and the per-call maps keep the cache
     // entries alive while the call uses them.
@@ -853,36 +833,50 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         return a;
     };
     auto window_table = [&](PlanAxis& a) { return a.windows >= 0 ? a.windows : a.windows = append({a.entry, &a.entry->words}); };
-    auto start_table = [&](PlanAxis& a) { return a.starts >= 0 ? a.starts : a.starts = append({a.entry, &a.entry->f.start}); };
-    // the slot table of an axis with its own number of slots, or a larger one
-    auto slot_entry = [&](const AxisFilter& f, int32_t slots) {
-        return cached(g_slot_cache, std::make_tuple(f.n_in, f.n_out, false, slots), [&] {
-            auto v = std::make_shared<SlotEntry>();
-            v->m = build_slots(f, &v->words, false, slots);
-            return std::shared_ptr<const SlotEntry>(std::move(v));
-        });
+    // The streaming kernels' tables are computed on the device (their weights
+    // are functions of the axis alone): their words there, and their pieces.
+    auto words_for = [&](int64_t words) -> int32_t {
+        const int32_t o = static_cast<int32_t>(p->gen_words);
+        p->gen_words += static_cast<size_t>(words);
+        return o;
     };
-    std::map<SlotKey, int32_t> slot_tables;
-    auto slots_for = [&](const AxisFilter& f, int32_t slots) -> int32_t {
-        const SlotKey key = std::make_tuple(f.n_in, f.n_out, false, slots);
-        auto found = slot_tables.find(key);
-        if (found == slot_tables.end()) {
-            auto e = slot_entry(f, slots);
-            found = slot_tables.emplace(key, append(std::shared_ptr<const std::vector<int32_t>>(e, &e->words))).first;
+    auto pieces = [&](vp::TableKind kind, int32_t lanes, const AxisFilter& f, int32_t a, int32_t band, int32_t row_px,
+                      int32_t off, int64_t elements, int64_t piece) {
+        for (int64_t base = 0; base < elements; base += piece)
+            p->jobs.push_back({kind | lanes << 8, f.n_in, f.n_out, a, band, row_px, off, static_cast<int32_t>(base)});
+    };
+    auto lanes_for = [](int32_t taps) {
+        int32_t lanes = 4;
+        while (lanes < taps && lanes < vp::kUploadThreads) lanes *= 2;
+        return lanes;
+    };
+    auto start_table = [&](PlanAxis& a) {
+        if (a.starts < 0) {
+            const AxisFilter& f = a.entry->f;
+            a.starts = words_for(f.n_out);
+            pieces(vp::kTableStarts, 1, f, 0, 0, 0, a.starts, f.n_out, vp::kTablePiece);
+        }
+        return a.starts;
+    };
+    std::map<std::tuple<int32_t, int32_t, int32_t>, int32_t> slot_tables;
+    auto slots_for = [&](const AxisFilter& f, int32_t m) -> int32_t {
+        const auto [found, made] = slot_tables.emplace(std::make_tuple(f.n_in, f.n_out, m), 0);
+        if (made) {
+            const int64_t weights = int64_t(f.n_in + vp::kSlotMax) * m;
+            const int32_t lanes = lanes_for(f.taps), off = words_for(weights + f.n_out + 2);
+            found->second = off;
+            pieces(vp::kTableSlots, lanes, f, m, 0, 0, off, f.n_out, vp::table_outputs(lanes));
+            pieces(vp::kTableZeros, 1, f, m, 0, 0, off, weights + 2, vp::kTablePiece);
         }
         return found->second;
     };
-    std::map<ColumnKey, int32_t> column_tables;
+    std::map<std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t>, int32_t> column_tables;
     auto columns_for = [&](const AxisFilter& f, int32_t kx, int32_t band, int32_t row_px) -> int32_t {
-        const ColumnKey key = std::make_tuple(f.n_in, f.n_out, kx, band, row_px, false);
-        auto found = column_tables.find(key);
-        if (found == column_tables.end()) {
-            auto e = cached(g_column_cache, key, [&] {
-                auto v = std::make_shared<std::vector<int32_t>>();
-                build_columns(f, kx, band, row_px, v.get());
-                return std::shared_ptr<const std::vector<int32_t>>(std::move(v));
-            });
-            found = column_tables.emplace(key, append(e)).first;
+        const auto [found, made] = column_tables.emplace(std::make_tuple(f.n_in, f.n_out, kx, band, row_px), 0);
+        if (made) {
+            const int32_t lanes = lanes_for(kx), off = words_for(int64_t(f.n_out) * (1 + kx));
+            found->second = off;
+            pieces(vp::kTableColumns, lanes, f, kx, band, row_px, off, f.n_out, vp::table_outputs(lanes));
         }
         return found->second;
     };
@@ -916,7 +910,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         d.kx = fx->taps;
         d.route = vp::kRouteGeneric;
         StreamShape sh;
-        const int32_t m = slot_entry(*fy, 0)->m;
+        const int32_t m = ay.entry->slots;
         const bool near_one = double(it.src_h) <= kXFirstMaxScale * double(it.dst_h);
         if (m > 0 && ((near_one && xfirst_shape(it, *fx, m, P, false, &sh)) || stream_shape(it, *fx, m, P, &sh))) {
             d.route = vp::kRouteStream;   // (band and column table below, once the shape is final)
@@ -1006,7 +1000,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         vp::DevItem& d = p->items[b];
         if (d.route != vp::kRouteStream) continue;
         const StreamShape& sh = shapes[b];
-        d.sy_off = slots_for(*y_axes[b], sh.m == slot_entry(*y_axes[b], 0)->m ? 0 : sh.m);
+        d.sy_off = slots_for(*y_axes[b], sh.m);
         d.band = sh.band;
         d.row_px = sh.px > 0 ? 64 * sh.px : d.W + sh.kx;
         d.sx_off = columns_for(*x_axes[b], sh.kx, sh.band, d.row_px);
@@ -1055,14 +1049,24 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         p->off_tables = align_up(p->off_indices + sizeof(int32_t) * p->indices.size());
         p->off_units = align_up(p->off_tables + sizeof(int32_t) * p->table_words);
         p->off_wgs = align_up(p->off_units + sizeof(vp::StreamUnit) * p->units.size());
-        p->bytes = align_up(p->off_wgs + sizeof(uint32_t) * p->wgs.size());
+        p->off_jobs = align_up(p->off_wgs + sizeof(uint32_t) * p->wgs.size());
+        p->off_gen = align_up(p->off_jobs + sizeof(vp::TableJob) * p->jobs.size());
+        p->bytes = align_up(p->off_gen + sizeof(int32_t) * p->gen_words);
         return VP_OK;
     };
-    const int32_t st = lay_out(short_rows);
+    int32_t st = lay_out(short_rows);
     // (more units make a larger plan: one that no longer fits the no-alloc
     // entry's plan memory keeps the longer units)
-    if (st == VP_OK && short_rows > 0 && p->bytes > static_cast<size_t>(vp::kNoAllocPlanBytes)) return lay_out(0);
-    return st;
+    if (st == VP_OK && short_rows > 0 && p->bytes > static_cast<size_t>(vp::kNoAllocPlanBytes)) st = lay_out(0);
+    if (st != VP_OK) return st;
+    // the computed tables' offsets, from the first tables section like the others
+    const int64_t gen = static_cast<int64_t>(p->off_gen - p->off_tables) / 4;
+    if (gen + static_cast<int64_t>(p->gen_words) > INT32_MAX) return fail(VP_ERR_CAPACITY, "the plan's tables exceed 8 GiB");
+    for (vp::TableJob& j : p->jobs) j.off += static_cast<int32_t>(gen);
+    for (vp::DevItem& d : p->items)
+        if (d.route == vp::kRouteStream)
+            for (int32_t* off : {&d.ty_off, &d.tx_off, &d.sy_off, &d.sx_off}) *off += static_cast<int32_t>(gen);
+    return VP_OK;
 }
 
 // Plan of vp_patchify_batch: items whose frames are already at the target
@@ -1126,6 +1130,7 @@ int32_t build_patch_plan(const vp_item* items, int32_t n, Plan* p) {
     p->off_units = p->off_tables;
     p->off_wgs = p->off_tables;
     p->bytes = p->off_tables;
+    p->all_copied();
     return VP_OK;
 }
 
@@ -1175,6 +1180,7 @@ int32_t build_rows_plan(const vp_item* items, int32_t n, Plan* p) {
     p->off_units = p->off_indices;
     p->off_wgs = p->off_indices;
     p->bytes = p->off_indices;
+    p->all_copied();
     return VP_OK;
 }
 
@@ -1268,12 +1274,12 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
     auto start_table = [&](PlanAxis& a) { return a.starts >= 0 ? a.starts : a.starts = append({a.entry, &a.entry->f.start}); };
     std::map<SlotKey, std::pair<int32_t, std::shared_ptr<const SlotEntry>>> slot_tables;
     auto slots_for = [&](const AxisFilter& f, int32_t* off, int32_t* m) -> bool {
-        const SlotKey key = std::make_tuple(f.n_in, f.n_out, true, 0);
+        const SlotKey key = std::make_pair(f.n_in, f.n_out);
         auto found = slot_tables.find(key);
         if (found == slot_tables.end()) {
             auto e = cached(g_slot_cache, key, [&] {
                 auto v = std::make_shared<SlotEntry>();
-                v->m = build_slots(f, &v->words, true);
+                v->m = build_slots(f, &v->words);
                 return std::shared_ptr<const SlotEntry>(std::move(v));
             });
             const int32_t o = e->m > 0 ? append(std::shared_ptr<const std::vector<int32_t>>(e, &e->words)) : -1;
@@ -1454,6 +1460,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
     p->off_units = align_up(p->off_tables + sizeof(int32_t) * p->table_words);
     p->off_wgs = align_up(p->off_units + sizeof(vp::StreamUnit) * p->units.size());
     p->bytes = align_up(p->off_wgs + sizeof(uint32_t) * p->wgs.size());
+    p->all_copied();
     return VP_OK;
 }
 
@@ -1559,7 +1566,8 @@ int32_t hip_fail(hipError_t e, const char* what) {
     return fail(VP_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-// Writes the plan blob (p.bytes bytes, the layout of vp_plan.h) to `base`:
+// Writes the copied part of the plan blob (p.off_gen bytes, the layout of
+// vp_plan.h) to `base`:
 // each section, then zeros up to the next one (the gaps are never read;
 // zeroing them keeps the blob deterministic).
 void pack_plan(const Plan& p, uint8_t* base) {
@@ -1575,7 +1583,8 @@ void pack_plan(const Plan& p, uint8_t* base) {
                     sizeof(int32_t) * part.second->size());
     put(p.off_tables + sizeof(int32_t) * p.table_words, nullptr, 0, p.off_units);
     put(p.off_units, p.units.data(), sizeof(vp::StreamUnit) * p.units.size(), p.off_wgs);
-    put(p.off_wgs, p.wgs.data(), sizeof(uint32_t) * p.wgs.size(), p.bytes);
+    put(p.off_wgs, p.wgs.data(), sizeof(uint32_t) * p.wgs.size(), p.off_jobs);
+    put(p.off_jobs, p.jobs.data(), sizeof(vp::TableJob) * p.jobs.size(), p.off_gen);
 }
 
 int32_t upload_plan(const Plan& p, void* workspace, hipStream_t stream) {
@@ -1595,11 +1604,11 @@ int32_t upload_plan(const Plan& p, void* workspace, hipStream_t stream) {
         e = hipEventCreateWithFlags(&s.done, hipEventDisableTiming);
         if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
     }
-    if (s.cap < p.bytes) {
+    if (s.cap < p.off_gen) {
         if (s.host != nullptr) (void)hipHostFree(s.host);
         s.host = nullptr;
         s.cap = 0;
-        size_t cap = align_up(p.bytes * 2);
+        size_t cap = align_up(p.off_gen * 2);
         e = hipHostMalloc(&s.host, cap, hipHostMallocCoherent);
         if (e != hipSuccess) return hip_fail(e, "hipHostMalloc");
         s.cap = cap;
@@ -1608,7 +1617,10 @@ int32_t upload_plan(const Plan& p, void* workspace, hipStream_t stream) {
     void* src = nullptr;
     e = hipHostGetDevicePointer(&src, s.host, 0);
     if (e != hipSuccess) return hip_fail(e, "hipHostGetDevicePointer");
-    const int err = vp::launch_upload(workspace, src, static_cast<int64_t>(p.bytes), stream);
+    const int err = vp::launch_upload(
+        workspace, src, static_cast<int64_t>(p.off_gen),
+        reinterpret_cast<const vp::TableJob*>(static_cast<const uint8_t*>(src) + p.off_jobs),
+        static_cast<int>(p.jobs.size()), reinterpret_cast<int32_t*>(static_cast<uint8_t*>(workspace) + p.off_tables), stream);
     if (err != 0) return hip_fail(static_cast<hipError_t>(err), "plan upload launch");
     e = hipEventRecord(s.done, stream);
     if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -1784,10 +1796,15 @@ int32_t run_batch(bool patch_only, const vp_item* items, int32_t n_items, const 
         if (err != 0) return hip_fail(static_cast<hipError_t>(err), "hipGetSymbolAddress (plan memory)");
         // pageable host memory: the copy has read it when hipMemcpyAsync returns
         thread_local std::vector<uint8_t> blob;
-        if (blob.size() < p.bytes) blob.resize(p.bytes);
+        if (blob.size() < p.off_gen) blob.resize(p.off_gen);
         pack_plan(p, blob.data());
-        const hipError_t e = hipMemcpyAsync(workspace, blob.data(), p.bytes, hipMemcpyHostToDevice, stream);
+        const hipError_t e = hipMemcpyAsync(workspace, blob.data(), p.off_gen, hipMemcpyHostToDevice, stream);
         if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (plan)");
+        auto* const base = static_cast<uint8_t*>(workspace);
+        const int te = vp::launch_upload(nullptr, nullptr, 0, reinterpret_cast<const vp::TableJob*>(base + p.off_jobs),
+                                         static_cast<int>(p.jobs.size()), reinterpret_cast<int32_t*>(base + p.off_tables),
+                                         stream);
+        if (te != 0) return hip_fail(static_cast<hipError_t>(te), "plan tables launch");
     } else {
         if (workspace_bytes < static_cast<int64_t>(p.bytes))
             return fail(VP_ERR_CAPACITY, "workspace holds " + std::to_string(workspace_bytes) +

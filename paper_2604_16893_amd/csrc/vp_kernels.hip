@@ -100,14 +100,146 @@ __device__ __forceinline__ int find_item(const int32_t* prefix, int n_items, int
 // Plan upload
 // ===========================================================================
 
-// The plan blob from pinned host memory to the workspace, 64 bytes a thread
-// with its four loads in flight: a small plan costs the host link's latency
-// (about 2 us), a large one its rate.  A kernel and not hipMemcpyAsync: the
-// copy engine's hand-over on both sides left the chip idle for about 10 us a
-// call (one photo 33 -> 23 us a call, a 480p clip 90 -> 80).
-__global__ __launch_bounds__(kUploadThreads) void upload_kernel(uint4* __restrict__ dst,
-                                                                const uint4* __restrict__ src, int n16) {
-    const int i0 = blockIdx.x * (4 * kUploadThreads) + threadIdx.x;
+// Filter tables on the device: the host's double expressions in the same
+// order and without contraction (IEEE operations on both sides), so that the
+// weights are the same bits.  Keys (1981) cubic, a = -1/2.
+__device__ double cubic_a_half(double x) {
+#pragma clang fp contract(off)
+    const double t = __builtin_fabs(x);
+    if (t < 1.0) return 1.5 * t * t * t - 2.5 * t * t + 1.0;
+    if (t < 2.0) return -0.5 * t * t * t + 2.5 * t * t - 4.0 * t + 2.0;
+    return 0.0;
+}
+
+struct AxisWindow {
+    double centre, sigma;
+    int lo, hi;
+};
+
+// Window of output i; scale = n_in / n_out.
+__device__ AxisWindow axis_window(double scale, int n_in, int i) {
+#pragma clang fp contract(off)
+    const double s = scale > 1.0 ? scale : 1.0;
+    const double support = 2.0 * s;
+    const double c = (static_cast<double>(i) + 0.5) * scale;
+    double a = __builtin_floor(c - support + 0.5);
+    double b = __builtin_floor(c + support + 0.5);
+    if (a < 0.0) a = 0.0;
+    if (b > n_in) b = n_in;
+    return AxisWindow{c, s, static_cast<int>(a), static_cast<int>(b)};
+}
+
+// Whether a weight stands in slot s of source row y: whether the window of an
+// output row i = s (mod m) holds y.
+__device__ bool slot_taken(double scale, int n_in, int n_out, int m, int y, int s) {
+    const double reach = 2.0 * (scale > 1.0 ? scale : 1.0) + 2.0;
+    int i = max(0, static_cast<int>((y - reach) / scale) - 1);   // windows before it end at or before y
+    const int last = min(n_out - 1, static_cast<int>((y + 1 + reach) / scale) + 1);
+    for (i += ((s - i) % m + m) % m; i <= last; i += m) {
+        const AxisWindow w = axis_window(scale, n_in, i);
+        if (w.lo <= y && y < w.hi) return true;
+    }
+    return false;
+}
+
+// One piece of a table (the layouts are in vp_plan.h), by a workgroup.  The
+// taps of an output are evaluated side by side, one a lane, and every lane adds
+// all of them in order from LDS: a piece takes about three divisions' time,
+// where a lane that evaluated its output's taps one after another took 3 us
+// more of every small call.
+__device__ void table_piece(const TableJob& t, int32_t* tables, double (&raws)[kUploadThreads]) {
+#pragma clang fp contract(off)
+    const int kind = t.kind_lanes & 255, lanes = t.kind_lanes >> 8;
+    const int n_in = t.n_in, n_out = t.n_out, tid = threadIdx.x;
+    const double scale = static_cast<double>(n_in) / static_cast<double>(n_out);
+    int32_t* const out = tables + t.off;
+    if (kind == kTableStarts) {
+        for (int e = t.base + tid; e < min(n_out, t.base + kTablePiece); e += kUploadThreads)
+            out[e] = axis_window(scale, n_in, e).lo;
+        return;
+    }
+    const int m = t.a, rows = n_in + kSlotMax;
+    if (kind == kTableZeros) {
+        const int words = rows * m;
+        for (int e = t.base + tid; e < min(words + 2, t.base + kTablePiece); e += kUploadThreads) {
+            if (e >= words)
+                out[e + n_out] = INT32_MAX;   // close rows that are never reached
+            else if (e / m >= n_in || !slot_taken(scale, n_in, n_out, m, e / m, e % m))
+                out[e] = 0;
+        }
+        return;
+    }
+    if (kind == kTableSlots && lanes == kUploadThreads) {   // more than 128 taps: an output at a time
+        for (int j = t.base; j < min(n_out, t.base + table_outputs(lanes)); ++j) {
+            const AxisWindow w = axis_window(scale, n_in, j);
+            const int count = w.hi - w.lo;
+            double sum = 0.0;
+            for (int q0 = 0; q0 < count; q0 += kUploadThreads) {
+                raws[tid] = cubic_a_half((static_cast<double>(w.lo + q0 + tid) + 0.5 - w.centre) / w.sigma);
+                __syncthreads();
+                for (int q = 0; q < min(kUploadThreads, count - q0); ++q) sum += raws[q];
+                __syncthreads();
+            }
+            for (int q = tid; q < count; q += kUploadThreads)
+                reinterpret_cast<float*>(out)[int64_t(w.lo + q) * m + j % m] =
+                    static_cast<float>(cubic_a_half((static_cast<double>(w.lo + q) + 0.5 - w.centre) / w.sigma) / sum) *
+                    16777216.0f;
+            if (tid == 0) out[int64_t(rows) * m + j] = w.hi - 1;
+        }
+        return;
+    }
+    const int per = kUploadThreads / lanes, k = tid % lanes;   // outputs at a time, the lane's tap
+    const double* const mine = raws + tid - k;
+    for (int j0 = t.base; j0 < min(n_out, t.base + table_outputs(lanes)); j0 += per) {   // (uniform: barriers inside)
+        const int j = j0 + tid / lanes;
+        const AxisWindow w = axis_window(scale, n_in, min(j, n_out - 1));
+        const int count = w.hi - w.lo;
+        raws[tid] = cubic_a_half((static_cast<double>(w.lo + k) + 0.5 - w.centre) / w.sigma);
+        __syncthreads();
+        double sum = 0.0;
+        for (int q = 0; q < count; ++q) sum += mine[q];
+        if (j < n_out) {
+            if (kind == kTableSlots) {
+                if (k < count)   // (times 2^24: the kernels read bytes as f16 denormals)
+                    reinterpret_cast<float*>(out)[int64_t(w.lo + k) * m + j % m] =
+                        static_cast<float>(mine[k] / sum) * 16777216.0f;
+                if (k == 0) out[int64_t(rows) * m + j] = w.hi - 1;
+            } else {
+                // columns: starts from the band's first pixel, lowered so that
+                // start + KX stays inside the row, and the weights shifted to match
+                const int kx = t.a;
+                const int l = w.lo - axis_window(scale, n_in, j / t.band * t.band).lo;
+                const int start = min(l, t.row_px - kx), q = k - (l - start);
+                if (k < kx)
+                    reinterpret_cast<float*>(out)[n_out + int64_t(j) * kx + k] =
+                        q >= 0 && q < count ? static_cast<float>(mine[q] / sum) : 0.0f;
+                if (k == 0) out[j] = start;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The plan: the first `copy_blocks` workgroups copy the blob from pinned host
+// memory to the workspace, 64 bytes a thread with its four loads in flight (a
+// small plan costs the host link's latency, about 2 us, a large one its rate);
+// the others compute a piece of a table each.  A kernel and not
+// hipMemcpyAsync: the copy engine's hand-over on both sides left the chip idle
+// for about 10 us a call (one photo 33 -> 23 us a call, a 480p clip 90 -> 80).
+// Tables computed here and not copied: packing and copying 1.2 MB of them
+// took 24 ragged images 50 us of a call (190 -> 137).
+__global__ __launch_bounds__(kUploadThreads) void upload_kernel(uint4* __restrict__ dst, const uint4* __restrict__ src,
+                                                                int n16, int copy_blocks,
+                                                                const TableJob* __restrict__ jobs,
+                                                                int32_t* __restrict__ tables) {
+    __shared__ double raws[kUploadThreads];
+    const int block = blockIdx.x;
+    if (block >= copy_blocks) {
+        const TableJob t = jobs[block - copy_blocks];
+        table_piece(t, tables, raws);
+        return;
+    }
+    const int i0 = block * (4 * kUploadThreads) + threadIdx.x;
     uint4 v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -2219,12 +2351,14 @@ int noalloc_plan_memory(void** ptr) {
     return 0;
 }
 
-int launch_upload(void* dst, const void* src, int64_t bytes, hipStream_t stream) {
-    if (bytes <= 0) return 0;
-    if (bytes % 16 != 0 || bytes / 16 > INT32_MAX) return static_cast<int>(hipErrorInvalidValue);
+int launch_upload(void* dst, const void* src, int64_t bytes, const TableJob* jobs, int n_jobs, int32_t* tables,
+                  hipStream_t stream) {
+    if (bytes < 0 || bytes % 16 != 0 || bytes / 16 > INT32_MAX) return static_cast<int>(hipErrorInvalidValue);
     const int n16 = static_cast<int>(bytes / 16);
-    hipLaunchKernelGGL(upload_kernel, dim3((n16 + 4 * kUploadThreads - 1) / (4 * kUploadThreads)),
-                       dim3(kUploadThreads), 0, stream, static_cast<uint4*>(dst), static_cast<const uint4*>(src), n16);
+    const int copy_blocks = (n16 + 4 * kUploadThreads - 1) / (4 * kUploadThreads);
+    if (copy_blocks + n_jobs <= 0) return 0;
+    hipLaunchKernelGGL(upload_kernel, dim3(static_cast<unsigned>(copy_blocks + n_jobs)), dim3(kUploadThreads), 0, stream,
+                       static_cast<uint4*>(dst), static_cast<const uint4*>(src), n16, copy_blocks, jobs, tables);
     return static_cast<int>(hipGetLastError());
 }
 

@@ -12,11 +12,15 @@
 //   StreamUnit units[...]                 streaming-kernel work units
 //   uint32     wgs[...]                   streaming-kernel workgroups, grouped per launch:
 //                                         unit index | column band << 20, or kNoWork
+//   TableJob   jobs[...]                  pieces of the tables that follow
+//   int32      tables[...]                the float streaming kernels' tables, computed on the
+//                                         device (not part of the copy; word offsets from the
+//                                         first tables section like the others)
 //
 // Tables (word offsets into `tables`; items with the same axis share them):
 //   window table of an axis n_in -> n_out, K taps:
 //       int32 start[n_out]; int32 count[n_out]; float weight[n_out][K]
-//     (an axis that only streaming kernels use: the starts alone)
+//     (the streaming kernels read a table of the starts alone)
 //   slot table of a y axis n_in -> n_out (streaming kernel), M slots:
 //       [n_in + 6] rows of M words: float weight[slot]
 //         -- output row i is accumulated in slot i mod M from the first row of
@@ -196,11 +200,34 @@ struct StreamLaunch {
 constexpr int64_t kNoAllocPlanBytes = int64_t(16) << 20;
 int noalloc_plan_memory(void** ptr);
 
+// A piece of a table that the device computes from the axis alone, one
+// workgroup's share of the table at word `off`:
+//   starts: the window starts of kTablePiece outputs from `base`;
+//   slots: the weights and close rows of table_outputs(lanes) outputs from
+//     `base` in a slot table of a = M slots;
+//   zeros: kTablePiece words from `base` of the same table, those that no
+//     output row's weight stands in, and the two close rows past the last;
+//   columns: the starts and weights of table_outputs(lanes) outputs from
+//     `base` in a column table of a = KX taps.
+// `lanes` threads work on one output: a power of two, no fewer than its taps
+// (columns: than KX), up to the whole workgroup.
+enum TableKind : int32_t { kTableStarts = 0, kTableSlots = 1, kTableZeros = 2, kTableColumns = 3 };
+struct TableJob {
+    int32_t kind_lanes;   // kind | lanes << 8
+    int32_t n_in, n_out, a, band, row_px, off, base;
+};
+static_assert(sizeof(TableJob) == 32, "TableJob layout");
+constexpr int kUploadThreads = 256;
+constexpr int kTablePiece = 4 * kUploadThreads;
+constexpr int table_outputs(int lanes) { return kTablePiece / lanes; }
+
 // Kernel launchers (vp_kernels.hip).  Return a hipError_t value.
 // The plan blob, `bytes` (a multiple of 16, both ends 16-byte aligned) from
-// host memory the device can read.
-constexpr int kUploadThreads = 256;
-int launch_upload(void* dst, const void* src, int64_t bytes, hipStream_t stream);
+// host memory the device can read, and the tables of `n_jobs` pieces (`jobs`
+// readable by the device: the blob's, in host memory, or with bytes = 0 a copy
+// on the device) into `tables`.
+int launch_upload(void* dst, const void* src, int64_t bytes, const TableJob* jobs, int n_jobs, int32_t* tables,
+                  hipStream_t stream);
 int launch_generic(const PlanView& plan, void* out, int out_dtype, const Norm& norm,
                    hipStream_t stream);
 int launch_stream(const PlanView& plan, const StreamLaunch& launch, void* out, int out_dtype,

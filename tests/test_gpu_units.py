@@ -98,3 +98,41 @@ def test_patch14_bands(H, W, h, w, kind, taps, dtype):
     else:
         res = compare.check_f32(rows.cpu().numpy(), ref)
     assert res["ok"], res
+
+
+@pytest.mark.parametrize("H,W,h,w", [(37, 53, 64, 96), (97, 131, 96, 128), (241, 330, 160, 224), (700, 1291, 256, 448),
+                                     (64, 64, 64, 64), (540, 3840, 96, 672), (33, 5, 32, 32), (1201, 40, 32, 32),
+                                     (9001, 70, 32, 64)])
+def test_device_tables_are_the_hosts_bits(H, W, h, w):
+    """The column weights that the device computes for a plan are the bits of
+    vp_filter_table, for upscales, identity and long windows: the whole table
+    (zero-padded to the kernel's taps) stands in the workspace."""
+    item = vp.Item(torch.zeros((1, H, W, 3), dtype=torch.uint8, device=DEV), [0], h, w)
+    kind, m, kx = (int(v) for v in vp.vp_batch_kernels([item])[0][:3])
+    assert kind in (vp.VP_KERNEL_XFIRST, vp.VP_KERNEL_YFIRST)
+    _, _, rows, ws = vp.vp_batch_layout([item])
+    work = torch.zeros(ws, dtype=torch.uint8, device=DEV)
+    out = torch.empty((rows, vp.VP_ROW), dtype=torch.float32, device=DEV)
+    vp.vp_preprocess_batch([item], MEAN, STD, vp.VP_OUT_F32, out, work)
+    torch.cuda.synchronize()
+    plan = work.cpu().numpy()
+    start, count, weight = vp.vp_filter_table(W, w)
+    words = plan.view(np.int32)
+    table = np.zeros((w, kx), np.float32)
+    table[:, :weight.shape[1]] = weight[:, :kx]
+    at = [k for k in np.flatnonzero(words == table.view(np.int32)[0, 0]) if k + w * kx <= len(words)]
+    assert at, "the first column's first weight is not in the plan"
+    best = max(at, key=lambda k: int((words[k:k + w * kx] == table.view(np.int32).reshape(-1)).sum()))
+    got = words[best:best + w * kx].view(np.float32).reshape(w, kx)
+    for j in range(w):   # a column at its band's right edge has its weights shifted
+        assert any(np.array_equal(got[j], np.roll(table[j], s)) for s in range(kx)), j
+    slots = (weight_slots(H, h, m) * np.float32(2.0 ** 24)).astype(np.float32).tobytes()
+    assert slots in plan.tobytes(), "the slot table is not in the plan"
+
+
+def weight_slots(H, h, m):
+    start, count, weight = vp.vp_filter_table(H, h)
+    table = np.zeros((H + 6, m), np.float32)
+    for i in range(h):
+        table[start[i]:start[i] + count[i], i % m] = weight[i, :count[i]]
+    return table
