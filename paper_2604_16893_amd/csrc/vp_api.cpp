@@ -440,7 +440,7 @@ int32_t band_span(const AxisFilter& fx, int32_t band) {
 // budget is checked with float32 staging, so the routing does not depend on
 // the output type.
 bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t patch, StreamShape* sh) {
-    if (m < 4 || m > vp::kSlotWords) return false;
+    if (m < 4 || m > vp::kStreamSlots) return false;
     const int32_t mm = m;
     // windows up to 16 taps run their own tap count (at least 4), longer ones a multiple of 4
     const int32_t kx = fx.taps <= 16 ? std::max<int32_t>(fx.taps, 4) : round_up(fx.taps, 4);
@@ -490,6 +490,7 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
 bool xfirst_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t patch, bool pairs_ok,
                   StreamShape* sh) {
     const int32_t kx = std::max<int32_t>(fx.taps, 4);
+    if (m > vp::kStreamSlots) m = m <= 12 ? 12 : 16;   // upscales over about 2x: 12 or 16 slots
     bool pairs = pairs_ok && vp::xfirst_shape_supported(m, kx, 2, patch) && fx.n_out % 2 == 0;
     for (int32_t j = 0; pairs && j + 1 < fx.n_out; j += 2) {
         const int32_t d = fx.start[j + 1] - fx.start[j];
@@ -1220,7 +1221,7 @@ bool resize_tiles(const AxisFilter& fy, const AxisFilter& fx, int32_t* rb, int32
 // The widest band that fits is taken: the horizontal pass costs the same per
 // output column whatever the band, and fewer bands unpack fewer pixels.
 bool resize_stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, StreamShape* sh) {
-    if (m < 4 || m > vp::kSlotWords) return false;
+    if (m < 4 || m > vp::kStreamSlots) return false;
     const int32_t kx = round_up(fx.taps + 3, 4);   // any window start, rounded down to a dword
     if (!vp::resize_stream_supported(m, kx, vp::kRsPx)) return false;
     if (int64_t(it.src_h + vp::kSlotMax + 8) * it.src_w * 3 + 64 >= (int64_t(1) << 32)) return false;

@@ -29,8 +29,8 @@
 //     waves (two neighbouring bands x a pair's two frames) that meet at a
 //     barrier once per patch row, to write whole output rows.
 //
-// Streaming kernel, x first (patch 16, vertical scales up to 1.6, x windows
-// of 4 to 12 taps): the same units, slots and store, but each lane x-filters
+// Streaming kernel, x first (vertical scales up to 1.6, upscales to 4x, x
+// windows of 4 to 12 taps): the same units, slots and store, but each lane x-filters
 // its own window of every source row, loaded straight from the frame, before
 // the y pass into the slots; LDS holds only the stage.
 //
@@ -1249,6 +1249,11 @@ int launch_stream_shape(const PlanView& plan, const StreamLaunch& L, void* out, 
 //     lanes per 128-byte run, as in the y-first kernel.
 // Window bytes past the end of a row are the next row's (or zeros past the
 // frame, from the buffer range check); they meet only zero weights.
+// Upscales over about 2x keep 9 to 16 output rows open: shapes of 12 and 16
+// slots (4 and 5 taps).  They cost 3 multiply-adds a slot per source row, of
+// which there are few; on the general kernel, a workgroup per merge window,
+// the same items took nine times as long (64 frames of 120x160 -> 320x448 in
+// bf16 285 -> 32 us).
 //
 // Patch 14 (single columns, up to 8 taps): four-wave workgroups as in the
 // y-first kernel (two neighbouring bands of 63 columns x the pair's two
@@ -1595,16 +1600,25 @@ __global__ __launch_bounds__(P == 16 ? 64 : 256) void xfirst_kernel(PlanView pla
         pf[k] = load_row(yb0, k);
         __builtin_amdgcn_sched_barrier(0);
     }
+    // a block's slot weights together, or for more than 8 slots a row's (four
+    // rows' would not fit the scalar registers)
+    constexpr int WB = M > kStreamSlots ? 1 : 4;
     for (int yb = yb0; yb < y1; yb += 4) {
         const cptr<float> wblk = slot_w + yb * M;
-        float wk[4][M];
+        float wk[WB][M];
+        if constexpr (WB == 4) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int s = 0; s < M; ++s) wk[k][s] = wblk[k * M + s];
+                for (int s = 0; s < M; ++s) wk[k][s] = wblk[k * M + s];
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int y = yb + k;
+            if constexpr (WB == 1) {
+#pragma unroll
+                for (int s = 0; s < M; ++s) wk[0][s] = wblk[k * M + s];
+            }
             Win& buf = pf[k % PF];
             // align first: the next load then reuses the buffer's registers
             // instead of copying them while it is in flight
@@ -1620,7 +1634,7 @@ __global__ __launch_bounds__(P == 16 ? 64 : 256) void xfirst_kernel(PlanView pla
             __builtin_amdgcn_s_setprio(2);
             buf = load_row(yb + (k + PF) / 4 * 4, (k + PF) % 4);
             __builtin_amdgcn_s_setprio(0);
-            if (y >= y0 && y < y1) process_row(y, a, wk[k]);
+            if (y >= y0 && y < y1) process_row(y, a, wk[WB == 4 ? k : 0]);
         }
     }
 }
@@ -2243,6 +2257,7 @@ int VP_CAT(launch_stream_part, VP_PART)(const PlanView& plan, const StreamLaunch
     VP_XF_CASE(MM, 8, 0) VP_XF_CASE(MM, 9, 0) VP_XF_CASE(MM, 10, 0) VP_XF_CASE(MM, 11, 0) VP_XF_CASE(MM, 12, 0)
 #define VP_XF_PAIR(MM, DB) VP_XF_CASE(MM, 6, DB) VP_XF_CASE(MM, 7, DB) VP_XF_CASE(MM, 8, DB)
     VP_XF_KX(4) VP_XF_KX(5) VP_XF_KX(6) VP_XF_KX(7) VP_XF_KX(8)
+    VP_XF_CASE(12, 4, 0) VP_XF_CASE(12, 5, 0) VP_XF_CASE(16, 4, 0) VP_XF_CASE(16, 5, 0)
     VP_XF_PAIR(4, 2) VP_XF_PAIR(5, 2) VP_XF_PAIR(6, 2) VP_XF_PAIR(7, 2) VP_XF_PAIR(8, 2)
 #undef VP_XF_PAIR
 #undef VP_XF_KX
@@ -2379,7 +2394,7 @@ int launch_resize(const PlanView& plan, void* out, hipStream_t stream) {
 }
 
 bool resize_stream_supported(int m, int kx, int px) {
-    return m >= 4 && m <= kSlotWords && kx >= 8 && kx <= 32 && kx % 4 == 0 && px == kRsPx;
+    return m >= 4 && m <= kStreamSlots && kx >= 8 && kx <= 32 && kx % 4 == 0 && px == kRsPx;
 }
 
 int launch_resize_stream(const PlanView& plan, const StreamLaunch& L, void* out, hipStream_t stream) {
@@ -2453,7 +2468,7 @@ int launch_generic(const PlanView& plan, void* out, int out_dtype, const Norm& n
 bool stream_shape_supported(int m, int kx, int px) {
     if (m < 4 || kx < 4 || kx > 32 || (kx > 16 && kx % 4 != 0)) return false;
     if (m > 6)   // 7 or 8 open rows: vertical upscales up to about 2x, whose x axis has short windows too
-        return m <= kSlotWords && px == 2 && kx <= 8;
+        return m <= kStreamSlots && px == 2 && kx <= 8;
     if (kx <= 16) return px == 2 || (px == 3 && m <= 5);
     // windows of 17 to 32 taps: x downscales of about 3.75x to 7.5x
     return px == 2 || (px == 3 && m <= 5 && kx <= 24);
@@ -2461,7 +2476,9 @@ bool stream_shape_supported(int m, int kx, int px) {
 
 bool xfirst_shape_supported(int m, int kx, int db, int patch) {
     if (patch == 14 && (db != 0 || kx > kXFirstTaps14)) return false;
-    return m >= 4 && m <= kSlotWords && kx >= 4 && (db == 0 ? kx <= 12 : db == 2 && kx >= 6 && kx <= 8);
+    if (m > kStreamSlots)   // upscales over about 2x in y, whose x windows are short too
+        return (m == 12 || m == 16) && db == 0 && (kx == 4 || kx == 5);
+    return m >= 4 && kx >= 4 && (db == 0 ? kx <= 12 : db == 2 && kx >= 6 && kx <= 8);
 }
 
 int launch_stream(const PlanView& plan, const StreamLaunch& L, void* out, int out_dtype,

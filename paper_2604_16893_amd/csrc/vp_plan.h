@@ -56,8 +56,9 @@ constexpr int kRow = 1536;            // 3 * 2 * 16 * 16
 constexpr int kWinElems = 4 * kRow;   // one merge window of one frame pair
 constexpr int kGenericThreads = 256;
 constexpr int kGenericTCap = 8192;    // floats of the general kernel's LDS column tile
-constexpr int kSlotWords = 8;         // most slots of a slot table
-constexpr int kSlotMax = 6;           // most output rows open at once (accumulator slots)
+constexpr int kSlotWords = 16;        // most slots of a slot table (x-first kernel)
+constexpr int kStreamSlots = 8;       // most slots of the y-first kernel and the uint8 writer's dot products
+constexpr int kSlotMax = 6;           // zero rows past a slot table's last source row
 constexpr int kStreamLdsBudget = 64 * 1024;   // LDS of one streaming workgroup (one wave)
 
 // LDS of one streaming workgroup.  Patch 16 (one wave): its source row (64 *

@@ -136,3 +136,36 @@ def weight_slots(H, h, m):
     for i in range(h):
         table[start[i]:start[i] + count[i], i % m] = weight[i, :count[i]]
     return table
+
+
+# Upscales over 2x on the x-first kernel: 12 and 16 slots (3x and 4x exactly,
+# and just past 2x), 4 and 5 column taps, a one-column source, both patches
+UPSCALES = [
+    # H, W, h, w, patch, slots, taps
+    (47, 45, 96, 96, 16, 12, 4),
+    (32, 33, 96, 64, 16, 12, 4),
+    (24, 70, 96, 64, 16, 16, 5),
+    (16, 1, 64, 32, 16, 16, 4),
+    (64, 64, 256, 256, 16, 16, 4),
+    (20, 66, 56, 56, 14, 12, 5),
+    (21, 40, 84, 140, 14, 16, 4),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,W,h,w,patch,slots,taps", UPSCALES)
+def test_upscales_of_many_slots(H, W, h, w, patch, slots, taps, dtype):
+    it = workloads.Item("video", 3, H, W, "uniform", 53, {"mode": "uniform", "n": 3})
+    idx = [1, 2, 0]
+    item = vp.Item(workloads.frames_torch(it, DEV), np.asarray(idx, np.int32), h, w, patch)
+    launches = vp.vp_batch_kernels([item])
+    assert [tuple(int(v) for v in r[:3]) for r in launches] == [(vp.VP_KERNEL_XFIRST, slots, taps)], launches.tolist()
+    print(f"[upscales] {H}x{W} -> {h}x{w} patch {patch} {dtype}", flush=True)
+    rows, _, _ = vp.preprocess([item], MEAN, STD, dtype)
+    torch.cuda.synchronize()
+    ref = oracle.preprocess_item(workloads.frames_np(it), idx, h, w, MEAN, STD, patch=patch)
+    if dtype == "bf16":
+        res = compare.check_bf16(rows.view(torch.int16).cpu().numpy().view(np.uint16), ref)
+    else:
+        res = compare.check_f32(rows.cpu().numpy(), ref)
+    assert res["ok"], res
