@@ -242,7 +242,7 @@ int32_t vp_batch_kernels(const vp_item* items, int32_t n_items, int32_t* launche
  * grid_thw, cu_seqlens: HOST outputs as in vp_batch_layout (may be NULL);
  *   final when the call returns.
  * workspace: DEVICE, >= the workspace_bytes of vp_batch_layout, 256-byte
- *   aligned; the call copies its plan (item table, filter tables, indices)
+ *   aligned; the call writes its plan (item table, filter tables, indices)
  *   there on `stream` and the kernels read it.  It may be reused by the
  *   next call on the same stream.
  * stream: the HIP stream all work is enqueued on (0 = the null stream).

@@ -1,9 +1,10 @@
 // vp_api.cpp -- host side of the C ABI declared in include/vp.h.
 //
 // Host work per call: validate the items, derive grid_thw / cu_seqlens,
-// build the per-axis filter tables (double precision, rounded once to
-// float), pack the plan into one blob in pinned host memory, copy it into
-// the caller's workspace on the caller's stream, and launch the kernels.
+// choose each item's kernel from its axes' windows, pack the plan into one blob
+// in pinned host memory, and launch the kernel that copies it into the
+// caller's workspace and computes the streaming kernels' filter tables there
+// (double precision, rounded once to float), then the kernels themselves.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -521,7 +522,8 @@ bool xfirst_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
 // bound it.
 constexpr double kXFirstMaxScale = 1.6;
 
-// Process-wide cache of per-axis tables.  The same axes recur from call to
+// Process-wide cache of per-axis tables (windows for the planner, weights for
+// the general kernel and the uint8 writer).  The same axes recur from call to
 // call (an RL loop preprocesses batches of the same shapes every step), and
 // building them is most of the host's work for a batch of many shapes.
 // Entries are immutable once built and shared by pointer; a cache is
