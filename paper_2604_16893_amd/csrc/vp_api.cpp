@@ -464,7 +464,9 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
             // and about 12 more
             const int64_t cost = int64_t(waves) * (int64_t(it.src_h) * (3 * px * mm + 2 * px + 4) +
                                                     int64_t(it.dst_h) * (4 * kx + 3 * px + 12));
-            if (best < 0 || cost < best) {
+            // (patch 14: of bands that give the same pairs, the narrowest; a
+            // pair's stage is its workgroup's LDS)
+            if (best < 0 || cost < best || (patch == 14 && cost == best)) {
                 best = cost;
                 sh->m = mm;
                 sh->kx = kx;
