@@ -457,6 +457,10 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
         for (int32_t px = 2; px <= 4; ++px) {
             if (!vp::stream_shape_supported(mm, kx, px)) continue;
             if (span > 64 * px || kx > 64 * px) continue;
+            // (patch 14 with px = 3 in float32: two bands of 63 columns leave
+            // two workgroups a CU their LDS, of 56 three; 900x1600 -> 588
+            // columns 244 -> 261 us for 128 frames, in bf16 188 -> 175)
+            if (patch == 14 && px > 2 && band > 56) continue;
             if (vp::stream_wave_bytes(px, kx, 4, patch, band_patches(band)) > vp::kStreamLdsBudget) continue;
             // vector instructions per wave: per source row 3 px M
             // multiply-adds, about 2 px unpacks and 4 more; per output row
