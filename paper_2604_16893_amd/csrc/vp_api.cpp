@@ -810,7 +810,9 @@ int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, Plan* p) {
     return VP_OK;
 }
 
-int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
+// With `most_slots` below kSlotWords, items that need more open rows than that
+// go to the general kernel, whose plan holds no work units.
+int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots = vp::kSlotWords) {
     if (items == nullptr) return fail(VP_ERR_NULL, "items is NULL");
     if (n < 1) return fail(VP_ERR_ARG, "n_items < 1");
     int32_t P = vp::kPatch;
@@ -921,7 +923,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p) {
         StreamShape sh;
         const int32_t m = ay.entry->slots;
         const bool near_one = double(it.src_h) <= kXFirstMaxScale * double(it.dst_h);
-        if (m > 0 && ((near_one && xfirst_shape(it, *fx, m, P, false, &sh)) || stream_shape(it, *fx, m, P, &sh))) {
+        if (m > 0 && m <= most_slots && ((near_one && xfirst_shape(it, *fx, m, P, false, &sh)) || stream_shape(it, *fx, m, P, &sh))) {
             d.route = vp::kRouteStream;   // (band and column table below, once the shape is final)
             shapes[b] = sh;
             x_axes[b] = fx;
@@ -1249,7 +1251,9 @@ bool resize_stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, Str
 // Plan of vp_resize_batch: per item its frames in index order (no padding),
 // fixed-point tables, the route (streaming, or the tile kernel where an axis
 // does not fit the streaming shapes) and its output byte offset.
-int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
+// `few_units`: the matrix-core form only in place of the dot-product form, not
+// of the general kernel, which needs no work units.
+int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_units = false) {
     if (items == nullptr) return fail(VP_ERR_NULL, "items is NULL");
     if (n < 1) return fail(VP_ERR_ARG, "n_items < 1");
     int32_t P = vp::kPatch;
@@ -1363,7 +1367,9 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
         if ((it.dst_w + 15) / 16 <= vp::kWgBandMax && int64_t(it.src_h + 64) * it.src_w * 3 + 256 < (int64_t(1) << 32) &&
             (dx = digits_for(*fx, true)).first >= 0)
             dy = digits_for(*fy, false);
-        const bool mm = dx.first >= 0 && dy.first >= 0;
+        const bool mm = dx.first >= 0 && dy.first >= 0 &&
+                        !(few_units && ((dx.second & vp::kRsMmWide) != 0 || ay.entry->slots < 0 ||
+                                        ay.entry->slots > vp::kStreamSlots));
         const bool slots = !mm && slots_for(*fy, &d.sy_off, &m);
         if (mm) {
             d.route = vp::kRouteStream;
@@ -1424,7 +1430,12 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
     for (int32_t b = 0; b < n; ++b)
         if (p->items[b].route == vp::kRouteStream && shapes[b].kx == vp::kRsMmShape)
             mm_waves += int64_t(p->items[b].t) * shapes[b].bands * ((p->items[b].h + 15) / 16);
-    const int64_t mm_rows = mm_waves < 3000 ? 16 : mm_waves < 6000 ? 32 : mm_waves < 60000 ? 64 : 128;
+    int64_t mm_rows = mm_waves < 3000 ? 16 : mm_waves < 6000 ? 32 : mm_waves < 60000 ? 64 : 128;
+    int64_t mm_units = 0;
+    for (int32_t b = 0; b < n; ++b)
+        if (p->items[b].route == vp::kRouteStream && shapes[b].kx == vp::kRsMmShape)
+            mm_units += int64_t(p->items[b].t) * ((p->items[b].h + mm_rows - 1) / mm_rows);
+    if (mm_units > vp::kWgUnitMask / 2) mm_rows = INT32_MAX;   // whole frames: units are numbered below 2^20
     const auto unit_waves = [&](int64_t rows) {   // of the dot-product form
         int64_t waves = 0;
         for (int32_t b = 0; b < n; ++b) {
@@ -1482,7 +1493,8 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p) {
 // used first.
 // ---------------------------------------------------------------------------
 
-enum class PlanKind : int64_t { kBatch = 1, kPatch = 2, kResize = 3, kRows = 4 };
+// (kBatchSmall: kBatch in less memory, upscales of many slots on the general kernel)
+enum class PlanKind : int64_t { kBatch = 1, kPatch = 2, kResize = 3, kRows = 4, kBatchSmall = 5 };
 
 constexpr size_t kPlanCacheMax = 8;
 std::mutex g_plan_mu;
@@ -1490,9 +1502,18 @@ std::list<std::pair<std::vector<int64_t>, std::shared_ptr<const Plan>>> g_plans;
 
 int32_t build_kind(PlanKind kind, const vp_item* items, int32_t n, Plan* p) {
     switch (kind) {
-        case PlanKind::kBatch: return build_plan(items, n, p);
+        case PlanKind::kBatch: {
+            // (more work units than a launch can index: as many items as may
+            // be on the general kernel, which needs none)
+            const int32_t st = build_plan(items, n, p);
+            return st == VP_ERR_CAPACITY ? build_plan(items, n, p, vp::kStreamSlots) : st;
+        }
+        case PlanKind::kBatchSmall: return build_plan(items, n, p, vp::kStreamSlots);
         case PlanKind::kPatch: return build_patch_plan(items, n, p);
-        case PlanKind::kResize: return build_resize_plan(items, n, p);
+        case PlanKind::kResize: {
+            const int32_t st = build_resize_plan(items, n, p);
+            return st == VP_ERR_CAPACITY ? build_resize_plan(items, n, p, true) : st;
+        }
         case PlanKind::kRows: return build_rows_plan(items, n, p);
     }
     return fail(VP_ERR_ARG, "unknown plan kind");
@@ -1792,6 +1813,15 @@ int32_t run_batch(bool patch_only, const vp_item* items, int32_t n_items, const 
     std::shared_ptr<const Plan> plan;
     int32_t st = get_plan(patch_only ? PlanKind::kPatch : PlanKind::kBatch, items, n_items, &plan);
     if (st != VP_OK) return st;
+    // Upscales of 2x to 4x: the x-first kernel's units (28 bytes a frame) are
+    // most of such a plan, and the general kernel needs none, so a batch whose
+    // plan is too large for the fixed memory may still fit on that kernel.
+    if (no_alloc && plan->bytes > static_cast<size_t>(vp::kNoAllocPlanBytes)) {
+        std::shared_ptr<const Plan> small;
+        if (get_plan(PlanKind::kBatchSmall, items, n_items, &small) == VP_OK &&
+            small->bytes <= static_cast<size_t>(vp::kNoAllocPlanBytes))
+            plan = std::move(small);
+    }
     const Plan& p = *plan;
     if (out_rows_capacity < p.total_rows)
         return fail(VP_ERR_CAPACITY, "out_rows holds " + std::to_string(out_rows_capacity) +

@@ -9,6 +9,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2604_16893_amd as vp
@@ -253,6 +254,42 @@ def test_noalloc_errors_before_any_gpu_work():
     assert vp.vp_batch_layout(small)[3] <= vp.VP_NOALLOC_PLAN_BYTES < vp.vp_batch_layout(big)[3]
     assert _raw_noalloc(big) == vp.VP_ERR_CAPACITY
     assert b"fixed plan memory" in vp.lib().vp_last_error_message()
+
+
+@pytest.mark.skipif(torch.cuda.device_count() > 0, reason="with a device the call would run on placeholder pointers")
+@pytest.mark.parametrize("H,W,h,w,patch", [(47, 45, 96, 96, 16), (12, 12, 32, 32, 16), (20, 66, 56, 56, 14)])
+def test_noalloc_takes_long_upscaled_batches(H, W, h, w, patch):
+    """Upscales over 2x whose streaming plan exceeds the fixed plan memory are
+    planned for the general kernel, which needs no work units: the call gets
+    past every check of the host's (and stops where it wants the device)."""
+    n = 700000 if patch == 16 else 1400000   # one unit a frame, or a pair for patch 14
+    it = vp.Item((0x10000, 2, H, W), np.arange(n, dtype=np.int32) % 2, h, w, patch)
+    assert vp.vp_batch_layout([it])[3] > vp.VP_NOALLOC_PLAN_BYTES
+    assert _raw_noalloc([it]) == vp.VP_ERR_HIP
+    down = vp.Item((0x10000, 2, 720, 1280), np.arange(1400000, dtype=np.int32) % 2, 8 * patch, 14 * patch, patch)
+    assert _raw_noalloc([it, down]) == vp.VP_ERR_CAPACITY
+
+
+def test_upscaled_batches_of_more_frames_than_work_units():
+    """2^20 streaming work units are the most of one batch; upscales over 2x
+    beyond that go to the general kernel, which has none."""
+    it = vp.Item((0x10000, 2, 12, 12), np.arange(1 << 20, dtype=np.int32) % 2, 32, 32)
+    assert [int(r[0]) for r in vp.vp_batch_kernels([it])] == [vp.VP_KERNEL_XFIRST]
+    assert [int(r[0]) for r in vp.vp_batch_kernels([it, it])] == [vp.VP_KERNEL_GENERIC]
+    down = vp.Item((0x10000, 2, 64, 64), it.indices, 32, 32)
+    with pytest.raises(vp.VPError) as e:
+        vp.vp_batch_kernels([down, down])
+    assert e.value.status == vp.VP_ERR_CAPACITY
+
+
+@pytest.mark.parametrize("H,W,h,w,n", [(300, 60, 160, 32, 600000), (600, 60, 288, 32, 400000), (12, 12, 32, 32, 1100000),
+                                       (300, 2000, 64, 448, 1000000)])
+def test_writer_batches_of_many_frames(H, W, h, w, n):
+    """The writer cuts frames into units only while 2^20 of them suffice, and
+    leaves upscales of many frames to the general kernel."""
+    it = vp.Item((0x10000, 2, H, W), np.arange(n, dtype=np.int32) % 2, h, w)
+    off, ws = vp.vp_resize_layout([it])
+    assert int(off[-1]) == n * h * w * 3 and ws > 0
 
 
 def _raw_patchify(items, mean=(0.5, 0.5, 0.5), std=(0.5, 0.5, 0.5), dtype=vp.VP_OUT_BF16,
