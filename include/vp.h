@@ -281,7 +281,8 @@ int32_t vp_preprocess_batch(const vp_item* items, int32_t n_items, const float* 
  * Arguments, outputs, ownership and asynchrony otherwise as for
  * vp_preprocess_batch.
  * Errors: as vp_preprocess_batch, with VP_ERR_CAPACITY when the batch's plan
- * (the workspace_bytes of vp_batch_layout) exceeds VP_NOALLOC_PLAN_BYTES;
+ * (the workspace_bytes of vp_batch_layout, or that of a plan with upscales
+ * over 2x on the general kernel, if smaller) exceeds VP_NOALLOC_PLAN_BYTES;
  * this and every other argument check happens before any HIP call.
  */
 #define VP_NOALLOC_PLAN_BYTES (16 * 1024 * 1024)
