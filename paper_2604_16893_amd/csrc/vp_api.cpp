@@ -1251,8 +1251,9 @@ bool resize_stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, Str
 // Plan of vp_resize_batch: per item its frames in index order (no padding),
 // fixed-point tables, the route (streaming, or the tile kernel where an axis
 // does not fit the streaming shapes) and its output byte offset.
-// `few_units`: the matrix-core form only in place of the dot-product form, not
-// of the general kernel, which needs no work units.
+// `few_units`: no more work units than whole frames and the dot-product form's
+// long units need: the matrix-core form on whole frames, and only in place of
+// the dot-product form, not of the general kernel, which needs none.
 int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_units = false) {
     if (items == nullptr) return fail(VP_ERR_NULL, "items is NULL");
     if (n < 1) return fail(VP_ERR_ARG, "n_items < 1");
@@ -1435,7 +1436,8 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
     for (int32_t b = 0; b < n; ++b)
         if (p->items[b].route == vp::kRouteStream && shapes[b].kx == vp::kRsMmShape)
             mm_units += int64_t(p->items[b].t) * ((p->items[b].h + mm_rows - 1) / mm_rows);
-    if (mm_units > vp::kWgUnitMask / 2) mm_rows = INT32_MAX;   // whole frames: units are numbered below 2^20
+    // (whole frames: units are numbered below 2^20)
+    if (few_units || mm_units > vp::kWgUnitMask / 2) mm_rows = INT32_MAX;
     const auto unit_waves = [&](int64_t rows) {   // of the dot-product form
         int64_t waves = 0;
         for (int32_t b = 0; b < n; ++b) {
@@ -1446,7 +1448,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
         }
         return waves;
     };
-    const int64_t short_rows = short_unit_rows(unit_waves, unit_waves, kShortWavesDot);
+    const int64_t short_rows = few_units ? 0 : short_unit_rows(unit_waves, unit_waves, kShortWavesDot);
     std::vector<Keyed> keyed;
     for (int32_t b = 0; b < n; ++b) {
         const vp::DevItem& d = p->items[b];

@@ -292,6 +292,22 @@ def test_writer_batches_of_many_frames(H, W, h, w, n):
     assert int(off[-1]) == n * h * w * 3 and ws > 0
 
 
+@pytest.mark.parametrize("dot,matrix", [
+    # items on the dot-product form (a vertical downscale of over 5.6x), one
+    # unit a frame, beside narrow ones on the matrix-core form, whose 128-row
+    # units alone stay below the limit: whole frames fit
+    ((1100, 40, 1024, 32, 62500), (600, 60, 64, 32, 600000)),
+    ((1100, 40, 1024, 32, 60000), (600, 60, 64, 32, 700000)),
+    # few items on the dot-product form, which short units would cut in 1,200
+    ((64000, 64, 640, 64, 30), (32, 64, 32, 64, 1048000)),
+])
+def test_writer_batches_of_both_forms_near_the_unit_limit(dot, matrix):
+    items = [vp.Item((0x10000 + 4096 * k, 2, H, W), np.arange(n, dtype=np.int32) % 2, h, w)
+             for k, (H, W, h, w, n) in enumerate((dot, matrix))]
+    off, ws = vp.vp_resize_layout(items)
+    assert int(off[-1]) == sum(n * h * w * 3 for _, _, h, w, n in (dot, matrix)) and ws > 0
+
+
 def _raw_patchify(items, mean=(0.5, 0.5, 0.5), std=(0.5, 0.5, 0.5), dtype=vp.VP_OUT_BF16,
                   out=0x100000, cap=1 << 30, ws=0x200000, ws_bytes=1 << 30):
     b = vp._Batch(items)
