@@ -1619,6 +1619,72 @@ void pack_plan(const Plan& p, uint8_t* base) {
     put(p.off_jobs, p.jobs.data(), sizeof(vp::TableJob) * p.jobs.size(), p.off_gen);
 }
 
+// The plan's copy of vp_preprocess_batch_noalloc comes from pageable memory.
+// The runtime sends up to 16 KiB of that with the stream's commands: 4.4 us of
+// the host and 2.5 us of the GPU a piece, measured; a larger copy is staged and
+// costs 22 us of the host and 17 us of the GPU, up to 64 KB (131 KB 24 us).  So
+// plans of up to four pieces go in pieces: 64 frames of 480p in float32 90 ->
+// 78 us a call back to back, 8 frames 36 -> 32.
+constexpr size_t kCopyPiece = 16384;
+constexpr size_t kCopyPieces = 4;
+
+// Whether that entry fills the computed tables on the host and copies them with
+// the rest: a kernel that computes them between the copy and the batch costs a
+// call 5 us of the GPU, the host about 1 ns a word, which a batch with work
+// enough hides.  In a plan that goes in one copy the tables' share of it costs
+// less than their kernel (64 frames of 1080p 155 -> 150 us, 32 of 4K 295 ->
+// 291), in one that goes in pieces no less.  Many tables stay on the device (20
+// ragged images 78 us, 338 with the host's), and so do those of small batches:
+// at 256 source pixels a word a batch streams for four times the host's work.
+constexpr size_t kHostTableWords = 32768;
+constexpr int64_t kHostTablePixels = 256;
+
+bool tables_on_host(const Plan& p) {
+    if (p.off_gen <= kCopyPieces * kCopyPiece || p.gen_words > kHostTableWords) return false;
+    int64_t pixels = 0;
+    for (const vp::DevItem& d : p.items)
+        if (d.route == vp::kRouteStream) pixels += int64_t(2) * d.t * d.H * d.W;
+    return pixels >= kHostTablePixels * static_cast<int64_t>(p.gen_words);
+}
+
+// The plan's computed tables on the host, into `tables` (the first tables
+// section's place in the blob; the computed words zeroed): the same words that
+// the upload kernel computes from the same pieces.
+void fill_tables(const Plan& p, int32_t* tables) {
+    std::shared_ptr<const AxisEntry> axis;
+    for (const vp::TableJob& t : p.jobs) {
+        if (axis == nullptr || axis->f.n_in != t.n_in || axis->f.n_out != t.n_out)
+            axis = cached(g_axis_cache, std::make_pair(t.n_in, t.n_out), [&] { return make_axis_entry(t.n_in, t.n_out); });
+        const AxisFilter& f = axis->f;
+        const int32_t kind = t.kind_lanes & 255, lanes = t.kind_lanes >> 8;
+        int32_t* const out = tables + t.off;
+        float* const weights = reinterpret_cast<float*>(out);
+        const int64_t rows = f.n_in + vp::kSlotMax;
+        const int32_t end = std::min(f.n_out, t.base + vp::table_outputs(lanes));   // (starts, zeros: one lane)
+        if (kind == vp::kTableStarts) {
+            std::copy(f.start.begin() + t.base, f.start.begin() + end, out + t.base);
+        } else if (kind == vp::kTableZeros) {   // the two close rows that are never reached
+            const int64_t words = rows * t.a;
+            for (int64_t e = std::max<int64_t>(words, t.base); e < std::min<int64_t>(words + 2, t.base + vp::kTablePiece); ++e)
+                out[e + f.n_out] = INT32_MAX;
+        } else if (kind == vp::kTableSlots) {
+            for (int32_t i = t.base; i < end; ++i) {
+                const int32_t slot = i % t.a;
+                for (int32_t k = 0; k < f.count[i]; ++k)
+                    weights[int64_t(f.start[i] + k) * t.a + slot] = f.weight[size_t(i) * f.taps + k] * 16777216.0f;   // times 2^24
+                out[rows * t.a + i] = f.start[i] + f.count[i] - 1;
+            }
+        } else {
+            for (int32_t j = t.base; j < end; ++j) {
+                const int32_t l = f.start[j] - f.start[j / t.band * t.band];
+                const int32_t s = std::min(l, t.row_px - t.a);
+                std::copy_n(f.weight.begin() + int64_t(j) * f.taps, f.count[j], weights + f.n_out + int64_t(j) * t.a + l - s);
+                out[j] = s;
+            }
+        }
+    }
+}
+
 int32_t upload_plan(const Plan& p, void* workspace, hipStream_t stream) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1835,17 +1901,29 @@ int32_t run_batch(bool patch_only, const vp_item* items, int32_t n_items, const 
                                              std::to_string(vp::kNoAllocPlanBytes));
         const int err = vp::noalloc_plan_memory(&workspace);
         if (err != 0) return hip_fail(static_cast<hipError_t>(err), "hipGetSymbolAddress (plan memory)");
-        // pageable host memory: the copy has read it when hipMemcpyAsync returns
+        // (pageable host memory: a copy has read it when hipMemcpyAsync returns)
+        const bool host_tables = tables_on_host(p);
+        const size_t copied = host_tables ? p.bytes : p.off_gen;
         thread_local std::vector<uint8_t> blob;
-        if (blob.size() < p.off_gen) blob.resize(p.off_gen);
+        if (blob.size() < copied) blob.resize(copied);
         pack_plan(p, blob.data());
-        const hipError_t e = hipMemcpyAsync(workspace, blob.data(), p.off_gen, hipMemcpyHostToDevice, stream);
-        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (plan)");
+        if (host_tables) {
+            std::memset(blob.data() + p.off_gen, 0, p.bytes - p.off_gen);
+            fill_tables(p, reinterpret_cast<int32_t*>(blob.data() + p.off_tables));
+        }
         auto* const base = static_cast<uint8_t*>(workspace);
-        const int te = vp::launch_upload(nullptr, nullptr, 0, reinterpret_cast<const vp::TableJob*>(base + p.off_jobs),
-                                         static_cast<int>(p.jobs.size()), reinterpret_cast<int32_t*>(base + p.off_tables),
-                                         stream);
-        if (te != 0) return hip_fail(static_cast<hipError_t>(te), "plan tables launch");
+        const size_t piece = copied <= kCopyPieces * kCopyPiece ? kCopyPiece : copied;
+        for (size_t at = 0; at < copied; at += piece) {
+            const hipError_t e = hipMemcpyAsync(base + at, blob.data() + at, std::min(piece, copied - at),
+                                                hipMemcpyHostToDevice, stream);
+            if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (plan)");
+        }
+        if (!host_tables) {
+            const int te = vp::launch_upload(nullptr, nullptr, 0, reinterpret_cast<const vp::TableJob*>(base + p.off_jobs),
+                                             static_cast<int>(p.jobs.size()),
+                                             reinterpret_cast<int32_t*>(base + p.off_tables), stream);
+            if (te != 0) return hip_fail(static_cast<hipError_t>(te), "plan tables launch");
+        }
     } else {
         if (workspace_bytes < static_cast<int64_t>(p.bytes))
             return fail(VP_ERR_CAPACITY, "workspace holds " + std::to_string(workspace_bytes) +

@@ -88,3 +88,37 @@ def test_noalloc_on_a_side_stream_in_order():
         ref, _, _ = vp.preprocess(items, mean, std, "bf16")
         torch.cuda.synchronize()
         assert torch.equal(got.view(torch.int16), ref.view(torch.int16))
+
+
+# The ways this entry's plan reaches the device: in one to four pieces of
+# 16 KiB with the tables computed there, and (many small frames: few tables
+# beside many units, `host`) in one copy with the tables filled on the host --
+# both patches and kernels, twelve slots, windows of 138 rows, long column
+# windows.  The workspace entry computes all tables on the device.
+PLANS = [
+    # n, H, W, h, w, patch, host
+    (2, 130, 170, 96, 128, 16, False),
+    (8, 480, 854, 352, 640, 16, False),
+    (48, 480, 854, 320, 576, 16, False),
+    (2600, 60, 90, 32, 64, 16, True),
+    (4096, 47, 45, 96, 96, 16, True),
+    (2600, 1100, 40, 32, 32, 16, True),
+    (2600, 40, 200, 32, 32, 16, True),
+    (6000, 56, 70, 56, 56, 14, True),
+    (9000, 90, 70, 28, 56, 14, True),
+]
+
+
+@pytest.mark.parametrize("n,H,W,h,w,patch,host", PLANS)
+def test_noalloc_plan_copies(n, H, W, h, w, patch, host):
+    it = workloads.Item("video", min(n, 64), H, W, "uniform", 700, {"mode": "uniform", "n": 1})
+    items = [vp.Item(workloads.frames_torch(it, DEV), np.arange(n, dtype=np.int32) % min(n, 64), h, w, patch)]
+    ws = vp.vp_batch_layout(items)[3]
+    log(f"plan of {ws} bytes: {n} x {H}x{W} -> {h}x{w} patch {patch}")
+    assert (ws > 4 * 16384 + 4 * 8192) if host else ws < 4 * 16384 + 4 * 8192
+    mean, std = (0.481, 0.458, 0.408), (0.269, 0.261, 0.276)
+    ref, _, _ = vp.preprocess(items, mean, std, "f32")
+    got = torch.full_like(ref, float("nan"))
+    vp.vp_preprocess_batch_noalloc(items, mean, std, vp.VP_OUT_F32, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int32), ref.view(torch.int32))
