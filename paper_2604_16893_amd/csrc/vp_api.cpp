@@ -1502,20 +1502,24 @@ constexpr size_t kPlanCacheMax = 8;
 std::mutex g_plan_mu;
 std::list<std::pair<std::vector<int64_t>, std::shared_ptr<const Plan>>> g_plans;
 
+// A first plan that needs more work units than a launch can index gives way to
+// one with as many items as may be on kernels that need none, or fewer; the
+// caller sees the error of a plan only where the call fails with it.
 int32_t build_kind(PlanKind kind, const vp_item* items, int32_t n, Plan* p) {
+    const std::string before = g_last_error;
+    const auto or_else = [&](int32_t st, auto second) {
+        if (st != VP_ERR_CAPACITY) return st;
+        st = second();
+        if (st == VP_OK) g_last_error = before;
+        return st;
+    };
     switch (kind) {
-        case PlanKind::kBatch: {
-            // (more work units than a launch can index: as many items as may
-            // be on the general kernel, which needs none)
-            const int32_t st = build_plan(items, n, p);
-            return st == VP_ERR_CAPACITY ? build_plan(items, n, p, vp::kStreamSlots) : st;
-        }
+        case PlanKind::kBatch:
+            return or_else(build_plan(items, n, p), [&] { return build_plan(items, n, p, vp::kStreamSlots); });
         case PlanKind::kBatchSmall: return build_plan(items, n, p, vp::kStreamSlots);
         case PlanKind::kPatch: return build_patch_plan(items, n, p);
-        case PlanKind::kResize: {
-            const int32_t st = build_resize_plan(items, n, p);
-            return st == VP_ERR_CAPACITY ? build_resize_plan(items, n, p, true) : st;
-        }
+        case PlanKind::kResize:
+            return or_else(build_resize_plan(items, n, p), [&] { return build_resize_plan(items, n, p, true); });
         case PlanKind::kRows: return build_rows_plan(items, n, p);
     }
     return fail(VP_ERR_ARG, "unknown plan kind");

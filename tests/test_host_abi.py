@@ -308,6 +308,19 @@ def test_writer_batches_of_both_forms_near_the_unit_limit(dot, matrix):
     assert int(off[-1]) == sum(n * h * w * 3 for _, _, h, w, n in (dot, matrix)) and ws > 0
 
 
+def test_a_plan_given_up_leaves_no_error_behind():
+    """vp_last_error_message is the detail of the last call that failed: a
+    call whose first plan has too many work units and whose second one fits
+    succeeds, and leaves the message as it was."""
+    with pytest.raises(vp.VPError):
+        vp.vp_filter_table(0, 32)
+    before = vp.lib().vp_last_error_message()
+    assert before
+    up = vp.Item((0x10000, 2, 12, 12), np.arange(1100000, dtype=np.int32) % 2, 32, 32)
+    assert [int(r[0]) for r in vp.vp_batch_kernels([up, up])] == [vp.VP_KERNEL_GENERIC]
+    assert vp.lib().vp_last_error_message() == before
+
+
 def _raw_patchify(items, mean=(0.5, 0.5, 0.5), std=(0.5, 0.5, 0.5), dtype=vp.VP_OUT_BF16,
                   out=0x100000, cap=1 << 30, ws=0x200000, ws_bytes=1 << 30):
     b = vp._Batch(items)
