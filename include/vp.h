@@ -328,6 +328,28 @@ int32_t vp_resize_layout(const vp_item* items, int32_t n_items, int64_t* frame_o
                          int64_t* workspace_bytes);
 
 /*
+ * Diagnostic: the kernel launches that vp_resize_batch makes for a batch,
+ * without running them, as vp_batch_kernels does for vp_preprocess_batch.
+ * launches: HOST int32[capacity][6], or NULL with capacity 0.  Row i:
+ *   kind: VP_WRITER_TILES, VP_WRITER_DOT or VP_WRITER_MATRIX;
+ *   dot: M, the accumulator slots; else 0;
+ *   dot: the column taps of its windows (rounded up); else 0;
+ *   matrix: source pixels per row of a workgroup's loads (32, 64 or 128);
+ *   else 0;
+ *   matrix: output columns per workgroup (32 or 16); else 0;
+ *   workgroups (tiles: output tiles).
+ *   Rows past `capacity` are not written.
+ * n_launches: HOST, receives the number of launches.
+ * Errors: as vp_resize_layout; VP_ERR_NULL (n_launches), VP_ERR_ARG
+ * (capacity < 0, or launches NULL with capacity > 0).
+ */
+#define VP_WRITER_TILES 0
+#define VP_WRITER_DOT 1
+#define VP_WRITER_MATRIX 2
+int32_t vp_resize_kernels(const vp_item* items, int32_t n_items, int32_t* launches,
+                          int32_t capacity, int32_t* n_launches);
+
+/*
  * uint8 cache writer (Section 3.1.1: the offline cache holds frames that are
  * already sampled and resized; as uint8 they take a quarter of the float
  * tensors' space).  For every item, every sampled frame, in index order and

@@ -42,7 +42,7 @@ VP_FACTOR = 32
 EXPORTED = ("vp_smart_resize_dims", "vp_sample_indices", "vp_filter_taps", "vp_filter_table",
             "vp_filter_table_fixed", "vp_batch_layout", "vp_patchify_layout", "vp_batch_kernels", "vp_preprocess_batch",
             "vp_preprocess_batch_noalloc", "vp_patchify_batch",
-            "vp_resize_layout", "vp_resize_batch", "vp_position_ids", "vp_status_string",
+            "vp_resize_layout", "vp_resize_kernels", "vp_resize_batch", "vp_position_ids", "vp_status_string",
             "vp_last_error_message", "vp_set_kernel_events")
 
 
@@ -85,6 +85,7 @@ def lib() -> ctypes.CDLL:
         L.vp_batch_layout.argtypes = [itemp, i32, i32p, i32p, i64p, i64p]
         L.vp_patchify_layout.argtypes = [itemp, i32, i64p, i64p]
         L.vp_batch_kernels.argtypes = [itemp, i32, i32p, i32, i32p]
+        L.vp_resize_kernels.argtypes = [itemp, i32, i32p, i32, i32p]
         L.vp_preprocess_batch.argtypes = [itemp, i32, f32p, f32p, i32, ctypes.c_void_p, i64,
                                           i32p, i32p, ctypes.c_void_p, i64, ctypes.c_void_p]
         L.vp_patchify_batch.argtypes = L.vp_preprocess_batch.argtypes
@@ -268,12 +269,26 @@ def vp_batch_kernels(items: Sequence):
     """The launches vp_preprocess_batch makes for the batch, as int32 rows
     (kind, slots M, column taps, y-first pixels per lane, x-first columns per
     lane, workgroups); no kernel runs."""
+    return _launches(items, "vp_batch_kernels")
+
+
+VP_WRITER_TILES, VP_WRITER_DOT, VP_WRITER_MATRIX = 0, 1, 2
+
+
+def vp_resize_kernels(items: Sequence):
+    """The launches vp_resize_batch makes for the batch, as int32 rows (kind,
+    dot slots M, dot column taps, matrix pixels per loaded row, matrix columns
+    per workgroup, workgroups); no kernel runs."""
+    return _launches(items, "vp_resize_kernels")
+
+
+def _launches(items: Sequence, name: str):
     b = _Batch(items)
     n = ctypes.c_int32()
-    _check(lib().vp_batch_kernels(b.arr, len(b), None, 0, ctypes.byref(n)), "vp_batch_kernels")
+    fn = getattr(lib(), name)
+    _check(fn(b.arr, len(b), None, 0, ctypes.byref(n)), name)
     rows = np.zeros((max(n.value, 1), 6), np.int32)
-    _check(lib().vp_batch_kernels(b.arr, len(b), _ptr(rows, ctypes.c_int32), n.value, ctypes.byref(n)),
-           "vp_batch_kernels")
+    _check(fn(b.arr, len(b), _ptr(rows, ctypes.c_int32), n.value, ctypes.byref(n)), name)
     return rows[:n.value]
 
 

@@ -1968,6 +1968,36 @@ int32_t run_batch(bool patch_only, const vp_item* items, int32_t n_items, const 
     return VP_OK;
 }
 
+// vp_batch_kernels and vp_resize_kernels: a row of six words per launch.
+int32_t describe_launches(PlanKind kind, const vp_item* items, int32_t n_items, int32_t* launches,
+                          int32_t capacity, int32_t* n_launches) {
+    if (n_launches == nullptr) return fail(VP_ERR_NULL, "n_launches is NULL");
+    if (capacity < 0 || (launches == nullptr && capacity > 0))
+        return fail(VP_ERR_ARG, "launches must hold capacity rows of 6 int32");
+    std::shared_ptr<const Plan> plan;
+    const int32_t st = get_plan(kind, items, n_items, &plan);
+    if (st != VP_OK) return st;
+    const Plan& p = *plan;
+    std::vector<std::array<int32_t, 6>> rows;
+    static_assert(VP_KERNEL_GENERIC == VP_WRITER_TILES);
+    if (p.prefix[n_items] > 0) rows.push_back({VP_KERNEL_GENERIC, 0, 0, 0, 0, p.prefix[n_items]});
+    for (const vp::StreamLaunch& L : p.launches) {
+        if (kind == PlanKind::kResize && L.kx == vp::kRsMmShape)
+            rows.push_back({VP_WRITER_MATRIX, 0, 0, 16 * (L.m % vp::kRsMmTwo),
+                            vp::resize_mm_cols((L.m & vp::kRsMmWide) != 0), L.count});
+        else if (kind == PlanKind::kResize)
+            rows.push_back({VP_WRITER_DOT, L.m, L.kx, 0, 0, L.count});
+        else if (L.px < 0)
+            rows.push_back({VP_KERNEL_XFIRST, L.m, L.kx, 0, vp::xfirst_db(L.px) > 0 ? 2 : 1, L.count});
+        else
+            rows.push_back({VP_KERNEL_YFIRST, L.m, L.kx, L.px, 0, L.count});
+    }
+    for (size_t i = 0; i < rows.size() && i < size_t(capacity); ++i)
+        std::memcpy(launches + 6 * i, rows[i].data(), sizeof(int32_t) * 6);
+    *n_launches = static_cast<int32_t>(rows.size());
+    return VP_OK;
+}
+
 }  // namespace
 
 // ===========================================================================
@@ -2104,25 +2134,12 @@ int32_t vp_patchify_layout(const vp_item* items, int32_t n_items, int64_t* total
 
 int32_t vp_batch_kernels(const vp_item* items, int32_t n_items, int32_t* launches,
                          int32_t capacity, int32_t* n_launches) {
-    if (n_launches == nullptr) return fail(VP_ERR_NULL, "n_launches is NULL");
-    if (capacity < 0 || (launches == nullptr && capacity > 0))
-        return fail(VP_ERR_ARG, "launches must hold capacity rows of 6 int32");
-    std::shared_ptr<const Plan> plan;
-    const int32_t st = get_plan(PlanKind::kBatch, items, n_items, &plan);
-    if (st != VP_OK) return st;
-    const Plan& p = *plan;
-    std::vector<std::array<int32_t, 6>> rows;
-    if (p.prefix[n_items] > 0) rows.push_back({VP_KERNEL_GENERIC, 0, 0, 0, 0, p.prefix[n_items]});
-    for (const vp::StreamLaunch& L : p.launches) {
-        if (L.px < 0)
-            rows.push_back({VP_KERNEL_XFIRST, L.m, L.kx, 0, vp::xfirst_db(L.px) > 0 ? 2 : 1, L.count});
-        else
-            rows.push_back({VP_KERNEL_YFIRST, L.m, L.kx, L.px, 0, L.count});
-    }
-    for (size_t i = 0; i < rows.size() && i < size_t(capacity); ++i)
-        std::memcpy(launches + 6 * i, rows[i].data(), sizeof(int32_t) * 6);
-    *n_launches = static_cast<int32_t>(rows.size());
-    return VP_OK;
+    return describe_launches(PlanKind::kBatch, items, n_items, launches, capacity, n_launches);
+}
+
+int32_t vp_resize_kernels(const vp_item* items, int32_t n_items, int32_t* launches,
+                          int32_t capacity, int32_t* n_launches) {
+    return describe_launches(PlanKind::kResize, items, n_items, launches, capacity, n_launches);
 }
 
 int32_t vp_preprocess_batch(const vp_item* items, int32_t n_items, const float* mean,

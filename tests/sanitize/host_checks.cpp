@@ -4,7 +4,7 @@
 // Drives every host path of the library's C ABI -- smart_resize, index
 // sampling, the float and fixed-point filter tables, the batch planner of
 // every entry point (through vp_batch_layout, vp_batch_kernels,
-// vp_resize_layout and the host part of vp_position_ids), the plan cache,
+// vp_resize_layout, vp_resize_kernels and the host part of vp_position_ids), the plan cache,
 // column pairs of the x-first kernel in a large batch, and the checks that
 // return before any HIP call -- and every function of the oracle, over
 // seeded random shapes, degenerate sizes and the workloads' own batches.
@@ -136,6 +136,9 @@ void library_host_paths() {
             count(vp_batch_kernels(b.items.data(), n, launches.data(), 2, &nl));   // maybe fewer rows than launches
             launches.assign(size_t(6) * (nl > 0 ? nl : 1), 0);
             count(vp_batch_kernels(b.items.data(), n, launches.data(), nl, &nl));
+            count(vp_resize_kernels(b.items.data(), n, nullptr, 0, &nl));
+            launches.assign(size_t(6) * (nl > 0 ? nl : 1), 0);
+            count(vp_resize_kernels(b.items.data(), n, launches.data(), nl, &nl));
         }
         std::vector<int64_t> off(n + 1);
         count(vp_resize_layout(b.items.data(), n, off.data(), &ws));

@@ -61,7 +61,7 @@ CASES = [
     ("downscale_2x", [(3, 64, 96, [2, 0], 32, 48 + 16)]),
     ("upscale_1_6x", [(2, 40, 50, [1, 0, 1], 64, 96)]),
     ("upscale_2x_eight_slots", [(2, 48, 80, [1, 0], 96, 160)]),
-    ("upscale_2_5x_tiles", [(1, 64, 64, [0], 160, 160)]),
+    ("upscale_2_5x", [(1, 64, 64, [0], 160, 160)]),
     ("identity", [(2, 64, 96, [1], 64, 96)]),
     ("mixed_axes", [(2, 100, 60, [0, 1], 64, 96)]),
     ("odd_width_854", [(2, 60, 854, [1, 0], 32, 640)]),
@@ -69,10 +69,10 @@ CASES = [
     ("wide_strong_downscale", [(1, 300, 3000, [0], 32, 96)]),
     ("long_window_4k_width", [(2, 540, 3840, [1, 0], 96, 672)]),
     # x downscale of 3.9x: 16-column blocks read more than 64 pixels, so the
-    # byte dot-product kernel takes it instead of the matrix-core one
-    ("dot4_kernel_3_9x", [(2, 100, 1000, [0, 1], 64, 256)]),
-    # matrix-core horizontal pass (windows of 10+ taps) with a vertical
-    # upscale that keeps seven rows open
+    # matrix-core form takes windows of 128 and bands of 16 columns
+    ("wide_blocks_3_9x", [(2, 100, 1000, [0, 1], 64, 256)]),
+    # matrix-core form, windows of 10 and more taps, with a vertical upscale
+    # that keeps seven rows open
     ("mfma_seven_slots", [(2, 40, 240, [1, 0], 64, 96)]),
     # matrix-core form on rows and frames that start off 4-byte boundaries
     # (3 W = 783 bytes per row, 58,725 bytes per frame)
@@ -81,6 +81,44 @@ CASES = [
     ("ragged_batch", [(4, 75, 101, [3, 1, 2], 64, 96), (1, 333, 257, [0], 320, 256),
                       (5, 120, 200, [4, 0], 96, 160)]),
 ]
+
+# One form of the writer each, with its shape (slots and column taps of the
+# dot-product form, pixels of a loaded row and columns a workgroup of the
+# matrix-core form).  Dot products: uniform downscales over 5.9x (column taps
+# 28 and 32, bands of 32 columns, a last one of 28), vertical ones over 5.6x
+# beside milder horizontal ones (bands of 64, a last one of 32 columns; four and
+# five slots), a target wider than the matrix-core form's 4,094 blocks (eight
+# slots); tiles: longer windows than either holds
+FORMS = [
+    # H, W, h, w, patch, kind and shape
+    (400, 1588, 64, 256, 16, [vp.VP_WRITER_DOT, 4, 28, 0, 0]),
+    (680, 2176, 96, 320, 16, [vp.VP_WRITER_DOT, 4, 32, 0, 0]),
+    (420, 1745, 56, 252, 14, [vp.VP_WRITER_DOT, 4, 32, 0, 0]),
+    (700, 700, 96, 224, 16, [vp.VP_WRITER_DOT, 4, 16, 0, 0]),
+    (900, 320, 128, 160, 16, [vp.VP_WRITER_DOT, 4, 12, 0, 0]),
+    (608, 200, 96, 96, 16, [vp.VP_WRITER_DOT, 5, 12, 0, 0]),
+    (4000, 100, 32, 96, 16, [vp.VP_WRITER_DOT, 4, 8, 0, 0]),
+    (16, 33000, 32, 66016, 16, [vp.VP_WRITER_DOT, 8, 8, 0, 0]),
+    (333, 4001, 64, 160, 16, [vp.VP_WRITER_TILES, 0, 0, 0, 0]),
+    (60, 1600, 96, 192, 16, [vp.VP_WRITER_TILES, 0, 0, 0, 0]),
+    (300, 3000, 28, 84, 14, [vp.VP_WRITER_TILES, 0, 0, 0, 0]),
+    (100, 1000, 64, 256, 16, [vp.VP_WRITER_MATRIX, 0, 0, 128, 16]),
+    (200, 301, 64, 128, 16, [vp.VP_WRITER_MATRIX, 0, 0, 128, 32]),
+]
+
+
+@pytest.mark.parametrize("H,W,h,w,patch,form", FORMS)
+def test_each_form_exact(H, W, h, w, patch, form):
+    it, fd = _video(431, 3, H, W)
+    idx = [2, 0, 1]
+    launches = vp.vp_resize_kernels([vp.Item(fd, np.array(idx, np.int32), h, w, patch)]).tolist()
+    log(f"form {H}x{W} -> {h}x{w} patch {patch}: {launches}")
+    assert [r[:5] for r in launches] == [form]
+    out, off = run([(fd, np.array(idx, np.int32), h, w)], patch=patch)
+    got = frames_of(out, off, 0, 3, h, w).cpu().numpy()
+    ref = oracle.resize_u8_item(workloads.frames_np(it), idx, h, w, patch=patch)
+    bad = np.argwhere(got != ref)
+    assert bad.size == 0, f"{len(bad)} bytes differ, first at {bad[0]}"
 
 
 @pytest.mark.parametrize("name,specs", CASES, ids=[c[0] for c in CASES])

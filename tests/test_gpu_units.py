@@ -48,14 +48,24 @@ def test_short_units_match_long_ones(n_src, H, W, idx, h, w, patch):
     assert res["ok"], res
 
 
-@pytest.mark.parametrize("n_src,H,W,idx,h,w", [(2, 421, 611, [1, 0], 160, 256), (2, 700, 1291, [0, 1], 256, 448)])
-def test_writer_short_units_match_long_ones(n_src, H, W, idx, h, w):
-    """The uint8 writer, on both of its forms: bytes equal the oracle's for
-    one item alone and for the first and last of many."""
+@pytest.mark.parametrize("n_src,H,W,idx,h,w,form", [
+    (2, 421, 611, [1, 0], 160, 256, vp.VP_WRITER_MATRIX),
+    (2, 700, 1291, [0, 1], 256, 448, vp.VP_WRITER_MATRIX),
+    (2, 900, 320, [1, 0], 128, 160, vp.VP_WRITER_DOT),
+    (2, 640, 1984, [0, 1], 96, 320, vp.VP_WRITER_DOT),
+])
+def test_writer_short_units_match_long_ones(n_src, H, W, idx, h, w, form):
+    """The uint8 writer's forms in units: bytes equal the oracle's for one item
+    alone, in short units, and for the first and last of many, in long ones."""
     it = workloads.Item("video", n_src, H, W, "uniform", 43, {"mode": "uniform", "n": n_src})
     one = vp.Item(workloads.frames_torch(it, DEV), np.asarray(idx, np.int32), h, w)
+    copies = 512
+    few, lots = vp.vp_resize_kernels([one]), vp.vp_resize_kernels([one] * copies)
+    assert [int(r[0]) for r in few] == [int(r[0]) for r in lots] == [form]
+    assert 2 * int(lots[0][5]) <= copies * int(few[0][5]), "the batch never took longer units"
+    print(f"[units] writer {H}x{W} -> {h}x{w}: {few.tolist()} {lots.tolist()}", flush=True)
     alone = vp.resize_u8([one])[0]
-    many = vp.resize_u8([one] * 512)
+    many = vp.resize_u8([one] * copies)
     torch.cuda.synchronize()
     src = workloads.frames_np(it)
     ref = np.stack([oracle.resize_u8(src[i], h, w) for i in idx])

@@ -481,6 +481,25 @@ def test_batch_kernels_routes():
     assert vp.lib().vp_batch_kernels(None, 1, None, 0, ctypes.byref(n)) == vp.VP_ERR_NULL   # items
 
 
+def test_resize_kernels_describes_the_writers_launches():
+    """The writer's launch description: its forms side by side, workgroups,
+    truncation to the caller's capacity, and the errors of vp_batch_kernels."""
+    items = [vp.Item((0x10000, 2, 100, 70), [1, 0, 1], 64, 32),        # matrix cores: 3 frames x 1 band x 4 units
+             vp.Item((0x20000, 2, 400, 1588), [0, 1], 64, 256),        # dot products: 2 x 8 bands x 16 units
+             vp.Item((0x30000, 1, 300, 3000), [0], 32, 96)]            # tiles
+    rows = vp.vp_resize_kernels(items)
+    assert sorted(int(r[0]) for r in rows) == [vp.VP_WRITER_TILES, vp.VP_WRITER_DOT, vp.VP_WRITER_MATRIX]
+    dot = [r.tolist() for r in rows if r[0] == vp.VP_WRITER_DOT][0]
+    assert dot == [vp.VP_WRITER_DOT, 4, 28, 0, 0, 2 * 8 * 16]
+    b, n, L = vp._Batch(items), ctypes.c_int32(), vp.lib()
+    cut = np.full((3, 6), -7, np.int32)
+    assert L.vp_resize_kernels(b.arr, 3, vp._ptr(cut, ctypes.c_int32), 1, ctypes.byref(n)) == vp.VP_OK
+    assert n.value == 3 and cut[0].tolist() == rows[0].tolist() and (cut[1:] == -7).all()
+    assert L.vp_resize_kernels(b.arr, 3, None, 0, None) == vp.VP_ERR_NULL
+    assert L.vp_resize_kernels(b.arr, 3, None, 1, ctypes.byref(n)) == vp.VP_ERR_ARG
+    assert L.vp_resize_kernels(b.arr, 0, None, 0, ctypes.byref(n)) == vp.VP_ERR_ARG
+
+
 def test_tall_targets_take_the_streaming_kernels():
     """Targets of 2^15 rows and more are planned like any other: the layout
     counts their rows, and they take the streaming kernels (their GPU parity
