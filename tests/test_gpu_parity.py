@@ -144,12 +144,12 @@ SMALL = [
     ("partial_band", [(2, 300, 450, [1, 0], 128, 160)], "bf16"),
     ("unaligned_frames", [(4, 75, 101, [1, 2, 3], 64, 96)], "f32"),
     ("narrow_frame", [(2, 100, 40, [0, 1], 64, 32)], "f32"),
-    # vertical upscales on the streaming kernel (several output rows close
-    # on one source row; 2x keeps eight rows open); a stronger one on the
-    # general kernel, with an odd count whose padded pair is one frame twice
+    # vertical upscales on the streaming kernels (several output rows close on
+    # one source row; 2x keeps eight rows open, 2.7x eleven), the last with an
+    # odd count whose padded pair is one frame twice
     ("upscale_stream", [(2, 60, 70, [1, 0], 64, 96)], "f32"),
     ("upscale_2x_eight_slots", [(2, 48, 80, [1, 0], 96, 160), (1, 120, 160, [0], 224, 288)], "bf16"),
-    ("upscale_general_odd", [(3, 24, 40, [2, 0, 1], 64, 96)], "bf16"),
+    ("upscale_2_7x_odd", [(3, 24, 40, [2, 0, 1], 64, 96)], "bf16"),
     # long x windows (downscales of 4x to 7x): 28 taps with two pixels per
     # lane in 16-column bands, 20 taps with three in 32-column bands, and a
     # 4K-wide frame (24 taps)
@@ -201,6 +201,38 @@ def test_small_cases_full(name, specs, dtype):
     for k, (f, idx, h, w) in enumerate(items):
         ref = oracle.preprocess_item(host[k], idx, h, w, mean, std)
         assert_close(host_rows(out, cu[k], cu[k + 1], dtype), ref, dtype, f"{name} item {k}")
+
+
+# The general kernel: upscales over 4x in either direction, a short source with
+# a long x window, windows cut into sub-tiles of both kinds (fewer rows, fewer
+# columns), a one-pixel source; three frames, so that the last pair is one
+# frame twice
+GENERAL = [
+    # H, W, h, w, patch
+    (20, 40, 96, 96, 16),
+    (30, 400, 64, 96, 16),
+    (333, 4001, 64, 160, 16),
+    (7, 9, 32, 64, 16),
+    (20, 30, 112, 112, 14),
+    (300, 3000, 28, 84, 14),
+    (30, 400, 56, 84, 14),
+    (1, 1, 28, 56, 14),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,W,h,w,patch", GENERAL)
+def test_general_kernel(H, W, h, w, patch, dtype):
+    mean, std = (0.481, 0.458, 0.408), (0.269, 0.261, 0.276)
+    it = _rand_video(171, 3, H, W)
+    f, idx = workloads.frames_torch(it, DEV), np.array([2, 0, 1], np.int32)
+    launches = vp.vp_batch_kernels([vp.Item(f, idx, h, w, patch)])
+    assert [int(r[0]) for r in launches] == [vp.VP_KERNEL_GENERIC], launches.tolist()
+    log(f"general {H}x{W} -> {h}x{w} patch {patch} {dtype}")
+    out, grid, cu = run_gpu([(f, idx, h, w)], mean, std, dtype, patch=patch)
+    assert all_written(out)
+    ref = oracle.preprocess_item(workloads.frames_np(it), idx, h, w, mean, std, patch=patch)
+    assert_close(host_rows(out, cu[0], cu[1], dtype), ref, dtype, f"general {H}x{W} -> {h}x{w} patch {patch}")
 
 
 def _pairs_batch(items):

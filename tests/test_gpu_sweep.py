@@ -2,8 +2,8 @@
 
 Each case is a small ragged batch of one to three items drawn from one of
 eight shape families: downscales up to 6x, near-identity scales, mild
-upscales, 2x upscales (eight open output rows), 3x-4x upscales (the general
-kernel), extreme aspect ratios up to 200:1 in either direction, and images.
+upscales, 2x upscales (eight open output rows), 3x-4x upscales (nine to sixteen
+of them), extreme aspect ratios up to 200:1 in either direction, and images.
 Sizes are odd as often as not, index lists are unsorted with repeats and
 odd counts, and the cases alternate fp32 / bf16 output and patch 16 / 14.
 Every output element is compared with the oracle; the NaN sentinel rows
