@@ -454,7 +454,7 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
         const int32_t waves = patch == 14 ? round_up(bands, 2) : bands;
         if (bands > vp::kWgBandMax) continue;   // the band index field of a workgroup entry
         const int32_t span = band_span(fx, band);
-        for (int32_t px = 2; px <= 4; ++px) {
+        for (int32_t px = 2; px <= 3; ++px) {
             if (!vp::stream_shape_supported(mm, kx, px)) continue;
             if (span > 64 * px || kx > 64 * px) continue;
             // (patch 14 with px = 3 in float32: two bands of 63 columns leave
@@ -551,8 +551,8 @@ struct SlotEntry {
     int32_t m = -1;               // slots, or -1 if the axis needs too many
     std::vector<int32_t> words;
 };
-using ColumnKey = std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t, bool>;   // n_in, n_out, kx, band, row_px, fixed
-using SlotKey = std::pair<int32_t, int32_t>;                                        // n_in, n_out
+using ColumnKey = std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t>;   // n_in, n_out, kx, band, row_px
+using SlotKey = std::pair<int32_t, int32_t>;                                  // n_in, n_out
 
 constexpr size_t kTableCacheMax = 4096;
 std::mutex g_cache_mu;
@@ -1306,7 +1306,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
     std::map<ColumnKey, int32_t> column_tables;
     // the dot-product column table, or -1 if a weight does not fit its digits
     auto columns_for = [&](const AxisFilter& f, int32_t kx, int32_t band, int32_t row_px) -> int32_t {
-        const ColumnKey key = std::make_tuple(f.n_in, f.n_out, kx, band, row_px, true);
+        const ColumnKey key = std::make_tuple(f.n_in, f.n_out, kx, band, row_px);
         auto found = column_tables.find(key);
         if (found == column_tables.end()) {
             auto e = cached(g_column_cache, key, [&] {
@@ -1325,7 +1325,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
         auto found = digit_tables.find(at);
         if (found == digit_tables.end()) {
             // (the extent rides behind the words)
-            auto e = cached(g_column_cache, std::make_tuple(f.n_in, f.n_out, vp::kRsMmShape, columns ? 1 : 0, 0, true), [&] {
+            auto e = cached(g_column_cache, std::make_tuple(f.n_in, f.n_out, vp::kRsMmShape, columns ? 1 : 0, 0), [&] {
                 auto v = std::make_shared<std::vector<int32_t>>();
                 int32_t extent = 0;
                 if (build_digits(f, columns, v.get(), &extent)) v->push_back(extent);
@@ -1402,8 +1402,10 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
             tiles += int64_t(it.n_idx) * d.hm * d.wm;
             p->generic_cost += int64_t(8) * it.n_idx * it.src_h * it.src_w;   // about 8x the streaming cost per pixel
         }
-        d.ty_off = d.route == vp::kRouteStream ? start_table(ay) : window_table(ay);
-        d.tx_off = d.route == vp::kRouteStream ? start_table(ax) : window_table(ax);
+        if (!mm) {   // (the matrix-core form reads its digit tables only)
+            d.ty_off = d.route == vp::kRouteStream ? start_table(ay) : window_table(ay);
+            d.tx_off = d.route == vp::kRouteStream ? start_table(ax) : window_table(ax);
+        }
         if (tiles > INT32_MAX) return fail(VP_ERR_CAPACITY, "batch has more than 2^31-1 tiles");
         p->byte_off[b + 1] = bytes;
         p->prefix[b + 1] = static_cast<int32_t>(tiles);

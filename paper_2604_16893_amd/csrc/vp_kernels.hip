@@ -786,7 +786,8 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
     using elem_t = typename std::conditional<OUT_BF16 != 0, uint16_t, float>::type;
     constexpr int kRowPx = 64 * PX;
     constexpr int V = 3 * PX;                      // values per lane per source row
-    constexpr int kLoadDwords = PX == 4 ? 4 : 3;   // 3*PX bytes plus up to 3 of misalignment
+    static_assert(PX == 2 || PX == 3, "pixels per lane: 3*PX bytes and up to 3 of misalignment are three dwords");
+    constexpr int kLoadDwords = 3;
     constexpr int S = 16 / int(sizeof(elem_t));    // output columns per 16-byte store
     extern __shared__ __align__(16) unsigned char smem[];
 
@@ -907,7 +908,7 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
     // that y % 4 = k is known at every step: the lane's byte offset inside
     // row y is then voff[k] (dword aligned) + shf[k] (0..3), with the row
     // block's own offset, a multiple of 4, in the block's buffer resource.
-    using load_t = typename std::conditional<kLoadDwords == 4, uint4, uint3>::type;
+    using load_t = uint3;
     // sel[k]: the v_perm selector that moves bytes shift and shift + 1 of
     // the loaded dwords (shift = the lane's byte offset mod 4 in row phase k)
     // into the low bytes of two 16-bit halves and zeroes the high bytes.
@@ -937,13 +938,8 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
         const uint32_t b_hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bp >> 32));
         const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
             reinterpret_cast<void*>((uintptr_t(b_hi) << 32) | b_lo), (short)0, static_cast<int>(n), 0x00020000);
-        if constexpr (kLoadDwords == 4) {
-            const auto r = __builtin_amdgcn_raw_buffer_load_b128(rb, voff[k], 0, 0);
-            return make_uint4(r[0], r[1], r[2], r[3]);
-        } else {
-            const auto r = __builtin_amdgcn_raw_buffer_load_b96(rb, voff[k], 0, 0);
-            return make_uint3(r[0], r[1], r[2]);
-        }
+        const auto r = __builtin_amdgcn_raw_buffer_load_b96(rb, voff[k], 0, 0);
+        return make_uint3(r[0], r[1], r[2]);
     };
 
     // Patch 14: the lane's column is column c14 of the workgroup's, at this
@@ -1081,11 +1077,7 @@ void stream_kernel(PlanView plan, int wg0, void* out, Norm norm) {
     // p/2 + 1: the selector is sel, plus 2 per byte for odd p.
     constexpr int kPairs = (V + 1) / 2;
     auto unpack = [&](load_t cur, uint32_t s0, uint32_t (&hv)[kPairs]) __attribute__((always_inline)) {
-        uint32_t d[kLoadDwords];
-        d[0] = cur.x;
-        d[1] = cur.y;
-        d[2] = cur.z;
-        if constexpr (kLoadDwords == 4) d[3] = cur.w;
+        const uint32_t d[kLoadDwords] = {cur.x, cur.y, cur.z};
         // (formed here, per row: hoisted out of the row loop, the four odd
         // selectors would hold four more registers)
         uint32_t s1;
