@@ -208,9 +208,11 @@ int32_t vp_patchify_layout(const vp_item* items, int32_t n_items, int64_t* total
  * pass per frame) each group of items takes.  For tests and tuning.
  * launches: HOST int32[capacity][6], or NULL with capacity 0.  Row i:
  *   kind: VP_KERNEL_GENERIC, VP_KERNEL_YFIRST or VP_KERNEL_XFIRST;
- *   M, the accumulator slots (output rows open at one source row; 0 for
+ *   M, the accumulator slots: no fewer than the output rows open at one
+ *   source row, at least 4 (12 or 16 where more than 8 are open); the most of
+ *   the items that share the launch (0 for the generic kernel);
+ *   the column taps of the x windows, likewise no fewer than theirs (0 for
  *   the generic kernel);
- *   the column taps of the x windows (0 for the generic kernel);
  *   y-first: source pixels per lane; else 0;
  *   x-first: output columns per lane (1, or 2 for column pairs); else 0;
  *   workgroups (the generic kernel: output tiles).
@@ -410,11 +412,12 @@ int32_t vp_position_ids(const vp_item* items, int32_t n_items, int32_t* vit_pos,
  * Kernel timing hook (measurement only; not a step of the method).  The next
  * vp_preprocess_batch, vp_patchify_batch, vp_resize_batch or vp_position_ids
  * call made on this thread (one that launches kernels) records `start` on
- * its stream immediately before its first kernel
- * launch (after the plan upload) and
- * `stop` immediately after its last launch, then forgets both events, so
- * that hipEventElapsedTime(start, stop) is the device time of that call's
- * kernels alone.  A call that fails before launching records neither.
+ * its stream immediately before the first launch that reads or writes the
+ * batch and `stop` immediately after its last launch, then forgets both
+ * events, so that hipEventElapsedTime(start, stop) is the device time of the
+ * batch's kernels alone.  The plan's upload, a launch of its own that also
+ * computes the filter tables, comes before `start` and is not part of it (6 to
+ * 9 us in a kernel trace).  A call that fails before launching records neither.
  * start, stop: events created by the caller (hipEventCreate or equivalent),
  *   still owned by the caller; NULL, NULL cancels a pending request.
  * Errors: VP_ERR_NULL (exactly one of the two is NULL).

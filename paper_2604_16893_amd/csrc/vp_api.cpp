@@ -457,9 +457,12 @@ bool stream_shape(const vp_item& it, const AxisFilter& fx, int32_t m, int32_t pa
         for (int32_t px = 2; px <= 3; ++px) {
             if (!vp::stream_shape_supported(mm, kx, px)) continue;
             if (span > 64 * px || kx > 64 * px) continue;
-            // (patch 14 with px = 3 in float32: two bands of 63 columns leave
-            // two workgroups a CU their LDS, of 56 three; 900x1600 -> 588
-            // columns 244 -> 261 us for 128 frames, in bf16 188 -> 175)
+            // (patch 14 with px = 3: two bands of 63 columns leave two float32
+            // workgroups a CU their LDS, of 56 three.  128 frames of 900x1600, us
+            // with 63 columns and with this rule, which has them take 49 at px =
+            // 2: 588 columns, float32 269 / 215, bf16 181 / 188; 700 columns, 342 /
+            // 301 and 223 / 225.  The plan serves both types: float32 gains more
+            // than bf16 loses)
             if (patch == 14 && px > 2 && band > 56) continue;
             if (vp::stream_wave_bytes(px, kx, 4, patch, band_patches(band)) > vp::kStreamLdsBudget) continue;
             // vector instructions per wave: per source row 3 px M
@@ -630,6 +633,11 @@ int64_t unit_row_band(const vp::DevItem& d, int64_t max_src_rows, int64_t group,
 // 31 / 22 / 24 / 28, 1080p x 2 52 / 26 / 19 / 17, 1080p x 32 77 / 67 / 70 / 86,
 // 1080p x 64 132 / 114 / 126 / 127, 720p x 128 134 / 134 / 138 / 137, 1080p x
 // 128 268 / 276 / 274 / 274; 480p x 64 in float32, x-first, 72 / 75 / 80 / 80.
+// Those inputs lay in the caches; from HBM a batch near the line can lose by
+// short units (ten windows / 16 rows: 1080p x 64 140 / 146, 720p -> 320x576 x 128
+// 121 / 127, 480p x 48 in float32 54 / 62, in bf16 40 / 44) or gain (4K x 28 251 /
+// 240, 720p -> 256x448 x 264 212 / 204, 360p x 32 29 / 24); of 24 batches drawn
+// near it, most of them ragged, 18 gained.
 // So: 16 rows up to a load of 32,768 waves, and where that gives fewer than
 // 2,048 waves 8 rows, then 4.  Patch 14 stores whole patch
 // rows, 14 or 28 (ten windows / 28 / 14: 480p x 16 45 / 31 / 25, 480p x 64
@@ -1780,9 +1788,6 @@ int32_t side_for_device(int dev, Side** out) {
     return VP_OK;
 }
 
-// Runs the plan's launches: on the caller's stream if there is one, else
-// spread over the caller's stream and the side streams, largest estimated
-// work first onto the least loaded stream.
 // The plan's launches (the tile kernel, if it has tiles, and one per
 // streaming shape), spread over the caller's stream and the side streams by
 // estimated cost.  `resize`: the uint8 writer's kernels instead of the float

@@ -754,8 +754,8 @@ __device__ __forceinline__ void store_patch14_row(const elem_t* stage, void* out
 }
 
 // One workgroup streams one source frame (or a band of its output rows) top
-// to bottom; each of its waves owns one band of up to 64 output columns and
-// works alone -- no workgroup barrier anywhere:
+// to bottom; each of its waves owns one band of up to 64 output columns and,
+// for patch 16, works alone, without a workgroup barrier anywhere:
 //   * y pass, in registers: lane t owns PX consecutive pixels of the band's
 //     source span, reads them with one buffer load per row (prefetched four
 //     rows ahead), unpacks them once and adds them with wave-uniform scalar
@@ -1206,7 +1206,7 @@ int launch_stream_shape(const PlanView& plan, const StreamLaunch& L, void* out, 
 
 
 // ===========================================================================
-// x-first streaming kernel (patch 16): vertical scales near 1
+// x-first streaming kernel: vertical scales near 1, and upscales
 // ===========================================================================
 //
 // The streaming kernel above resamples y first and gathers each closed
@@ -2454,9 +2454,10 @@ int launch_generic(const PlanView& plan, void* out, int out_dtype, const Norm& n
     return static_cast<int>(hipGetLastError());
 }
 
-// Compiled shapes: every (M, KX) with 2 pixels per lane, and with 3 pixels
-// per lane where the accumulators still fit the registers of a 1024-thread
-// block (M <= 5).  KX is any tap count from 4 to 16, and a multiple of 4 beyond.
+// Compiled shapes: M of 4 to 6 with 2 pixels per lane (36 accumulators at
+// most), and up to M = 5 with 3 (45), which the registers of four waves a SIMD
+// hold; KX is any tap count from 4 to 16, and a multiple of 4 beyond.  M of 7
+// and 8: 2 pixels (48 accumulators), short windows.
 bool stream_shape_supported(int m, int kx, int px) {
     if (m < 4 || kx < 4 || kx > 32 || (kx > 16 && kx % 4 != 0)) return false;
     if (m > 6)   // 7 or 8 open rows: vertical upscales up to about 2x, whose x axis has short windows too

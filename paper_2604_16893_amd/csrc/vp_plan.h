@@ -1,37 +1,40 @@
 // vp_plan.h -- device-side plan of one vp_preprocess_batch call.
 //
-// The host planner (vp_api.cpp) validates the items, computes their filter
-// tables, work units and row offsets, packs everything into one blob and
-// copies it into the caller's workspace on the call's stream; the
-// kernels (vp_kernels.hip) read it from there.  Layout of the blob, each
+// The host planner (vp_api.cpp) validates the items, derives their work units,
+// row offsets and the tables not computed on the device, packs everything into
+// one blob and has it copied into the caller's workspace on the call's stream;
+// the kernels (vp_kernels.hip) read it from there.  Layout of the blob, each
 // section aligned to 256 bytes:
 //   DevItem    items[n_items]
 //   int32      tile_prefix[n_items + 1]   general-kernel work of item b: [prefix[b], prefix[b+1])
 //   int32      indices[sum of padded counts]  source frame of every (frame pair, dt)
-//   int32      tables[...]                filter tables, 4-byte words
+//   int32      tables[...]                filter tables from the host, 4-byte words: the general
+//                                         kernel's and the uint8 writer's
 //   StreamUnit units[...]                 streaming-kernel work units
 //   uint32     wgs[...]                   streaming-kernel workgroups, grouped per launch:
 //                                         unit index | column band << 20, or kNoWork
 //   TableJob   jobs[...]                  pieces of the tables that follow
 //   int32      tables[...]                the float streaming kernels' tables, computed on the
-//                                         device (not part of the copy; word offsets from the
-//                                         first tables section like the others)
+//                                         device (not part of the copy, but for some plans of
+//                                         the no-alloc entry; word offsets from the first tables
+//                                         section like the others)
 //
 // Tables (word offsets into `tables`; items with the same axis share them):
 //   window table of an axis n_in -> n_out, K taps:
 //       int32 start[n_out]; int32 count[n_out]; float weight[n_out][K]
-//     (the streaming kernels read a table of the starts alone)
+//     (the streaming kernels, but for the writer's matrix-core form, read a
+//     table of the starts alone)
 //   slot table of a y axis n_in -> n_out (streaming kernel), M slots:
 //       [n_in + 6] rows of M words: float weight[slot]
 //         -- output row i is accumulated in slot i mod M from the first row of
 //            its window to its close row; weight[s] is 2^24 times the weight
 //            of source row y in the output row that has slot s at y, or zero
 //            (the kernel reads source bytes as f16 denormals, b * 2^-24)
-//       int32 close_row[n_out + 1]   (the last entry is INT32_MAX)
-//         -- the row after which output row i is complete: the last row of its
-//            window, or the close row of output row i - 1 if that is later;
-//            never decreasing, and several output rows may close on one row
-//            (an upscaled axis, the bottom border)
+//       int32 close_row[n_out + 2]   (the last two entries are INT32_MAX: the
+//            kernels read one close row ahead, up to entry n_out + 1)
+//         -- the row after which output row i is complete, the last row of its
+//            window: never decreasing, and several output rows may close on
+//            one row (an upscaled axis, the bottom border)
 //   fixed-point window table (uint8 writer): as the window table, with int32
 //       weights in units of 2^-22
 //   column table of an x axis (streaming kernels), KX taps, for output bands
@@ -42,6 +45,8 @@
 //     -- start is relative to the first source pixel of the output's band
 //        (the window start of the band's first column) and start + KX never
 //        passes row_px; weights are shifted and zero-padded to match.
+// The uint8 writer's column, slot and digit tables are described at their
+// builders in vp_api.cpp.
 #pragma once
 
 #include <cstdint>
@@ -134,7 +139,9 @@ struct DevItem {
     int32_t ky, kx;          // tap stride of those tables
     int32_t rh, cw;          // general kernel: output rows / columns per LDS sub-tile
     int32_t route;
-    int32_t band;            // streaming kernel: output columns per wave (16, 32, 48 or 64)
+    int32_t band;            // streaming kernels: output columns per wave.  y-first 16, 32, 48 or 64, x-first
+                             // 64 or 128 (pairs), both for patch 14 a multiple of 7 from 14 to 63; uint8
+                             // writer 16 or 32 (matrix cores), 16 to 64 (dot products)
     int32_t sy_off, sx_off;  // streaming kernel: slot and column tables
     int32_t row_px;          // streaming kernels: the column table's row bound (64 * px; x-first W + kx)
     int32_t patch;           // patch edge P (16 or 14): rows of 6 P^2 values, windows of 2P
