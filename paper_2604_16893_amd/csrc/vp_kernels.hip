@@ -1248,7 +1248,7 @@ int launch_stream_shape(const PlanView& plan, const StreamLaunch& L, void* out, 
 // bf16 285 -> 32 us).
 //
 // Patch 14 (single columns, up to 8 taps): four-wave workgroups as in the
-// y-first kernel (two neighbouring bands of 63 columns x the pair's two
+// y-first kernel (two neighbouring bands of up to 63 columns x the pair's two
 // frames), which share a stage in output order and meet at a barrier once per
 // patch row.  256 frames at 588 columns, bf16, against the y-first kernel:
 // 360p 184 -> 141 us, 480p 219 -> 196 us (56-column bands: 147 and 213 us).

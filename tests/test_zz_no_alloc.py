@@ -3,7 +3,9 @@ plan goes to the library's fixed device memory) against vp_preprocess_batch
 through the C ABI: the same rows, bit for bit, with the same grid_thw and
 cu_seqlens, on two calls in a row -- the second with a smaller batch, whose
 plan is shorter than the one the fixed memory still holds -- in both output
-types.  Rows past the batch must stay untouched.
+types; the plan copied whole and in pieces, its tables computed on the device
+or filled on the host; calls in flight one behind another.  Rows past the
+batch must stay untouched.
 """
 import sys
 
@@ -122,3 +124,24 @@ def test_noalloc_plan_copies(n, H, W, h, w, patch, host):
     vp.vp_preprocess_batch_noalloc(items, mean, std, vp.VP_OUT_F32, got)
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int32), ref.view(torch.int32))
+
+
+def test_noalloc_calls_in_flight_keep_their_plans():
+    """Calls one after another on one stream, none waited for, with other
+    frames and sizes in turn: the host memory that a plan is copied from is
+    written again by the next call while earlier ones are still in flight."""
+    it = workloads.Item("video", 16, 480, 854, "uniform", 710, {"mode": "uniform", "n": 1})
+    f = workloads.frames_torch(it, DEV)
+    mean, std = (0.481, 0.458, 0.408), (0.269, 0.261, 0.276)
+    batches = [[vp.Item(f, (np.arange(n, dtype=np.int32) * step + k) % 16, h, w)]
+               for k, (n, step, h, w) in enumerate([(16, 1, 352, 640), (15, 3, 320, 576), (64, 5, 64, 96), (2, 7, 256, 448)])]
+    refs = [vp.preprocess(b, mean, std, "f32")[0] for b in batches]
+    outs = [[torch.full_like(r, float("nan")) for r in refs] for _ in range(5)]
+    torch.cuda.synchronize()
+    for turn in outs:
+        for b, out in zip(batches, turn):
+            vp.vp_preprocess_batch_noalloc(b, mean, std, vp.VP_OUT_F32, out)
+    torch.cuda.synchronize()
+    for turn in outs:
+        for ref, out in zip(refs, turn):
+            assert torch.equal(out.view(torch.int32), ref.view(torch.int32))
