@@ -281,6 +281,10 @@ int32_t vp_preprocess_batch(const vp_item* items, int32_t n_items, const float* 
  * calls whose work can overlap on one device (different streams, or other
  * threads, without synchronisation between them) race and give undefined
  * output.  Calls on one stream are ordered and safe.
+ * A captured call's graph copies the plan again at each replay, from host
+ * memory of the capturing thread that the thread's next call of this entry
+ * writes over: replays after that run the later call's plan on the captured
+ * call's launches, which is undefined.
  * Arguments, outputs, ownership and asynchrony otherwise as for
  * vp_preprocess_batch.
  * Errors: as vp_preprocess_batch, with VP_ERR_CAPACITY when the batch's plan

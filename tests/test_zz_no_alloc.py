@@ -145,3 +145,31 @@ def test_noalloc_calls_in_flight_keep_their_plans():
     for turn in outs:
         for ref, out in zip(refs, turn):
             assert torch.equal(out.view(torch.int32), ref.view(torch.int32))
+
+
+@pytest.mark.parametrize("specs", [
+    [(2, 130, 170, 96, 128)],                                                # one copy, tables on the device
+    [(8, 480, 854, 352, 640), (1, 1000, 700, 320, 224), (3, 90, 60, 96, 64)],   # several pieces, several kernels
+    [(64, 270, 480, 128, 224)] * 20,                                         # one copy with its tables
+], ids=["one_piece", "pieces", "whole"])
+def test_noalloc_captured_and_replayed(specs):
+    """A captured call replayed over frames that change, with the library's
+    other entry and torch's work between the replays: each replay's rows are
+    the eager call's."""
+    items = [vp.Item(torch.randint(0, 256, (n, H, W, 3), dtype=torch.uint8, device=DEV),
+                     np.arange(n, dtype=np.int32), h, w) for n, H, W, h, w in specs]
+    mean, std = (0.481, 0.458, 0.408), (0.269, 0.261, 0.276)
+    out = torch.empty_like(vp.preprocess(items, mean, std, "f32")[0])
+    vp.vp_preprocess_batch_noalloc(items, mean, std, vp.VP_OUT_F32, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        vp.vp_preprocess_batch_noalloc(items, mean, std, vp.VP_OUT_F32, out)
+    for _ in range(4):
+        items[0].frames.random_(0, 256)
+        out.fill_(float("nan"))
+        ref = vp.preprocess(items, mean, std, "f32")[0]
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int32), ref.view(torch.int32))
