@@ -747,8 +747,9 @@ void merge_shapes(const vp_item* items, const std::vector<vp::DevItem>& dev, con
     }
 }
 
-// Lays out the streaming units as launches and their workgroup lists.
-int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, Plan* p) {
+// Lays out the streaming units as launches, of workgroups of `threads`, and
+// their workgroup lists.
+int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, int32_t threads, Plan* p) {
     // Units of one kernel shape form one launch, whatever their widths.  Its
     // workgroups are listed explicitly: entry g (unit index | band << 20, or
     // kNoWork) runs as workgroup g, and consecutive workgroups go to the
@@ -761,6 +762,10 @@ int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, Plan* p) {
     // g-th eight is (x + g) mod 8: a pattern in the units' lengths that
     // repeats every few units (the units of one frame) then spreads over all
     // eight XCDs instead of loading some more than others.
+    // A launch holds fewer than 2^32 threads: one that would reach half of that
+    // (the writer's 16- and 32-column bands of half a million wide frames) goes
+    // on in another.
+    const int32_t most_wgs = static_cast<int32_t>((int64_t(1) << 31) / threads);
     if (keyed.size() > vp::kWgUnitMask + 1)
         return fail(VP_ERR_CAPACITY, "batch has more than 2^20 streaming work units");
     // order: by shape, then band count, then as generated (a grouping: the
@@ -794,6 +799,12 @@ int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, Plan* p) {
             const size_t c1 = std::min(c0 + 8, k1);
             int32_t rounds = 0;
             for (size_t k = c0; k < c1; ++k) rounds = std::max(rounds, keyed[order[k]].bands);
+            if (static_cast<int64_t>(p->wgs.size()) - L.first + 8 * int64_t(rounds) > most_wgs) {
+                L.count = static_cast<int32_t>(p->wgs.size()) - L.first;
+                p->launches.push_back(L);
+                L.first += L.count;
+                L.cost = 0;
+            }
             const uint32_t u0 = static_cast<uint32_t>(p->units.size());
             for (size_t k = c0; k < c1; ++k) {
                 const Keyed& e = keyed[order[k]];
@@ -1061,7 +1072,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
                 }
             }
         }
-        if (const int32_t st = assemble_launches(keyed, P, p); st != VP_OK) return st;
+        if (const int32_t st = assemble_launches(keyed, P, P == 14 ? 256 : 64, p); st != VP_OK) return st;
         p->off_items = 0;
         p->off_prefix = align_up(p->off_items + sizeof(vp::DevItem) * p->items.size());
         p->off_indices = align_up(p->off_prefix + sizeof(int32_t) * p->prefix.size());
@@ -1483,7 +1494,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
             }
         }
     }
-    if (const int32_t st = assemble_launches(keyed, P, p); st != VP_OK) return st;
+    if (const int32_t st = assemble_launches(keyed, P, 64, p); st != VP_OK) return st;
 
     p->off_items = 0;
     p->off_prefix = align_up(p->off_items + sizeof(vp::DevItem) * p->items.size());

@@ -308,6 +308,19 @@ def test_writer_batches_of_both_forms_near_the_unit_limit(dot, matrix):
     assert int(off[-1]) == sum(n * h * w * 3 for _, _, h, w, n in (dot, matrix)) and ws > 0
 
 
+def test_writer_launches_of_wide_frames_stay_below_the_grid_limit():
+    """A launch holds fewer than 2^32 threads.  128 bands of 16 columns of half
+    a million frames (104 GB of them) are 67.8 million single-wave workgroups,
+    4.34e9 threads, which go in several launches; the dot-product form's bands
+    of 64 columns would fit one."""
+    n = 530000
+    it = vp.Item((0x10000, 2, 40, 8192), np.arange(n, dtype=np.int32) % 2, 32, 2048)
+    rows = vp.vp_resize_kernels([it]).tolist()
+    assert {(r[0], r[4]) for r in rows} == {(vp.VP_WRITER_MATRIX, 16)}
+    assert sum(r[5] for r in rows) == n * 128   # (frames in eights: no empty entries)
+    assert all(64 * r[5] < 1 << 32 and r[5] % 8 == 0 for r in rows)
+
+
 def test_a_plan_given_up_leaves_no_error_behind():
     """vp_last_error_message is the detail of the last call that failed: a
     call whose first plan has too many work units and whose second one fits
