@@ -386,9 +386,9 @@ def _event_handle(ev) -> int:
 
 def vp_set_kernel_events(start, stop):
     """Ask the next vp_preprocess_batch call on this thread to record `start`
-    before its first kernel and `stop` after its last one (torch.cuda.Event
-    objects that have been recorded at least once, raw hipEvent_t handles, or
-    None, None to cancel)."""
+    before the batch's first kernel (after the plan's upload) and `stop` after
+    its last one (torch.cuda.Event objects that have been recorded at least
+    once, raw hipEvent_t handles, or None, None to cancel)."""
     _check(lib().vp_set_kernel_events(ctypes.c_void_p(_event_handle(start)),
                                       ctypes.c_void_p(_event_handle(stop))),
            "vp_set_kernel_events")
