@@ -747,6 +747,69 @@ void merge_shapes(const vp_item* items, const std::vector<vp::DevItem>& dev, con
     }
 }
 
+// Likewise of the uint8 writer's matrix-core form: a kernel of more loads a
+// chunk (T), of windows that start anywhere (A) or of two products a group
+// (TWO) serves what asks for less, with the same bytes.  Instructions per wave:
+// about 20 a load and chunk, 12 a chunk for LDS reads of 8 bytes and 72 for
+// unaligned ones, 40 a second product of a group.  Measured, us a call as two
+// launches and as one: 102 frames of 688x86 with 49 of 190x239 70 -> 32, four
+// items of 2 to 34 frames 106 -> 48, 16 frames each of 480p and 1080p 76 -> 62;
+// at the limit, 128 frames each of 480p and 1080p 329 -> 331, of 200x300 and
+// 720p 196 -> 189.
+void merge_matrix_shapes(const std::vector<vp::DevItem>& dev, std::vector<StreamShape>* shapes) {
+    using Key = std::tuple<bool, int32_t, int32_t, bool>;   // wide, T, A, TWO
+    const auto key_of = [](const StreamShape& sh) {
+        return Key((sh.m & vp::kRsMmWide) != 0, sh.m % vp::kRsMmTwo, sh.px, (sh.m & vp::kRsMmTwo) != 0);
+    };
+    const auto chunk_cost = [](const Key& k) {   // a chunk of 16 source rows
+        return 20 * std::get<1>(k) + (std::get<2>(k) == 16 ? 0 : std::get<2>(k) == 8 ? 12 : 72);
+    };
+    std::map<Key, std::vector<int32_t>> groups;
+    for (size_t b = 0; b < dev.size(); ++b)
+        if (dev[b].route == vp::kRouteStream && (*shapes)[b].kx == vp::kRsMmShape)
+            groups[key_of((*shapes)[b])].push_back(static_cast<int32_t>(b));
+    while (groups.size() > 1) {
+        int64_t best = kMergeInstructions;
+        auto best_a = groups.end(), best_b = groups.end();
+        Key best_key;
+        for (auto a = groups.begin(); a != groups.end(); ++a)
+            for (auto b = std::next(a); b != groups.end(); ++b) {
+                const auto& [wide, ta, aa, two_a] = a->first;
+                const auto& [wide_b, tb, ab, two_b] = b->first;
+                if (wide != wide_b) continue;
+                const int32_t align = std::min(aa, ab);
+                Key to(wide, align == 16 ? std::max(ta, tb) : 8, wide && align == 8 ? 1 : align, two_a || two_b);
+                int64_t extra = 0;
+                for (const auto* g : {&*a, &*b})
+                    for (const int32_t k : g->second) {
+                        const vp::DevItem& d = dev[k];
+                        const int64_t waves = int64_t(d.t) * (*shapes)[k].bands;
+                        extra += waves * ((d.H + 15) / 16) * (chunk_cost(to) - chunk_cost(g->first));
+                        if (std::get<3>(to) != std::get<3>(g->first)) extra += waves * ((d.h + 15) / 16) * 40;
+                    }
+                if (extra < best) {
+                    best = extra;
+                    best_a = a;
+                    best_b = b;
+                    best_key = to;
+                }
+            }
+        if (best_a == groups.end()) return;
+        std::vector<int32_t> both = std::move(best_a->second);
+        both.insert(both.end(), best_b->second.begin(), best_b->second.end());
+        std::sort(both.begin(), both.end());
+        const auto& [wide, t, align, two] = best_key;
+        for (const int32_t k : both) {
+            (*shapes)[k].m = t + (wide ? vp::kRsMmWide : 0) + (two ? vp::kRsMmTwo : 0);
+            (*shapes)[k].px = align;
+        }
+        groups.erase(best_a);
+        groups.erase(best_b);
+        auto& into = groups[best_key];   // (both were joined into a shape that one of them may have had)
+        into.insert(into.end(), both.begin(), both.end());
+    }
+}
+
 // Lays out the streaming units as launches, of workgroups of `threads`, and
 // their workgroup lists.
 int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, int32_t threads, Plan* p) {
@@ -1430,6 +1493,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
         p->prefix[b + 1] = static_cast<int32_t>(tiles);
     }
     p->total_rows = 0;
+    merge_matrix_shapes(p->items, &shapes);
 
     // Streaming units: one per (item, frame, band of output rows), the
     // bands sized as for the float path (multiples of the kernel's store

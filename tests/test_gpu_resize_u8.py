@@ -230,3 +230,36 @@ def test_matrix_core_form_edges(H, W, h, w, patch):
         ref = oracle.resize_u8(src[f], h, w)
         bad = np.argwhere(got[k] != ref)
         assert bad.size == 0, f"frame {f}: {len(bad)} bytes differ, first at {bad[0]}"
+
+
+# Batches whose launches are joined: the kernel of more loads, unaligned windows
+# or two products runs items that alone take less
+JOINED = [
+    # patch, [(H, W, h, w)], {(source pixels per row, columns per workgroup)}
+    ("every_form", 16, [c[:4] for c in MM_CASES if c[4] == 16], {(128, 32), (128, 16)}),
+    ("every_form_patch14", 14, [c[:4] for c in MM_CASES if c[4] == 14], {(128, 32), (128, 16)}),
+    ("loads", 16, [(40, 33, 96, 128), (101, 150, 64, 128)], {(64, 32)}),
+    ("second_product", 16, [(96, 150, 96, 128), (400, 150, 96, 128)], {(64, 32)}),
+    ("windows_on_8", 16, [(64, 100, 64, 96), (61, 360, 64, 128)], {(128, 32)}),
+    ("windows_on_1", 16, [(61, 360, 64, 128), (64, 300, 64, 128), (90, 420, 64, 128)], {(128, 32)}),
+    ("wide_windows_on_1", 16, [(120, 395, 64, 64), (100, 500, 64, 128)], {(128, 16)}),
+]
+
+
+@pytest.mark.parametrize("name,patch,specs,shapes", JOINED, ids=[c[0] for c in JOINED])
+def test_joined_launches_give_the_same_bytes(name, patch, specs, shapes):
+    items, hosts = [], []
+    for k, (H, W, h, w) in enumerate(specs):
+        it, fd = _video(520 + k, 2, H, W)
+        items.append((fd, np.array([1, 0], np.int32), h, w))
+        hosts.append(workloads.frames_np(it))
+    launches = vp.vp_resize_kernels([vp.Item(f, i, h, w, patch) for f, i, h, w in items]).tolist()
+    log(f"joined {name}: {launches}")
+    assert len(launches) == len(shapes) and {(r[3], r[4]) for r in launches} == shapes
+    assert all(r[0] == vp.VP_WRITER_MATRIX for r in launches)
+    out, off = run(items, patch=patch)
+    for k, (H, W, h, w) in enumerate(specs):
+        got = frames_of(out, off, k, 2, h, w).cpu().numpy()
+        for m, f in enumerate([1, 0]):
+            bad = np.argwhere(got[m] != oracle.resize_u8(hosts[k][f], h, w))
+            assert bad.size == 0, f"{H}x{W} -> {h}x{w}, frame {f}: {len(bad)} bytes differ, first at {bad[0]}"

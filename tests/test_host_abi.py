@@ -513,6 +513,18 @@ def test_resize_kernels_describes_the_writers_launches():
     assert L.vp_resize_kernels(b.arr, 0, None, 0, ctypes.byref(n)) == vp.VP_ERR_ARG
 
 
+@pytest.mark.parametrize("n,launches", [(16, 1), (400, 2)])
+def test_writer_launches_of_small_batches_are_joined(n, launches):
+    """Items of 200x300 and of 720p take matrix-core kernels of their own; a
+    small batch of both is one launch of the one that serves both."""
+    a, b = (vp.Item((0x10000 << 24 * k, n, H, W), np.arange(n, dtype=np.int32), h, w)
+            for k, (H, W, h, w) in enumerate(((200, 300, 320, 480), (720, 1280, 384, 672))))
+    alone = [vp.vp_resize_kernels([x]).tolist()[0] for x in (a, b)]
+    assert [r[3] for r in alone] == [64, 128]
+    rows = vp.vp_resize_kernels([a, b]).tolist()
+    assert [r[3] for r in rows] == ([128] if launches == 1 else [64, 128])
+
+
 def test_tall_targets_take_the_streaming_kernels():
     """Targets of 2^15 rows and more are planned like any other: the layout
     counts their rows, and they take the streaming kernels (their GPU parity
