@@ -161,6 +161,7 @@ struct Plan {
     int64_t total_rows = 0;
     std::vector<int64_t> byte_off;   // uint8 writer: [n + 1] output byte offsets of the items
     int64_t generic_cost = 0;   // source pixels the general kernel reads, roughly
+    int64_t generic_chain = 0;  // most steps of one of its workgroups, each waiting for a load (INT64_MAX: the tile kernel)
     // tables computed on the device: their pieces, their words, and where they
     // begin (the blob up to there is copied)
     std::vector<vp::TableJob> jobs;
@@ -900,7 +901,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
     int32_t P = vp::kPatch;
     if (const int32_t st = batch_patch(items, n, &P); st != VP_OK) return st;
     p->items.assign(n, vp::DevItem{});
-    p->generic_cost = 0;
+    p->generic_cost = p->generic_chain = 0;
     p->prefix.assign(n + 1, 0);
     p->grid.assign(size_t(n) * 3, 0);
     p->cu.assign(n + 1, 0);
@@ -1025,6 +1026,9 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
         if (d.route == vp::kRouteGeneric) {
             tiles += int64_t(d.t) * d.hm * d.wm;
             p->generic_cost += int64_t(2) * d.t * d.H * d.W;
+            const int64_t span = int64_t(d.cw) * d.W / d.w + d.kx;
+            const int64_t steps = (d.rh * span * 3 / vp::kGenericThreads + 1) * d.ky + (d.rh * d.cw * 3 / vp::kGenericThreads + 1) * d.kx;
+            p->generic_chain = std::max(p->generic_chain, 2 * (4 * P * P / (d.rh * d.cw)) * steps);
         }
         if (rows > INT32_MAX || tiles > INT32_MAX)
             return fail(VP_ERR_CAPACITY, "batch has more than 2^31-1 rows");
@@ -1180,7 +1184,7 @@ int32_t build_patch_plan(const vp_item* items, int32_t n, Plan* p) {
     p->units.clear();
     p->wgs.clear();
     p->launches.clear();
-    p->generic_cost = 0;
+    p->generic_cost = p->generic_chain = 0;
     int64_t rows = 0, tiles = 0;
     for (int32_t b = 0; b < n; ++b) {
         const vp_item& it = items[b];
@@ -1243,7 +1247,7 @@ int32_t build_rows_plan(const vp_item* items, int32_t n, Plan* p) {
     p->units.clear();
     p->wgs.clear();
     p->launches.clear();
-    p->generic_cost = 0;
+    p->generic_cost = p->generic_chain = 0;
     int64_t rows = 0;
     for (int32_t b = 0; b < n; ++b) {
         const vp_item& it = items[b];
@@ -1352,7 +1356,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
     p->units.clear();
     p->wgs.clear();
     p->launches.clear();
-    p->generic_cost = 0;
+    p->generic_cost = p->generic_chain = 0;
     auto append = [&](std::shared_ptr<const std::vector<int32_t>> words) -> int32_t {
         const int32_t o = static_cast<int32_t>(p->table_words);
         p->table_words += words->size();
@@ -1483,6 +1487,7 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
             d.route = vp::kRouteResize;
             tiles += int64_t(it.n_idx) * d.hm * d.wm;
             p->generic_cost += int64_t(8) * it.n_idx * it.src_h * it.src_w;   // about 8x the streaming cost per pixel
+            p->generic_chain = INT64_MAX;
         }
         if (!mm) {   // (the matrix-core form reads its digit tables only)
             d.ty_off = d.route == vp::kRouteStream ? start_table(ay) : window_table(ay);
@@ -1553,7 +1558,8 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
                 e.unit.p_flags = k;
                 e.unit.i0 = i0;
                 e.unit.i1 = i1;
-                e.cost = int64_t(i1 - i0) * d.H / d.h * d.W;
+                // (times the bands: those of the matrix-core form are a half or a quarter of 64 columns)
+                e.cost = int64_t(i1 - i0) * d.H / d.h * d.W * sh.band / 64;
                 keyed.push_back(e);
             }
         }
@@ -1875,11 +1881,21 @@ int32_t run_launches(const Plan& p, const vp::PlanView& view, void* out_rows, in
     struct Job {
         int32_t launch;   // index into p.launches, or -1 for the general kernel
         int64_t cost;
+        int32_t rank;     // launched before those of a lower one
     };
+    // A general or tile kernel whose workgroups run long goes first: of 57 KB
+    // of LDS each, they find no room on CUs that small workgroups have filled
+    // (132 frames of 350x915 with 12 of 408x5886 on the writer's tile kernel
+    // 504 -> 279 us a call; 284 frames of 1037x236 and 1165x347 with 3 of
+    // 335x2602 on the general one 2,128 -> 1,651).  Up to about 200 steps, 25
+    // us, it follows by its cost (64 frames of 720p with 8 of 60x60 -> 320x320:
+    // first 123, by cost 113).  The writer's dot products, a row at a time, go
+    // before its matrix-core form (201 frames of 161x369 with 207 of 434x538 on
+    // dot products 228 -> 139).
     std::vector<Job> jobs;
-    if (view.n_tiles > 0) jobs.push_back(Job{-1, p.generic_cost});
+    if (view.n_tiles > 0) jobs.push_back(Job{-1, p.generic_cost, p.generic_chain > 200 ? 2 : 0});
     for (size_t k = 0; k < p.launches.size(); ++k)
-        jobs.push_back(Job{static_cast<int32_t>(k), p.launches[k].cost});
+        jobs.push_back(Job{static_cast<int32_t>(k), p.launches[k].cost, resize && p.launches[k].kx != vp::kRsMmShape ? 1 : 0});
     auto launch = [&](const Job& j, hipStream_t st) -> int32_t {
         if (resize) {
             const int err = j.launch < 0 ? vp::launch_resize(view, out_rows, st)
@@ -1907,7 +1923,7 @@ int32_t run_launches(const Plan& p, const vp::PlanView& view, void* out_rows, in
     Side* side = nullptr;
     int32_t st = side_for_device(dev, &side);
     if (st != VP_OK) return st;
-    std::stable_sort(jobs.begin(), jobs.end(), [](const Job& a, const Job& b) { return a.cost > b.cost; });
+    std::stable_sort(jobs.begin(), jobs.end(), [](const Job& a, const Job& b) { return std::make_pair(a.rank, a.cost) > std::make_pair(b.rank, b.cost); });
     const int lanes = std::min<int>(static_cast<int>(jobs.size()), kSideStreams + 1);
     std::vector<int> lane_of(jobs.size(), 0);
     std::vector<int64_t> load(lanes, 0);
