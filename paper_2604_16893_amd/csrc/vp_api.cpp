@@ -1067,11 +1067,11 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
         return wave_rows / (kWaveSlots * 8);
     };
     auto workgroup_waves = [&](int64_t min_windows, int64_t max_src_rows, int64_t short_rows = 0,
-                               bool as_load = false) {
+                               bool as_load = false, int32_t over_slots = 0) {
         int64_t waves = 0;
         for (int32_t b = 0; b < n; ++b) {
             const vp::DevItem& d = p->items[b];
-            if (d.route != vp::kRouteStream) continue;
+            if (d.route != vp::kRouteStream || shapes[b].m <= over_slots) continue;
             const int64_t group = d.patch == 16 ? 4 : d.patch;
             const int64_t units = UnitSplit(d.h, unit_row_band(d, max_src_rows, group, min_windows, short_rows), group).n;
             // units per row band: one per distinct frame (patch 14: per pair)
@@ -1107,7 +1107,17 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
     const int64_t short_rows =
         short_unit_rows([&](int64_t rows) { return workgroup_waves(10, max_src_rows, rows); },
                         [&](int64_t rows) { return workgroup_waves(10, max_src_rows, rows, true); }, kShortWaves, P);
-    const auto lay_out = [&](int64_t short_rows) -> int32_t {
+    // Upscales of 12 or 16 slots in a batch of long units are judged alone: a
+    // source row costs their waves about 1 us, and a launch of a few long units
+    // lasts as long as one (an image of 110x121 -> 224x256 behind 121 frames of
+    // 474x693, no-alloc entry, where launches follow one another: 137 us with
+    // long units, 117 with short ones).
+    const int64_t short_many =
+        short_rows > 0 ? short_rows
+                       : short_unit_rows([&](int64_t rows) { return workgroup_waves(10, 0, rows, false, vp::kStreamSlots); },
+                                         [&](int64_t rows) { return workgroup_waves(10, 0, rows, true, vp::kStreamSlots); },
+                                         kShortWaves, P);
+    const auto lay_out = [&](int64_t short_rows, int64_t short_many) -> int32_t {
         std::vector<Keyed> keyed;
         keyed.reserve(static_cast<size_t>(stream_frames));
         for (int32_t b = 0; b < n; ++b) {
@@ -1117,7 +1127,8 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
             // whole store groups: multiples of 4 rows for patch 16, whole
             // patch rows (14 output rows, stored at once) for patch 14
             const int64_t group = d.patch == 16 ? 4 : d.patch;
-            const UnitSplit split(d.h, unit_row_band(d, max_src_rows, group, min_windows, short_rows), group);
+            const bool alone = short_rows == 0 && short_many > 0 && sh.m > vp::kStreamSlots;
+            const UnitSplit split(d.h, unit_row_band(d, alone ? 0 : max_src_rows, group, min_windows, alone ? short_many : short_rows), group);
             for (int32_t tt = 0; tt < d.t; ++tt) {
                 const bool same = p->indices[d.idx_off + 2 * tt] == p->indices[d.idx_off + 2 * tt + 1];
                 const bool pair_units = d.patch == 14;   // both frames in one unit
@@ -1151,10 +1162,14 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
         p->bytes = align_up(p->off_gen + sizeof(int32_t) * p->gen_words);
         return VP_OK;
     };
-    int32_t st = lay_out(short_rows);
+    const std::string before = g_last_error;
+    int32_t st = lay_out(short_rows, short_many);
     // (more units make a larger plan: one that no longer fits the no-alloc
-    // entry's plan memory keeps the longer units)
-    if (st == VP_OK && short_rows > 0 && p->bytes > static_cast<size_t>(vp::kNoAllocPlanBytes)) st = lay_out(0);
+    // entry's plan memory, or the work units, keeps the longer units)
+    if (short_many > 0 && (st == VP_ERR_CAPACITY || (st == VP_OK && p->bytes > static_cast<size_t>(vp::kNoAllocPlanBytes)))) {
+        st = lay_out(0, 0);
+        if (st == VP_OK) g_last_error = before;
+    }
     if (st != VP_OK) return st;
     // the computed tables' offsets, from the first tables section like the others
     const int64_t gen = static_cast<int64_t>(p->off_gen - p->off_tables) / 4;

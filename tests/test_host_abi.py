@@ -525,6 +525,19 @@ def test_writer_launches_of_small_batches_are_joined(n, launches):
     assert [r[3] for r in rows] == ([128] if launches == 1 else [64, 128])
 
 
+def test_upscales_of_many_slots_are_cut_short_in_a_batch_of_long_units():
+    """An image raised over 2x behind a large clip: one launch of its own,
+    whose few workgroups are as short as in a batch of its own."""
+    clip = vp.Item((0x10000, 121, 474, 693), np.arange(121, dtype=np.int32), 416, 704)
+    image = vp.Item((0x80000000, 1, 110, 121), [0], 256, 224)
+    own = vp.vp_batch_kernels([image]).tolist()
+    assert [r[:3] for r in own] == [[vp.VP_KERNEL_XFIRST, 12, 4]]
+    rows = vp.vp_batch_kernels([clip, image]).tolist()
+    assert own[0] in rows
+    long_units = vp.vp_batch_kernels([clip]).tolist()[0]
+    assert long_units in rows
+
+
 def test_tall_targets_take_the_streaming_kernels():
     """Targets of 2^15 rows and more are planned like any other: the layout
     counts their rows, and they take the streaming kernels (their GPU parity
