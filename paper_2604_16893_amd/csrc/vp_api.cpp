@@ -643,9 +643,11 @@ int64_t unit_row_band(const vp::DevItem& d, int64_t max_src_rows, int64_t group,
 // 2,048 waves 8 rows, then 4.  Patch 14 stores whole patch
 // rows, 14 or 28 (ten windows / 28 / 14: 480p x 16 45 / 31 / 25, 480p x 64
 // 89 / 69 / 70, 720p x 64 92 / 82 / 86): 14 up to 10,240 waves.  The uint8
-// writer's dot-product form re-reads at a higher price (ten windows / 16 rows:
-// 720p x 64 108 / 99, 480p x 128 130 / 137).
-constexpr int64_t kShortWaves = 32768, kShortWavesDot = 20480;
+// writer's dot-product form re-reads at a higher price (ten windows / 16 rows, us
+// a call: 841x2431 -> 128x352 x 120, 10,560 waves, 330 / 323, x 150 391 / 387, x
+// 182, 16,016 waves, 457 / 484; 4K -> 320x576 x 36, 12,960 waves, 425 / 402;
+// 1080p -> 160x288 x 200, 18,000 waves, 536 / 550).
+constexpr int64_t kShortWaves = 32768, kShortWavesDot = 14000;
 
 template <class Waves, class Load>
 int64_t short_unit_rows(Waves waves, Load load, int64_t most, int32_t patch = 16) {
