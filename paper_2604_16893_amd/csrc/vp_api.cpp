@@ -1739,6 +1739,7 @@ void pack_plan(const Plan& p, uint8_t* base) {
 // 78 us a call back to back, 8 frames 36 -> 32.
 constexpr size_t kCopyPiece = 16384;
 constexpr size_t kCopyPieces = 4;
+constexpr int64_t kCopyRows = 32768;     // (upload_plan)
 
 // Whether that entry fills the computed tables on the host and copies them with
 // the rest: a kernel that computes them between the copy and the batch costs a
@@ -1827,11 +1828,23 @@ int32_t upload_plan(const Plan& p, void* workspace, hipStream_t stream) {
     void* src = nullptr;
     e = hipHostGetDevicePointer(&src, s.host, 0);
     if (e != hipSuccess) return hip_fail(e, "hipHostGetDevicePointer");
-    const int err = vp::launch_upload(
-        workspace, src, static_cast<int64_t>(p.off_gen),
-        reinterpret_cast<const vp::TableJob*>(static_cast<const uint8_t*>(src) + p.off_jobs),
-        static_cast<int>(p.jobs.size()), reinterpret_cast<int32_t*>(static_cast<uint8_t*>(workspace) + p.off_tables), stream);
-    if (err != 0) return hip_fail(static_cast<hipError_t>(err), "plan upload launch");
+    // A small plan without computed tables: the runtime sends its copy with the
+    // stream's commands, sooner than a kernel reads it, but takes the host 1 us
+    // more, which calls of little GPU work wait for (position tables 16.3 ->
+    // 17.7 us a call).  So: for the general (or the writer's tile) kernel alone
+    // (59 frames of 42x67 -> 28x140 in float32 55.0 -> 51.7), and for patchify
+    // of 100 MB of rows and more (64 frames of 512x704 in bf16 38.5 -> 37.2).
+    const bool long_call = (p.generic_cost > 0 && p.launches.empty()) ||
+                           (p.items[0].route == vp::kRoutePatch && p.total_rows >= kCopyRows);
+    if (long_call && p.off_gen <= kCopyPiece)
+        e = hipMemcpyAsync(workspace, s.host, p.off_gen, hipMemcpyHostToDevice, stream);
+    else
+        e = static_cast<hipError_t>(vp::launch_upload(
+            workspace, src, static_cast<int64_t>(p.off_gen),
+            reinterpret_cast<const vp::TableJob*>(static_cast<const uint8_t*>(src) + p.off_jobs),
+            static_cast<int>(p.jobs.size()), reinterpret_cast<int32_t*>(static_cast<uint8_t*>(workspace) + p.off_tables),
+            stream));
+    if (e != hipSuccess) return hip_fail(e, "plan upload");
     e = hipEventRecord(s.done, stream);
     if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
     s.pending = true;
