@@ -159,6 +159,7 @@ struct Plan {
     std::vector<int32_t> grid;  // [n][3]
     std::vector<int32_t> cu;    // [n + 1]
     int64_t total_rows = 0;
+    int64_t long_unit_rows = 0;   // most source rows of a float streaming unit where none is cut short (INT64_MAX: over 8 slots)
     std::vector<int64_t> byte_off;   // uint8 writer: [n + 1] output byte offsets of the items
     int64_t generic_cost = 0;   // source pixels the general kernel reads, roughly
     int64_t generic_chain = 0;  // most steps of one of its workgroups, each waiting for a load (INT64_MAX: the tile kernel)
@@ -896,8 +897,9 @@ int32_t assemble_launches(const std::vector<Keyed>& keyed, int32_t P, int32_t th
 }
 
 // With `most_slots` below kSlotWords, items that need more open rows than that
-// go to the general kernel, whose plan holds no work units.
-int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots = vp::kSlotWords) {
+// go to the general kernel, whose plan holds no work units.  `long_units`: no
+// unit is cut short for a small batch.
+int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots = vp::kSlotWords, bool long_units = false) {
     if (items == nullptr) return fail(VP_ERR_NULL, "items is NULL");
     if (n < 1) return fail(VP_ERR_ARG, "n_items < 1");
     int32_t P = vp::kPatch;
@@ -1106,7 +1108,16 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
     }
     const int64_t max_src_rows = source_row_cap();
     const int64_t min_windows = workgroup_waves(15, max_src_rows) >= 4 * kWaveSlots ? 15 : 10;
+    p->long_unit_rows = 0;
+    for (int32_t b = 0; b < n; ++b) {
+        const vp::DevItem& d = p->items[b];
+        if (d.route == vp::kRouteStream)
+            p->long_unit_rows = std::max(p->long_unit_rows, shapes[b].m > vp::kStreamSlots
+                                                                ? INT64_MAX
+                                                                : std::min<int64_t>(d.H, std::max(10 * int64_t(d.ky), max_src_rows) + d.ky));
+    }
     const int64_t short_rows =
+        long_units ? 0 :
         short_unit_rows([&](int64_t rows) { return workgroup_waves(10, max_src_rows, rows); },
                         [&](int64_t rows) { return workgroup_waves(10, max_src_rows, rows, true); }, kShortWaves, P);
     // Upscales of 12 or 16 slots in a batch of long units are judged alone: a
@@ -1115,7 +1126,7 @@ int32_t build_plan(const vp_item* items, int32_t n, Plan* p, int32_t most_slots 
     // 474x693, no-alloc entry, where launches follow one another: 137 us with
     // long units, 117 with short ones).
     const int64_t short_many =
-        short_rows > 0 ? short_rows
+        short_rows > 0 || long_units ? short_rows
                        : short_unit_rows([&](int64_t rows) { return workgroup_waves(10, 0, rows, false, vp::kStreamSlots); },
                                          [&](int64_t rows) { return workgroup_waves(10, 0, rows, true, vp::kStreamSlots); },
                                          kShortWaves, P);
@@ -1604,7 +1615,8 @@ int32_t build_resize_plan(const vp_item* items, int32_t n, Plan* p, bool few_uni
 // ---------------------------------------------------------------------------
 
 // (kBatchSmall: kBatch in less memory, upscales of many slots on the general kernel)
-enum class PlanKind : int64_t { kBatch = 1, kPatch = 2, kResize = 3, kRows = 4, kBatchSmall = 5 };
+// (kBatchLong: kBatch without short units)
+enum class PlanKind : int64_t { kBatch = 1, kPatch = 2, kResize = 3, kRows = 4, kBatchSmall = 5, kBatchLong = 6 };
 
 constexpr size_t kPlanCacheMax = 8;
 std::mutex g_plan_mu;
@@ -1625,6 +1637,7 @@ int32_t build_kind(PlanKind kind, const vp_item* items, int32_t n, Plan* p) {
         case PlanKind::kBatch:
             return or_else(build_plan(items, n, p), [&] { return build_plan(items, n, p, vp::kStreamSlots); });
         case PlanKind::kBatchSmall: return build_plan(items, n, p, vp::kStreamSlots);
+        case PlanKind::kBatchLong: return build_plan(items, n, p, vp::kSlotWords, true);
         case PlanKind::kPatch: return build_patch_plan(items, n, p);
         case PlanKind::kResize:
             return or_else(build_resize_plan(items, n, p), [&] { return build_resize_plan(items, n, p, true); });
@@ -1740,6 +1753,7 @@ void pack_plan(const Plan& p, uint8_t* base) {
 constexpr size_t kCopyPiece = 16384;
 constexpr size_t kCopyPieces = 4;
 constexpr int64_t kCopyRows = 32768;     // (upload_plan)
+constexpr int64_t kCopyLongRows = 72;    // (run_batch)
 
 // Whether that entry fills the computed tables on the host and copies them with
 // the rest: a kernel that computes them between the copy and the batch costs a
@@ -1749,10 +1763,17 @@ constexpr int64_t kCopyRows = 32768;     // (upload_plan)
 // 291), in one that goes in pieces no less.  Many tables stay on the device (20
 // ragged images 78 us, 338 with the host's), and so do those of small batches:
 // at 256 source pixels a word a batch streams for four times the host's work.
+// Tables that fit into the pieces that their plan takes anyway ride along too,
+// and save the launch (13 frames of 18x19 -> 32x32 21.1 -> 18.4 us a call); at
+// the price of one more piece they do not (an image of 110x121 -> 224x256 20.7
+// with the kernel, 21.5 with the piece).
 constexpr size_t kHostTableWords = 32768;
 constexpr int64_t kHostTablePixels = 256;
 
+size_t copy_pieces(size_t bytes) { return (bytes + kCopyPiece - 1) / kCopyPiece; }
+
 bool tables_on_host(const Plan& p) {
+    if (p.bytes <= kCopyPieces * kCopyPiece && copy_pieces(p.bytes) == copy_pieces(p.off_gen)) return true;
     if (p.off_gen <= kCopyPieces * kCopyPiece || p.gen_words > kHostTableWords) return false;
     int64_t pixels = 0;
     for (const vp::DevItem& d : p.items)
@@ -2021,6 +2042,20 @@ int32_t run_batch(bool patch_only, const vp_item* items, int32_t n_items, const 
         if (get_plan(PlanKind::kBatchSmall, items, n_items, &small) == VP_OK &&
             small->bytes <= static_cast<size_t>(vp::kNoAllocPlanBytes))
             plan = std::move(small);
+    }
+    // Frames of few rows: short units save up to 8 us of the GPU, which such a
+    // call does not wait for, and make more pieces of the copy, which it does
+    // (77 frames of 61x100 -> 64x96 24.6 -> 19.1 us a call, 500 28.7 -> 23.1, 200
+    // of 111x121 -> 96x96, units of 55 rows, 24.9 -> 26.1; patch 14, whose units
+    // take longer, 500 of 60x70 -> 56x56 22.5 -> 29.5).
+    const auto submissions = [](const Plan& q) {
+        return tables_on_host(q) ? copy_pieces(q.bytes) : copy_pieces(q.off_gen) + 1;
+    };
+    if (no_alloc && plan->items[0].patch == 16 && plan->long_unit_rows <= kCopyLongRows && submissions(*plan) > 1 &&
+        plan->off_gen <= kCopyPieces * kCopyPiece) {
+        std::shared_ptr<const Plan> longer;
+        if (get_plan(PlanKind::kBatchLong, items, n_items, &longer) == VP_OK && submissions(*longer) < submissions(*plan))
+            plan = std::move(longer);
     }
     const Plan& p = *plan;
     if (out_rows_capacity < p.total_rows)

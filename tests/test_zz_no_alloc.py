@@ -102,6 +102,10 @@ PLANS = [
     (2, 130, 170, 96, 128, 16, False),
     (8, 480, 854, 352, 640, 16, False),
     (48, 480, 854, 320, 576, 16, False),
+    (1, 18, 19, 32, 32, 16, False),     # the tables in the pieces that the plan takes anyway: x-first,
+    (1, 57, 17, 168, 56, 14, False),    # many slots,
+    (3, 400, 300, 32, 64, 16, False),   # the general kernel, without any,
+    (124, 52, 78, 64, 96, 16, False),   # two pieces
     (2600, 60, 90, 32, 64, 16, True),
     (4096, 47, 45, 96, 96, 16, True),
     (2600, 1100, 40, 32, 32, 16, True),
