@@ -606,7 +606,10 @@ __global__ __launch_bounds__(256) void patchify_kernel(PlanView plan, void* out,
 // more stores.  Measured, 512 frames of 336x588: float32 449 -> 262 us (5.8
 // TB/s; with 1, 3, 4, 6 windows 264, 271, 307, 311), bf16 253 -> 174 us (5.3
 // TB/s; 1, 2, 4, 6 windows 261, 204, 194, 201).  Loading window by window,
-// also where they lie side by side, took bf16 195 us.
+// also where they lie side by side, took bf16 195 us.  100 frames in bf16, us a
+// call against lane-by-lane stores: frames and rows that change from call to
+// call 67 -> 47; the same buffers again, all in the cache (where partial lines
+// cost nothing), 39 -> 43.
 template <int OUT_BF16>
 __global__ __launch_bounds__(256) void patchify14_kernel(PlanView plan, int block0, void* out, Norm norm) {
     constexpr int P = 14, NW = patch14_windows(OUT_BF16);
