@@ -272,9 +272,9 @@ int32_t vp_preprocess_batch(const vp_item* items, int32_t n_items, const float* 
  * The plan goes to a fixed array of device memory inside the library,
  * VP_NOALLOC_PLAN_BYTES (16 MiB) per device, held by every device the
  * library runs on until the process ends; it is copied there on `stream`
- * from pageable host memory (small plans in several copies, without their
- * filter tables, which a kernel computes there), and every kernel runs on
- * `stream` itself (no side streams).  The call allocates no device memory, creates no stream or
+ * from pageable host memory (small plans in up to four copies; filter tables
+ * that do not go with them are computed there by a kernel), and every kernel
+ * runs on `stream` itself (no side streams).  The call allocates no device memory, creates no stream or
  * event, and makes no hipMalloc, hipHostMalloc or hipFree call; its first
  * call on a device looks up that device's copy of the array.
  * All calls on one device share the array, which keeps the last call's plan:
